@@ -337,8 +337,9 @@ pccl_status pccl_get_link_usage(pccl_ctx *ctx, uint64_t *busy_ns, uint32_t n_bin
  *   clashes -- picks that lost a (destination, chunk) clash,
  *   windows -- synchronous look-ahead windows the device loop ran (the
  *              device's own step count: events inside one window of the
- *              smallest link time need no grid-wide exchange, so this is
- *              what bounds the matching time, not `events`).
+ *              smallest link time need no exchange between devices, so this
+ *              is what bounds the matching time, not `events`).  The kernel
+ *              that synchronises neighbours only counts empty windows too.
  * Any pointer may be NULL.
  */
 pccl_status pccl_get_stats(pccl_ctx *ctx, uint64_t *events, uint64_t *rounds,

@@ -34,6 +34,9 @@ struct pccl_ctx {
     uint32_t N = 0, S = 0, D = 0, L = 0;
     std::vector<uint32_t> src, dst, alpha, bw;
     std::vector<uint32_t> in_off, slot_link, slot_src, slot_cum, dest_pairs, rev;
+    std::vector<uint32_t> poll_off, poll;  // entries each device polls in the neighbour-stepped matcher
+    bool poll_built = false;               // the lists match the topology
+    uint32_t max_poll = 0, max_in = 0;     // most polled entries / in-links of one device
     std::vector<uint32_t> wave_dest;  // destination of (pass, wave) in the matching kernel
     std::vector<uint32_t> wave_part;  // its part when the destination is split over a workgroup's waves
     std::vector<uint32_t> split;      // split destinations, each taking one workgroup (heaviest first)
@@ -74,6 +77,10 @@ struct pccl_ctx {
     char *pin_img = nullptr;
     size_t pin_img_cap = 0;
     size_t img_off[16] = {}, img_len[16] = {};
+    // neighbour-stepped matching kernel: chosen by the plan (nbr_ok: not
+    // ruled out by a workspace only the windowed kernel fits in)
+    bool nbr_ok = true, nbr = false;
+    size_t nbr_lds = 0;            // LDS per workgroup
     uint64_t serial = 0;           // unique per context
     uint64_t static_call = 0;      // the static-scratch call whose result this context holds
     // workspace
@@ -168,6 +175,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     sz.resident = c->resident ? 1u : 0u;
     sz.sw_gate = c->sw_active && c->sw_gate ? 1u : 0u;
     sz.sw_nbt = c->sw_active ? c->sw_nbt : 0u;
+    sz.nbr = c->nbr ? 1u : 0u;
     const uint64_t hb = (uint64_t)sz.D * sz.Wp * sizeof(uint64_t);
     sz.hbytes = hb < (1ull << 31) ? (uint32_t)hb : 0u;
     const uint64_t nsort = std::max<uint64_t>(c->C, max_sends);
@@ -175,6 +183,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     if (sz.max_tiles == 0) sz.max_tiles = 1;
     const uint64_t L = c->L, D = c->D, N = c->N, C = c->C;
     Carver cv{base};
+    ly = Layout{};
     ly.ctl = cv.take<Control>(1);
     ly.lsrc = cv.take<uint32_t>(L);
     ly.ldst = cv.take<uint32_t>(L);
@@ -200,22 +209,40 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     ly.sp_dist = cv.take<uint64_t>(N * D);
     ly.sp_parent = cv.take<uint32_t>(N * D);
     ly.skey[0] = cv.take<uint64_t>(nsort);
-    ly.skey[1] = cv.take<uint64_t>(nsort);
+    // the neighbour-stepped matcher keeps its candidate rows and column list
+    // in the second sort buffers, which no sort uses between the priority
+    // order and the output: in-links * ceil(cols / 64) words per device
+    uint64_t cand = 0;
+    if (c->nbr) cand = std::min<uint64_t>(L * sz.W, (uint64_t)c->max_in * ((max_sends + 63) / 64) + L);
+    sz.cand_words = cand;
+    ly.skey[1] = cv.take<uint64_t>(std::max(nsort, cand));
     ly.sval[0] = cv.take<uint32_t>(nsort);
     ly.sval[1] = cv.take<uint32_t>(nsort);
     ly.hist = cv.take<uint32_t>(256ull * hist_stride(sz.max_tiles));
-    ly.holds = cv.take<uint64_t>(D * sz.Wp);
     ly.needs = cv.take<uint64_t>(D * sz.Wp);
-    ly.busy = cv.take<uint32_t>(L);
-    ly.infl = cv.take<uint32_t>(L);
-    ly.cur = cv.take<uint32_t>(L);
-    ly.lflags = cv.take<uint32_t>(L);
-    ly.lcnt = cv.take<uint32_t>(L);
-    ly.snap = cv.take<uint64_t>(3 * L);
     ly.dest_log = cv.take<unsigned long long>(D);
-    ly.xslot = cv.take<uint64_t>(2ull * MAX_MATCH_GRID * XSLOT_WORDS);
     ly.wave_dest = cv.take<uint32_t>(D + (uint64_t)MATCH_WAVES * MAX_MATCH_GRID);
     ly.wave_part = cv.take<uint32_t>(D + (uint64_t)MATCH_WAVES * MAX_MATCH_GRID);
+    if (c->nbr) {
+        ly.cand = ly.skey[1];
+        ly.col_rank = ly.sval[1];
+        ly.rank_src = ly.holder_cnt;  // the counts are read before the ranks are known
+        ly.need_pre = cv.take<uint32_t>(D * sz.Wp);
+        ly.pub = cv.take<uint64_t>(4 * L);
+        ly.cand_off = cv.take<uint64_t>(D);
+        ly.dest_cols = cv.take<uint32_t>(D);
+        ly.poll_off = cv.take<uint32_t>(D + 1);
+        ly.poll = cv.take<uint32_t>(c->poll.size());
+    } else {
+        ly.holds = cv.take<uint64_t>(D * sz.Wp);
+        ly.busy = cv.take<uint32_t>(L);
+        ly.infl = cv.take<uint32_t>(L);
+        ly.cur = cv.take<uint32_t>(L);
+        ly.lflags = cv.take<uint32_t>(L);
+        ly.lcnt = cv.take<uint32_t>(L);
+        ly.snap = cv.take<uint64_t>(3 * L);
+        ly.xslot = cv.take<uint64_t>(2ull * MAX_MATCH_GRID * XSLOT_WORDS);
+    }
     ly.out = cv.take<pccl_send>((c->op == PCCL_OP_ALLREDUCE ? 2 : 1) * max_sends);
     ly.sw = SwTab{};
     if (c->sw_active) {
@@ -482,6 +509,15 @@ pccl_status deal_switch_groups(pccl_ctx *c)
     return PCCL_OK;
 }
 
+// Heaviest devices first: most arrival pairs, then most in-links.
+void deal_order(const pccl_ctx *c, std::vector<uint32_t> &v)
+{
+    std::stable_sort(v.begin(), v.end(), [&](uint32_t a, uint32_t b) {
+        if (c->dest_pairs[a] != c->dest_pairs[b]) return c->dest_pairs[a] > c->dest_pairs[b];
+        return c->in_off[a + 1] - c->in_off[a] > c->in_off[b + 1] - c->in_off[b];
+    });
+}
+
 // Destinations of the matching kernel's waves.  Split destinations first,
 // each taking a whole workgroup (wave p is part p; parts past the last are
 // empty and only take part in the part barriers).  The others heaviest first
@@ -498,10 +534,7 @@ void deal_destinations(pccl_ctx *c)
     byweight.reserve(D);
     for (uint32_t v = 0; v < D; v++)
         if (!is_split[v]) byweight.push_back(v);
-    std::stable_sort(byweight.begin(), byweight.end(), [&](uint32_t a, uint32_t b) {
-        if (c->dest_pairs[a] != c->dest_pairs[b]) return c->dest_pairs[a] > c->dest_pairs[b];
-        return c->in_off[a + 1] - c->in_off[a] > c->in_off[b + 1] - c->in_off[b];
-    });
+    deal_order(c, byweight);
     // the `alone` heaviest unsplit destinations take wave 0 of the next
     // workgroups (one pass, by construction of the grid)
     const uint32_t hs = (uint32_t)c->split.size(), ha = c->alone, h = hs + ha;
@@ -565,7 +598,7 @@ pccl_status ensure_pinned(pccl_ctx *c, char **buf, size_t *cap, size_t bytes)
     return PCCL_OK;
 }
 
-constexpr int IMG_PARTS = 14;
+constexpr int IMG_PARTS = 16;
 
 // Parts of destination d for a split over the waves of a workgroup:
 // consecutive in-links, at most `target` links and MAX_PAIRS arrival pairs
@@ -588,6 +621,192 @@ std::vector<uint32_t> cut_parts(const pccl_ctx *c, uint32_t d, uint32_t target)
     }
     cut.push_back(n);
     return cut;
+}
+
+// Entries each device polls in the neighbour-stepped matcher: the in-links of
+// its in-links' sources (a chunk the device itself sends is none it needs),
+// and one in-link of every other device that reads its own entries.  Made
+// once per topology.
+void build_poll(pccl_ctx *c)
+{
+    const uint32_t D = c->D, L = c->L;
+    c->poll_built = true;
+    c->max_in = c->max_poll = 0;
+    uint64_t most = L;
+    for (uint32_t d = 0; d < D; d++) {
+        c->max_in = std::max(c->max_in, c->in_off[d + 1] - c->in_off[d]);
+        most += c->dest_pairs[d];
+    }
+    c->poll.clear();
+    if (c->max_in > MAX_IN_LINKS) {
+        c->max_poll = NONE32;
+        return;
+    }
+    std::vector<uint32_t> out_off(D + 2, 0), out_slot(L), polled(D, NONE32);
+    for (uint32_t sl = 0; sl < L; sl++) out_off[c->slot_src[sl] + 2]++;
+    for (uint32_t v = 0; v < D; v++) out_off[v + 2] += out_off[v + 1];
+    for (uint32_t sl = 0; sl < L; sl++) out_slot[out_off[c->slot_src[sl] + 1]++] = sl;
+    c->poll_off.resize(D + 1);
+    c->poll.resize(most);
+    uint32_t *q = c->poll.data();
+    const uint32_t *src = c->slot_src.data(), *in_off = c->in_off.data();
+    c->poll_off[0] = 0;
+    for (uint32_t d = 0; d < D; d++) {
+        uint32_t *const first = q;
+        for (uint32_t j = 0, sl = in_off[d]; sl < in_off[d + 1]; sl++, j++) {
+            const uint32_t s = src[sl];
+            for (uint32_t p = in_off[s]; p < in_off[s + 1]; p++)
+                if (src[p] != d) {
+                    *q++ = (p << 8) | j;
+                    polled[s] = d;
+                }
+        }
+        for (uint32_t k = out_off[d]; k < out_off[d + 1]; k++) {
+            const uint32_t sl = out_slot[k], v = c->dst[c->slot_link[sl]];
+            if (polled[v] != d) *q++ = (sl << 8) | 0xFFu;
+        }
+        c->max_poll = std::max<uint32_t>(c->max_poll, (uint32_t)(q - first));
+        c->poll_off[d + 1] = (uint32_t)(q - c->poll.data());
+    }
+    c->poll.resize(q - c->poll.data());
+}
+
+// The neighbour-stepped kernel's launch shape, when it takes the collective:
+// no switch model, one wavefront per device (at most 64 in-links and 512
+// polled entries), at most 2^18 chunks (two summary levels), all devices
+// resident with the live set and the summaries of the worst case (a device
+// that needs every chunk) in their share of LDS, and link times within a
+// factor of NBR_MAX_RATIO (its windows do not skip idle time).  It takes at
+// most one wave per SIMD: with several workgroups per compute unit (2,200
+// devices, three workgroups of three waves) a wait on a neighbour's entry ran
+// into the spin limit, which reading has not explained; such networks stay
+// with the windowed kernel.
+bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
+{
+    if (!c->nbr_ok || c->sw_active || c->D == 0 || c->L == 0 || c->C > NBR_MAX_CHUNKS) return false;
+    uint32_t tmax = 0;
+    for (uint32_t t : c->T) tmax = std::max(tmax, t);
+    if (tmax / NBR_MAX_RATIO > c->tmin) return false;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus <= 0)
+        return false;
+    // one workgroup per compute unit with all of its LDS, a wave per SIMD:
+    // as few waves as the devices need, the heavy devices alone when it fits
+    const uint32_t w = std::max<uint32_t>(1, (c->D + cus - 1) / cus);
+    if (w > MATCH_WAVES) return false;
+    if (!c->poll_built) build_poll(c);
+    if (c->max_in > MAX_IN_LINKS || c->max_poll > NBR_MAX_POLL) return false;
+    const bool wide = c->max_poll > 64, l3 = c->C > 4096;
+    const uint64_t W = words(c->C);
+    auto worst = [&](uint32_t n) { return (size_t)(W * 8 + n * 8 + (l3 ? n * (((W + 63) / 64) | 1) * 8 : 0) + 16); };
+    const size_t share = (lds_cu / w) & ~size_t(15);
+    uint32_t alone = w > 1 ? n_heavy : 0;
+    uint64_t grid = alone + ((uint64_t)c->D - alone + w - 1) / w;
+    if (grid > (uint64_t)cus) {
+        alone = 0;
+        grid = ((uint64_t)c->D + w - 1) / w;
+    }
+    if (grid > MAX_MATCH_GRID) return false;
+    // the worst case of the devices that share a workgroup, and of the
+    // others (the heavy devices come first in the deal)
+    uint32_t n_shared = 0;
+    {
+        std::vector<uint32_t> order(c->D);
+        std::iota(order.begin(), order.end(), 0u);
+        deal_order(c, order);
+        for (uint32_t i = alone; i < c->D; i++) n_shared = std::max(n_shared, c->in_off[order[i] + 1] - c->in_off[order[i]]);
+    }
+    if (worst(n_shared) > (w > 1 ? share : lds_cu) || worst(c->max_in) > (alone || w == 1 ? lds_cu : share)) return false;
+    if ((uint64_t)match_nbr_max_grid(c->device, (int)w, wide, l3, lds_cu) < grid) return false;
+    c->wpb = (int)w;
+    c->grid = (int)grid;
+    c->alone = alone;
+    c->resident = true;
+    c->mirror = false;
+    c->nbr_lds = lds_cu;
+    c->split.clear();
+    c->split_cuts.clear();
+    return true;
+}
+
+// The windowed kernel's launch shape: waves per workgroup, needs rows in
+// LDS, grid, split and lone destinations.
+pccl_status plan_windowed(pccl_ctx *c, const std::vector<uint32_t> &must, uint32_t need_w, uint32_t n_heavy, bool desc_ok,
+                          size_t lds_cu, uint64_t Wp)
+{
+    const uint32_t D1 = std::max<uint32_t>(c->D, 1);
+    // the grid for w waves per workgroup with at most gmax workgroups:
+    // split destinations take a workgroup each, heavy ones too if it fits,
+    // the others a wave each
+    auto shape = [&](uint32_t w, int gmax, int &grid, bool &resident, uint32_t &alone) {
+        const uint64_t ns = must.size();
+        alone = 0;
+        const uint64_t g0 = ns + ((uint64_t)c->D - ns + w - 1) / w;
+        if (g0 > (uint64_t)gmax) {
+            if (ns) return false;
+            grid = std::min<int>(gmax, (int)((D1 + w - 1) / w));
+            resident = (uint64_t)grid * w >= c->D;
+            return grid > 0;
+        }
+        grid = (int)std::max<uint64_t>(g0, 1);
+        resident = true;
+        if (w > 1 && n_heavy) {
+            const uint64_t g1 = ns + n_heavy + ((uint64_t)c->D - ns - n_heavy + w - 1) / w;
+            if (g1 <= (uint64_t)gmax) {
+                alone = n_heavy;
+                grid = (int)g1;
+            }
+        }
+        return true;
+    };
+    // waves per workgroup: as few as keep the grid near MATCH_TARGET_GRID
+    // workgroups, so that few destinations still spread over many compute
+    // units while many destinations do not make the window exchange poll
+    // too many slots; at least as many as the largest split destination has
+    // parts
+    int wpb = (int)std::min<uint32_t>(MATCH_WAVES, std::max<uint32_t>(1, (D1 + MATCH_TARGET_GRID - 1) / MATCH_TARGET_GRID));
+    wpb = std::max<int>(wpb, (int)need_w);
+    // needs rows in LDS: with as many of those waves as leave room for one
+    // row per wave, when every wave then owns one destination (or part)
+    c->mirror = false;
+    const size_t lds_static = match_static_lds(), row_bytes = (size_t)Wp * sizeof(uint64_t);
+    const bool spl = !must.empty();
+    int grid = 0;
+    bool resident = false;
+    uint32_t alone = 0;
+    for (int w = wpb; w >= (int)need_w && lds_static > 0 && desc_ok; w--) {
+        const size_t dyn = (size_t)w * row_bytes;
+        if (lds_static + dyn > lds_cu) continue;
+        const int gmax = std::min<int>(match_max_grid(c->device, w, true, dyn, spl), (int)MAX_MATCH_GRID);
+        if (gmax > 0 && shape((uint32_t)w, gmax, grid, resident, alone) && resident) {
+            wpb = w;
+            c->mirror = true;
+            break;
+        }
+    }
+    if (!c->mirror) {
+        const int gmax = std::min<int>(match_max_grid(c->device, wpb, false, 0, spl), (int)MAX_MATCH_GRID);
+        if (gmax <= 0) return fail(c, PCCL_EDEVICE, "matching kernel cannot be resident");
+        if (!shape((uint32_t)wpb, gmax, grid, resident, alone))
+            return fail(c, PCCL_EUNSUPPORTED, "device %u needs %u waves for its in-links and arrival pairs; the "
+                        "matching kernel cannot keep a workgroup per such device and a wave per other device "
+                        "resident (%d workgroups of %d waves at most)", must[0], need_w, gmax, wpb);
+    }
+    c->wpb = wpb;
+    c->grid = grid;
+    c->resident = resident;
+    c->alone = alone;
+    c->split = must;
+    c->split_cuts.clear();
+    for (uint32_t d : c->split) {
+        // the in-links spread evenly over the workgroup's waves (as few
+        // parts as fit when the pairs do not allow that)
+        const uint32_t n = c->in_off[d + 1] - c->in_off[d];
+        std::vector<uint32_t> cut = cut_parts(c, d, (n + wpb - 1) / wpb);
+        if (cut.size() - 1 > (size_t)wpb) cut = cut_parts(c, d, MAX_IN_LINKS);
+        c->split_cuts.push_back(cut);
+    }
+    return PCCL_OK;
 }
 
 // Everything that depends on the topology, the collective and the switch
@@ -632,79 +851,12 @@ pccl_status plan(pccl_ctx *c)
         for (uint32_t v = 0; v < c->D; v++)
             if (!is_must[v] && c->dest_pairs[v] > 0 && (uint64_t)c->dest_pairs[v] * c->D >= 4 * tot) n_heavy++;
     }
-    const uint32_t D1 = std::max<uint32_t>(c->D, 1);
-    // the grid for w waves per workgroup with at most gmax workgroups:
-    // split destinations take a workgroup each, heavy ones too if it fits,
-    // the others a wave each
-    auto shape = [&](uint32_t w, int gmax, int &grid, bool &resident, uint32_t &alone) {
-        const uint64_t ns = must.size();
-        alone = 0;
-        const uint64_t g0 = ns + ((uint64_t)c->D - ns + w - 1) / w;
-        if (g0 > (uint64_t)gmax) {
-            if (ns) return false;
-            grid = std::min<int>(gmax, (int)((D1 + w - 1) / w));
-            resident = (uint64_t)grid * w >= c->D;
-            return grid > 0;
-        }
-        grid = (int)std::max<uint64_t>(g0, 1);
-        resident = true;
-        if (w > 1 && n_heavy) {
-            const uint64_t g1 = ns + n_heavy + ((uint64_t)c->D - ns - n_heavy + w - 1) / w;
-            if (g1 <= (uint64_t)gmax) {
-                alone = n_heavy;
-                grid = (int)g1;
-            }
-        }
-        return true;
-    };
-    // waves per workgroup: as few as keep the grid near MATCH_TARGET_GRID
-    // workgroups, so that few destinations still spread over many compute
-    // units while many destinations do not make the window exchange poll
-    // too many slots; at least as many as the largest split destination has
-    // parts
-    int wpb = (int)std::min<uint32_t>(MATCH_WAVES, std::max<uint32_t>(1, (D1 + MATCH_TARGET_GRID - 1) / MATCH_TARGET_GRID));
-    wpb = std::max<int>(wpb, (int)need_w);
-    // needs rows in LDS: with as many of those waves as leave room for one
-    // row per wave, when every wave then owns one destination (or part)
-    c->mirror = false;
     int lds_cu = 0;
     HIP_OR_FAIL(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, c->device));
-    const size_t lds_static = match_static_lds(), row_bytes = (size_t)Wp * sizeof(uint64_t);
-    const bool spl = !must.empty();
-    int grid = 0;
-    bool resident = false;
-    uint32_t alone = 0;
-    for (int w = wpb; w >= (int)need_w && lds_static > 0 && desc_ok; w--) {
-        const size_t dyn = (size_t)w * row_bytes;
-        if (lds_static + dyn > (size_t)lds_cu) continue;
-        const int gmax = std::min<int>(match_max_grid(c->device, w, true, dyn, spl), (int)MAX_MATCH_GRID);
-        if (gmax > 0 && shape((uint32_t)w, gmax, grid, resident, alone) && resident) {
-            wpb = w;
-            c->mirror = true;
-            break;
-        }
-    }
-    if (!c->mirror) {
-        const int gmax = std::min<int>(match_max_grid(c->device, wpb, false, 0, spl), (int)MAX_MATCH_GRID);
-        if (gmax <= 0) return fail(c, PCCL_EDEVICE, "matching kernel cannot be resident");
-        if (!shape((uint32_t)wpb, gmax, grid, resident, alone))
-            return fail(c, PCCL_EUNSUPPORTED, "device %u needs %u waves for its in-links and arrival pairs; the "
-                        "matching kernel cannot keep a workgroup per such device and a wave per other device "
-                        "resident (%d workgroups of %d waves at most)", must[0], need_w, gmax, wpb);
-    }
-    c->wpb = wpb;
-    c->grid = grid;
-    c->resident = resident;
-    c->alone = alone;
-    c->split = must;
-    c->split_cuts.clear();
-    for (uint32_t d : c->split) {
-        // the in-links spread evenly over the workgroup's waves (as few
-        // parts as fit when the pairs do not allow that)
-        const uint32_t n = c->in_off[d + 1] - c->in_off[d];
-        std::vector<uint32_t> cut = cut_parts(c, d, (n + wpb - 1) / wpb);
-        if (cut.size() - 1 > (size_t)wpb) cut = cut_parts(c, d, MAX_IN_LINKS);
-        c->split_cuts.push_back(cut);
+    c->nbr = must.empty() && plan_nbr(c, (size_t)lds_cu, n_heavy);
+    if (!c->nbr) {
+        st = plan_windowed(c, must, need_w, n_heavy, desc_ok, (size_t)lds_cu, Wp);
+        if (st != PCCL_OK) return st;
     }
     deal_destinations(c);
     if (c->sw_active) {
@@ -724,7 +876,9 @@ pccl_status plan(pccl_ctx *c)
         {c->wave_dest.data(), 4ull * c->wave_dest.size()},
         {c->wave_part.data(), 4ull * c->wave_part.size()},
         {c->gmask.data(), 8ull * c->gmask.size()},
-        {c->swt.data(), c->sw_active ? 4ull * c->swt.size() : 0ull}};
+        {c->swt.data(), c->sw_active ? 4ull * c->swt.size() : 0ull},
+        {c->poll_off.data(), c->nbr ? 4ull * c->poll_off.size() : 0ull},
+        {c->poll.data(), c->nbr ? 4ull * c->poll.size() : 0ull}};
     size_t total = 0;
     for (int k = 0; k < IMG_PARTS; k++) {
         c->img_off[k] = total;
@@ -748,6 +902,20 @@ pccl_status bind_workspace(pccl_ctx *c, char *ptr, size_t bytes, uint64_t ms, hi
     Sizes sz{};
     size_t need = 0;
     carve(c, nullptr, ms, ly, sz, need);
+    if (bytes < need && c->nbr) {
+        // the windowed kernel's layout may still fit (it lacks the column
+        // and poll tables): plan for that kernel instead
+        c->nbr = false;
+        size_t alt = 0;
+        carve(c, nullptr, ms, ly, sz, alt);
+        c->nbr = true;
+        if (bytes >= alt) {
+            c->nbr_ok = false;
+            const pccl_status ps = plan(c);
+            if (ps != PCCL_OK) return ps;
+            need = alt;
+        }
+    }
     if (bytes < need) {
         if (is_static)
             return fail(c, PCCL_ENOMEM, "the library's static scratch holds %zu bytes, this collective needs %zu "
@@ -907,6 +1075,7 @@ pccl_status pccl_load_topology(pccl_ctx *c, uint32_t n_npus, uint32_t n_switches
     c->S = n_switches;
     c->D = D;
     c->L = L;
+    c->poll_built = false;
     c->src.assign(link_src, link_src + L);
     c->dst.assign(link_dst, link_dst + L);
     c->alpha.assign(alpha_ns, alpha_ns + L);
@@ -989,6 +1158,7 @@ pccl_status pccl_set_collective(pccl_ctx *c, uint32_t n_chunks, uint64_t chunk_b
     c->T.swap(T);
     c->slot_time.swap(slot_time);
     c->tmin = c->L ? tmin : 1;
+    c->nbr_ok = true;
     c->have_coll = true;
     return plan(c);
     GUARD_END(c)
@@ -1010,6 +1180,7 @@ pccl_status pccl_set_switch_model(pccl_ctx *c, uint32_t n_switches, const uint32
         any = any || c->sw_buf[i] || c->sw_uni[i];
     }
     c->sw_model = any;
+    c->nbr_ok = true;
     c->sw_built = c->sw_active = false;
     c->have_ws = c->uploaded = c->have_result = false;
     return c->have_coll ? plan(c) : PCCL_OK;
@@ -1054,7 +1225,8 @@ static pccl_status upload(pccl_ctx *c)
     hipStream_t st = c->stream;
     void *dst[IMG_PARTS] = {ly.lsrc,      ly.ldst,     ly.ltime,      ly.lrev,      ly.in_off,
                             ly.slot_link, ly.slot_src, ly.slot_time,  ly.slot_cum,  ly.dest_pairs,
-                            ly.wave_dest, ly.wave_part, ly.group_masks, const_cast<uint32_t *>(ly.sw.grp)};
+                            ly.wave_dest, ly.wave_part, ly.group_masks, const_cast<uint32_t *>(ly.sw.grp),
+                            ly.poll_off,  ly.poll};
     for (int k = 0; k < IMG_PARTS; k++)
         if (c->img_len[k])
             HIP_OR_FAIL(c, hipMemcpyAsync(dst[k], c->pin_img + c->img_off[k], c->img_len[k], hipMemcpyHostToDevice, st));
@@ -1120,6 +1292,8 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
         HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
     } else if (c->sw_active) {
         HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, c->sw_grid));
+    } else if (c->nbr) {
+        HIP_OR_FAIL(c, launch_match_nbr(c->ly, c->sz, st, c->grid, c->wpb, c->max_poll > 64, c->C > 4096, c->nbr_lds));
     } else {
         HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
     }

@@ -40,6 +40,11 @@ constexpr uint32_t SW_MAX_SRC_IN = 64;   // in-links of one source of a group li
 constexpr uint32_t SW_MAX_POOL = 1024;   // buffer places of a group's limited switches
 constexpr uint8_t SW_NONE8 = 0xFF;
 
+// Neighbour-stepped matching kernel envelope (one wavefront per device).
+constexpr uint32_t NBR_MAX_CHUNKS = 1u << 18;  // two summary levels over rows of 64-bit words
+constexpr uint32_t NBR_MAX_POLL = 512;         // entries one device polls per window
+constexpr uint32_t NBR_MAX_RATIO = 64;         // largest link time over the smallest
+
 // Status codes mirrored from the public header.
 enum : uint32_t {
     ST_OK = 0, ST_EINVAL = 1, ST_EUNREACHABLE = 2, ST_ERANGE = 3, ST_ENOMEM = 4,
@@ -158,6 +163,15 @@ struct Layout {
     uint64_t *xslot;          // [2 * MAX_MATCH_GRID * XSLOT_WORDS] window exchange slots of the matching kernel
     uint32_t *wave_dest;      // [D + MATCH_WAVES * MAX_MATCH_GRID] destination of (pass, wave), NONE32 if none
     uint32_t *wave_part;      // [same] for a split destination: parts << 24 | part << 16 | first link << 8 | links; 0 = whole
+    // neighbour-stepped matching kernel
+    uint64_t *pub;            // [4 * L] by slot: published link entries, four windows alternating
+    uint64_t *cand;           // candidate rows: per device its in-links' rows of ceil(cols / 64) words, from cand_off
+    uint64_t *cand_off;       // [D]
+    uint32_t *need_pre;       // [D * Wp] columns of the device before each word of its needs row
+    uint32_t *col_rank;       // chunk rank of every column, device d's from its send-log segment start
+    uint32_t *dest_cols;      // [D] columns (chunks the device needs)
+    uint32_t *rank_src;       // [C] priority position -> holder
+    uint32_t *poll_off, *poll; // [D+1], entries a device polls: slot << 8 | in-link fed (0xFF none)
     SwTab sw;                 // switch-model tables (null pointers without a switch model)
     // output
     void *out;                // pccl_send [2 * max_sends]
@@ -175,6 +189,8 @@ struct Sizes {
     uint32_t hbytes;  // bytes of the holds bitmap (D rows of Wp words) when below 2 GiB, else 0
     uint32_t resident; // every wave of the matching kernel owns one destination (or part) for the whole run
     uint32_t sw_gate;  // both matching kernels are queued; Control::sw_binds picks the one that runs
+    uint64_t cand_words;  // capacity of Layout::cand
+    uint32_t nbr;      // the neighbour-stepped matching kernel runs
     uint32_t sw_nbt;   // limited-switch rows of the switch tables (0: no switch model or no limited switch)
 };
 
@@ -189,6 +205,11 @@ hipError_t launch_match(const Layout &ly, const Sizes &sz, hipStream_t st, int g
                         bool split);
 int match_max_grid(int device, int waves_per_block, bool mirror, size_t dyn_lds, bool split);
 size_t match_static_lds();  // static LDS bytes of the matching kernel
+// wide: some device polls more than 64 entries; l3: more than 4,096 chunks;
+// dyn_lds bytes of LDS per workgroup
+hipError_t launch_match_nbr(const Layout &ly, const Sizes &sz, hipStream_t st, int grid, int waves_per_block, bool wide,
+                            bool l3, size_t dyn_lds);
+int match_nbr_max_grid(int device, int waves_per_block, bool wide, bool l3, size_t dyn_lds);
 hipError_t launch_match_sw(const Layout &ly, const Sizes &sz, hipStream_t st, int grid);
 // sets Control::sw_binds when two out-neighbours of one of the n_uni unicast
 // switches need the same chunk

@@ -284,6 +284,8 @@ __global__ void k_rank(Layout ly, Sizes sz)
     const uint32_t c = ly.sval[ly.ctl->sort_cur][r];
     ly.order[r] = c;
     ly.rank[c] = (uint32_t)r;
+    // (the counts of the array it shares are no longer read)
+    if (sz.nbr) ly.rank_src[r] = ly.chunk_src[c];
 }
 
 __global__ void k_holds(Layout ly, Sizes sz)
@@ -410,6 +412,111 @@ __global__ void k_init_match(Layout ly, Sizes sz)
     }
 }
 
+// Neighbour-stepped matcher: the columns of device d are the chunks it needs
+// in priority order.  Their number before each word of the needs row, and in
+// all (one workgroup per device, a thread per run of adjacent words).
+__global__ void __launch_bounds__(256) k_need_prefix(Layout ly, Sizes sz)
+{
+    __shared__ uint32_t part[256];
+    const uint32_t d = blockIdx.x, tid = threadIdx.x;
+    const uint32_t W = ly.ctl->error ? 0u : (uint32_t)sz.W;
+    const uint64_t *row = ly.needs + (uint64_t)d * sz.Wp;
+    uint32_t *pre = ly.need_pre + (uint64_t)d * sz.Wp;
+    const uint32_t per = (W + 255u) / 256u, lo = min(tid * per, W), hi = min(lo + per, W);
+    uint32_t c = 0;
+    for (uint32_t w = lo; w < hi; w++) c += (uint32_t)__popcll(row[w]);
+    part[tid] = c;
+    __syncthreads();
+    for (uint32_t off = 1; off < 256; off <<= 1) {
+        const uint32_t x = tid >= off ? part[tid - off] : 0u;
+        __syncthreads();
+        part[tid] += x;
+        __syncthreads();
+    }
+    uint32_t run = part[tid] - c;
+    for (uint32_t w = lo; w < hi; w++) {
+        pre[w] = run;
+        run += (uint32_t)__popcll(row[w]);
+    }
+    if (tid == 255) ly.dest_cols[d] = part[255];
+}
+
+// Send-log segments (a device's transfers are its columns) and candidate rows
+// of all devices: exclusive prefixes of cols and in-links * ceil(cols / 64).
+__global__ void __launch_bounds__(1024) k_nbr_offsets(Layout ly, Sizes sz, uint64_t cand_words)
+{
+    __shared__ unsigned long long pl[1024], pc[1024];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t per = (sz.D + 1023) / 1024;
+    const uint32_t lo = min(tid * per, sz.D), hi = min(lo + per, sz.D);
+    unsigned long long s = 0, r = 0;
+    for (uint32_t v = lo; v < hi; v++) {
+        const uint32_t m = ly.dest_cols[v];
+        s += m;
+        r += (unsigned long long)(ly.in_off[v + 1] - ly.in_off[v]) * ((m + 63u) >> 6);
+    }
+    pl[tid] = s;
+    pc[tid] = r;
+    __syncthreads();
+    for (uint32_t off = 1; off < 1024; off <<= 1) {
+        const unsigned long long x = tid >= off ? pl[tid - off] : 0, y = tid >= off ? pc[tid - off] : 0;
+        __syncthreads();
+        pl[tid] += x;
+        pc[tid] += y;
+        __syncthreads();
+    }
+    unsigned long long rl = pl[tid] - s, rc = pc[tid] - r;
+    for (uint32_t v = lo; v < hi; v++) {
+        const uint32_t m = ly.dest_cols[v];
+        ly.dest_log[v] = rl;
+        ly.cand_off[v] = rc;
+        rl += m;
+        rc += (unsigned long long)(ly.in_off[v + 1] - ly.in_off[v]) * ((m + 63u) >> 6);
+    }
+    if (tid == 1023) {
+        Control *ctl = ly.ctl;
+        ctl->needs_total = pl[1023];
+        if (!ctl->error && pl[1023] > ctl->max_sends)
+            record_error(ctl, ST_ENOMEM, (uint32_t)(pl[1023] >> 32), (uint32_t)pl[1023], 0);
+        else if (!ctl->error && pc[1023] > cand_words)
+            record_error(ctl, ST_EINTERNAL, 4, 0, 0);
+    }
+}
+
+// Column lists and initial candidate rows (one workgroup per device): a
+// thread per needs word writes the ranks of its columns, then a thread per
+// column looks up the chunk's holder and, when that is the source of an
+// in-link, sets the column's bit in the link's row.
+__global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
+{
+    __shared__ uint8_t link_of[MAX_DEVICES_SP];  // in-link of d whose source is the device, 0xFF none
+    const uint32_t d = blockIdx.x, tid = threadIdx.x;
+    // the published entries start with a window tag no early window uses
+    for (uint64_t i = (uint64_t)d * 1024u + tid; i < 4ull * sz.L; i += (uint64_t)gridDim.x * 1024u) ly.pub[i] = NONE64 >> 1;
+    if (ly.ctl->error) return;
+    const uint32_t M = ly.dest_cols[d];
+    if (M == 0) return;
+    const uint32_t base = ly.in_off[d], n = ly.in_off[d + 1] - base, mw = (M + 63u) >> 6;
+    unsigned long long *rows = (unsigned long long *)(ly.cand + ly.cand_off[d]);
+    uint32_t *rank = ly.col_rank + ly.dest_log[d];
+    const uint64_t *need = ly.needs + (uint64_t)d * sz.Wp;
+    const uint32_t *pre = ly.need_pre + (uint64_t)d * sz.Wp;
+    for (uint32_t v = tid; v < sz.D; v += 1024) link_of[v] = 0xFFu;
+    for (uint32_t i = tid; i < n * mw; i += 1024) rows[i] = 0ull;
+    for (uint32_t w = tid; w < (uint32_t)sz.W; w += 1024) {
+        uint32_t c = pre[w];
+        for (uint64_t x = need[w]; x; x &= x - 1) rank[c++] = w * 64u + (uint32_t)__builtin_ctzll(x);
+    }
+    __syncthreads();
+    for (uint32_t j = tid; j < n; j += 1024) link_of[ly.slot_src[base + j]] = (uint8_t)j;
+    __syncthreads();
+    for (uint32_t c = tid; c < M; c += 1024) {
+        const uint32_t s = ly.rank_src[rank[c]];
+        const uint32_t j = s != NONE32 ? link_of[s] : 0xFFu;
+        if (j != 0xFFu) atomicOr(&rows[(uint64_t)j * mw + (c >> 6)], 1ull << (c & 63u));
+    }
+}
+
 inline uint32_t blocks_for(uint64_t n, uint32_t t) { return (uint32_t)((n + t - 1) / t); }
 
 }  // namespace
@@ -427,7 +534,7 @@ hipError_t launch_setup(const Layout &ly, const Sizes &sz, const uint64_t *pre, 
     }
     k_fill32<<<blocks_for(sz.N, T), T, 0, st>>>(ly.src_index, sz.N, 0);
     const uint64_t bm = (uint64_t)sz.D * sz.Wp;
-    k_fill64<<<min(blocks_for(bm, T), 8192u), T, 0, st>>>(ly.holds, bm, 0);
+    if (!sz.nbr) k_fill64<<<min(blocks_for(bm, T), 8192u), T, 0, st>>>(ly.holds, bm, 0);
     k_fill64<<<min(blocks_for(bm, T), 8192u), T, 0, st>>>(ly.needs, bm, 0);
     const dim3 gw(blocks_for(sz.W ? sz.W : 1, T), sz.N);
     if (sz.W) k_conditions<<<gw, T, 0, st>>>(ly, sz, pre, post, chunk_group);
@@ -441,9 +548,15 @@ hipError_t launch_setup(const Layout &ly, const Sizes &sz, const uint64_t *pre, 
         if (e != hipSuccess) return e;
         k_key_ties<<<blocks_for(C, T), T, 0, st>>>(ly, sz, seed);
         k_rank<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
-        k_holds<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
+        if (!sz.nbr) k_holds<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
     }
     if (sz.W) k_needs<<<gw, T, 0, st>>>(ly, sz, pre, post);
+    if (sz.nbr) {
+        k_need_prefix<<<sz.D, 256, 0, st>>>(ly, sz);
+        k_nbr_offsets<<<1, 1024, 0, st>>>(ly, sz, sz.cand_words);
+        k_columns<<<sz.D, 1024, 0, st>>>(ly, sz);
+        return hipGetLastError();
+    }
     if (sz.sw_nbt && C) k_adm_counts<<<dim3(blocks_for(C, T), sz.sw_nbt), T, 0, st>>>(ly, sz);
     if (sz.L) k_link_counts<<<blocks_for(sz.L, 4), 256, 0, st>>>(ly, sz);
     k_needs_count<<<sz.D, 256, 0, st>>>(ly, sz);

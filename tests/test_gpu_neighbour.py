@@ -1,0 +1,84 @@
+"""GPU parity of the neighbour-stepped matching kernel where its dispatch and
+its tables change: whole schedules and statistics against the CPU oracle
+(integers, so equality is exact)."""
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2606_07019_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _generic(name, topo, n_chunks, chunk_bytes, max_dests, seed):
+    """Random sources and 1..max_dests destinations over all NPUs."""
+    rng = W.SplitMix64(seed)
+    n, src, dests = topo.n_npus, [], []
+    for _ in range(n_chunks):
+        s, k = rng.rand(n), 1 + rng.rand(max_dests)
+        src.append(s)
+        dests.append(sorted({rng.rand(n) for _ in range(k)} - {s}))
+    return W.Workload(name, topo, W.collective_from_lists(n, n_chunks, chunk_bytes, src, dests, [range(n)]), seed)
+
+
+def _digraph(n, degree, seed):
+    rng = W.SplitMix64(seed)
+    pairs = W.random_digraph(n, degree, rng)
+    return W.make_topology(n, 0, pairs, [300 + rng.rand(900) for _ in pairs], [(20, 35, 90)[rng.rand(3)] for _ in pairs])
+
+
+def _complete(n):
+    return W.make_topology(n, 0, [(i, j) for i in range(n) for j in range(n) if i != j], 500, 50)
+
+
+def _slow_link(ratio):
+    """An 8-ring whose links take 1,000 ns but one pair that takes ratio times
+    as long: the kernel is chosen up to a factor of 64."""
+    pairs = [(i, (i + s) % 8) for i in range(8) for s in (1, 7)]
+    alpha = [900 + (ratio - 1) * 1000 * ({a, b} == {3, 4}) for a, b in pairs]
+    return W.make_topology(8, 0, pairs, alpha, 1)
+
+
+CASES = {
+    # one-way links: readers that are no sources (their progress is polled, not their entries)
+    "one-way ring 5": lambda: _generic("ring5", W.ring(5, bidirectional=False), 40, 4096, 3, 1),
+    "one-way ring 70": lambda: _generic("ring70", W.ring(70, bidirectional=False), 300, 4096, 4, 2),
+    "digraph 60 degree 2": lambda: _generic("digraph60", _digraph(60, 2, 3), 500, 20000, 6, 3),
+    "digraph 300 degree 3": lambda: _generic("digraph300", _digraph(300, 3, 4), 3000, 20000, 5, 4),
+    # 56 and 72 polled entries per device: one and several per lane
+    "complete 9": lambda: _generic("complete9", _complete(9), 200, 10000, 8, 5),
+    "complete 10": lambda: _generic("complete10", _complete(10), 200, 10000, 9, 6),
+    # 64 and 65 chunks (one and two row words), 4,096 and 4,160 (one and two summary levels), all needed everywhere
+    "ring 4 x 16": lambda: W.Workload("r4", W.ring(4), W.all_gather(4, range(4), 16, 1 << 14), 7),
+    "ring 5 x 13": lambda: W.Workload("r5", W.ring(5), W.all_gather(5, range(5), 13, 1 << 14), 8),
+    "ring 8 x 512": lambda: W.Workload("r8", W.ring(8), W.all_gather(8, range(8), 512, 1 << 14), 9),
+    "ring 8 x 520": lambda: W.Workload("r8b", W.ring(8), W.all_gather(8, range(8), 520, 1 << 14), 10),
+    # link times a factor 64 and 65 apart
+    "slow link 64": lambda: _generic("slow64", _slow_link(64), 60, 100, 4, 11),
+    "slow link 65": lambda: _generic("slow65", _slow_link(65), 60, 100, 4, 12),
+    # four waves per workgroup, and one device too many for them
+    "mesh 32x32": lambda: _generic("mesh1024", W.mesh2d(32, 32), 600, 4096, 6, 13),
+    "mesh 41x25": lambda: _generic("mesh1025", W.mesh2d(41, 25), 600, 4096, 6, 14),
+    # switches with 16,128 columns: their column list stays in device memory
+    "rail 64x4": lambda: W.Workload("rail64x4", W.switch2level(64, 4), W.a2a_bitmaps(256, 8192), 15),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_neighbour_stepped_parity(name):
+    from paper_2606_07019_amd.pccl import Synthesizer
+    print(f"[neighbour] {name}", flush=True)
+    wl = CASES[name]()
+    ref = O.run_workload(wl)
+    assert ref.status == 0, ref.message
+    s = Synthesizer(wl.topo, wl.coll, tie_seed=wl.tie_seed)
+    try:
+        for _ in range(2):   # the second run starts from the first one's tables
+            s.synthesize()
+            np.testing.assert_array_equal(s.schedule(), ref.sends)
+            assert s.collective_time == ref.collective_time
+            st = s.stats()
+            assert [st[k] for k in ("events", "rounds", "clashes")] == [ref.stats[k] for k in ("events", "rounds", "clashes")]
+    finally:
+        s.close()
