@@ -34,6 +34,7 @@ struct pccl_ctx {
     uint32_t N = 0, S = 0, D = 0, L = 0;
     std::vector<uint32_t> src, dst, alpha, bw;
     std::vector<uint32_t> in_off, slot_link, slot_src, slot_cum, dest_pairs, rev;
+    std::vector<uint32_t> pub_off;         // where each device's published link entries start
     std::vector<uint32_t> poll_off, poll;  // entries each device polls in the neighbour-stepped matcher
     bool poll_built = false;               // the lists match the topology
     uint32_t max_poll = 0, max_in = 0;     // most polled entries / in-links of one device
@@ -76,11 +77,12 @@ struct pccl_ctx {
     // built by the plan; IMG_PARTS pieces at img_off[k], img_len[k] bytes
     char *pin_img = nullptr;
     size_t pin_img_cap = 0;
-    size_t img_off[16] = {}, img_len[16] = {};
+    size_t img_off[17] = {}, img_len[17] = {};
     // neighbour-stepped matching kernel: chosen by the plan (nbr_ok: not
     // ruled out by a workspace only the windowed kernel fits in)
     bool nbr_ok = true, nbr = false;
     size_t nbr_lds = 0;            // LDS per workgroup
+    uint32_t nbr_spread = 1;       // every how many workgroups of the launch one holds devices
     uint64_t serial = 0;           // unique per context
     uint64_t static_call = 0;      // the static-scratch call whose result this context holds
     // workspace
@@ -228,7 +230,9 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
         ly.col_rank = ly.sval[1];
         ly.rank_src = ly.holder_cnt;  // the counts are read before the ranks are known
         ly.need_pre = cv.take<uint32_t>(D * sz.Wp);
-        ly.pub = cv.take<uint64_t>(4 * L);
+        sz.pub_n = c->pub_off[D];
+        ly.pub = cv.take<uint64_t>(4ull * sz.pub_n);
+        ly.pub_off = cv.take<uint32_t>(D + 1);
         ly.cand_off = cv.take<uint64_t>(D);
         ly.dest_cols = cv.take<uint32_t>(D);
         ly.poll_off = cv.take<uint32_t>(D + 1);
@@ -598,7 +602,7 @@ pccl_status ensure_pinned(pccl_ctx *c, char **buf, size_t *cap, size_t bytes)
     return PCCL_OK;
 }
 
-constexpr int IMG_PARTS = 16;
+constexpr int IMG_PARTS = 17;
 
 // Parts of destination d for a split over the waves of a workgroup:
 // consecutive in-links, at most `target` links and MAX_PAIRS arrival pairs
@@ -642,6 +646,11 @@ void build_poll(pccl_ctx *c)
         c->max_poll = NONE32;
         return;
     }
+    // a device's entries lie in 128-byte lines of their own
+    c->pub_off.resize(D + 1);
+    c->pub_off[0] = 0;
+    for (uint32_t d = 0; d < D; d++)
+        c->pub_off[d + 1] = c->pub_off[d] + ((c->in_off[d + 1] - c->in_off[d] + 15u) & ~15u);
     std::vector<uint32_t> out_off(D + 2, 0), out_slot(L), polled(D, NONE32);
     for (uint32_t sl = 0; sl < L; sl++) out_off[c->slot_src[sl] + 2]++;
     for (uint32_t v = 0; v < D; v++) out_off[v + 2] += out_off[v + 1];
@@ -655,15 +664,15 @@ void build_poll(pccl_ctx *c)
         uint32_t *const first = q;
         for (uint32_t j = 0, sl = in_off[d]; sl < in_off[d + 1]; sl++, j++) {
             const uint32_t s = src[sl];
-            for (uint32_t p = in_off[s]; p < in_off[s + 1]; p++)
+            for (uint32_t p = in_off[s], x = c->pub_off[s]; p < in_off[s + 1]; p++, x++)
                 if (src[p] != d) {
-                    *q++ = (p << 8) | j;
+                    *q++ = (x << 8) | j;
                     polled[s] = d;
                 }
         }
         for (uint32_t k = out_off[d]; k < out_off[d + 1]; k++) {
             const uint32_t sl = out_slot[k], v = c->dst[c->slot_link[sl]];
-            if (polled[v] != d) *q++ = (sl << 8) | 0xFFu;
+            if (polled[v] != d) *q++ = ((c->pub_off[v] + sl - in_off[v]) << 8) | 0xFFu;
         }
         c->max_poll = std::max<uint32_t>(c->max_poll, (uint32_t)(q - first));
         c->poll_off[d + 1] = (uint32_t)(q - c->poll.data());
@@ -690,34 +699,54 @@ bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus <= 0)
         return false;
-    // one workgroup per compute unit with all of its LDS, a wave per SIMD:
-    // as few waves as the devices need, the heavy devices alone when it fits
-    const uint32_t w = std::max<uint32_t>(1, (c->D + cus - 1) / cus);
-    if (w > MATCH_WAVES) return false;
+    if (c->D > (uint32_t)cus * MATCH_WAVES) return false;
     if (!c->poll_built) build_poll(c);
     if (c->max_in > MAX_IN_LINKS || c->max_poll > NBR_MAX_POLL) return false;
-    const bool wide = c->max_poll > 64, l3 = c->C > 4096;
+    const bool l3 = c->C > 4096;
     const uint64_t W = words(c->C);
     auto worst = [&](uint32_t n) { return (size_t)(W * 8 + n * 8 + (l3 ? n * (((W + 63) / 64) | 1) * 8 : 0) + 16); };
-    const size_t share = (lds_cu / w) & ~size_t(15);
-    uint32_t alone = w > 1 ? n_heavy : 0;
-    uint64_t grid = alone + ((uint64_t)c->D - alone + w - 1) / w;
-    if (grid > (uint64_t)cus) {
-        alone = 0;
-        grid = ((uint64_t)c->D + w - 1) / w;
-    }
-    if (grid > MAX_MATCH_GRID) return false;
-    // the worst case of the devices that share a workgroup, and of the
-    // others (the heavy devices come first in the deal)
-    uint32_t n_shared = 0;
-    {
-        std::vector<uint32_t> order(c->D);
-        std::iota(order.begin(), order.end(), 0u);
-        deal_order(c, order);
+    if ((uint64_t)match_nbr_max_grid(c->device, 1, lds_cu) < (uint64_t)cus) return false;
+    // one workgroup per compute unit with all of its LDS, a wave per SIMD: as
+    // few waves as the devices need, the heavy devices alone when it fits.
+    // Devices that fit the compute units of one XCD are put there (every
+    // NBR_XCDS-th workgroup of the launch, the others end at once): a store
+    // on one XCD is seen by a load on the same one in 0.52-0.60 us, on
+    // another in 0.72-0.93 us, and that is most of a window.
+    uint32_t w = 0, alone = 0, spread = 0;
+    uint64_t grid = 0;
+    std::vector<uint32_t> order;
+    for (uint32_t sp : {NBR_XCDS, 1u}) {
+        const uint32_t room = (uint32_t)cus / sp;
+        if (c->D > room * MATCH_WAVES) continue;
+        w = std::max<uint32_t>(1, (c->D + room - 1) / room);
+        alone = w > 1 ? n_heavy : 0;
+        grid = alone + ((uint64_t)c->D - alone + w - 1) / w;
+        if (grid > room) {
+            alone = 0;
+            grid = ((uint64_t)c->D + w - 1) / w;
+        }
+        if (grid * sp > MAX_MATCH_GRID) continue;
+        // the worst case of the devices that share a workgroup, and of the
+        // others (the heavy devices come first in the deal)
+        if (order.empty()) {
+            order.resize(c->D);
+            std::iota(order.begin(), order.end(), 0u);
+            deal_order(c, order);
+        }
+        uint32_t n_shared = 0;
         for (uint32_t i = alone; i < c->D; i++) n_shared = std::max(n_shared, c->in_off[order[i] + 1] - c->in_off[order[i]]);
+        const size_t share = w > 1 ? (lds_cu / w) & ~size_t(15) : lds_cu;
+        if (worst(n_shared) > share || worst(c->max_in) > (alone ? lds_cu : share)) continue;
+        // (the tables of a device grow with the chunks: with a share of less
+        // than a byte per chunk some leave LDS, which costs more than the
+        // nearer neighbours give: 4x4x4 grid, 131,072 chunks, 10.4 ms spread
+        // over all XCDs, 10.6 ms on one; 8x8 mesh, 32,768 chunks, 3.2 and 2.9)
+        if (sp > 1 && share < c->C) continue;
+        spread = sp;
+        break;
     }
-    if (worst(n_shared) > (w > 1 ? share : lds_cu) || worst(c->max_in) > (alone || w == 1 ? lds_cu : share)) return false;
-    if ((uint64_t)match_nbr_max_grid(c->device, (int)w, wide, l3, lds_cu) < grid) return false;
+    if (!spread) return false;
+    c->nbr_spread = spread;
     c->wpb = (int)w;
     c->grid = (int)grid;
     c->alone = alone;
@@ -878,7 +907,8 @@ pccl_status plan(pccl_ctx *c)
         {c->gmask.data(), 8ull * c->gmask.size()},
         {c->swt.data(), c->sw_active ? 4ull * c->swt.size() : 0ull},
         {c->poll_off.data(), c->nbr ? 4ull * c->poll_off.size() : 0ull},
-        {c->poll.data(), c->nbr ? 4ull * c->poll.size() : 0ull}};
+        {c->poll.data(), c->nbr ? 4ull * c->poll.size() : 0ull},
+        {c->pub_off.data(), c->nbr ? 4ull * c->pub_off.size() : 0ull}};
     size_t total = 0;
     for (int k = 0; k < IMG_PARTS; k++) {
         c->img_off[k] = total;
@@ -1226,7 +1256,7 @@ static pccl_status upload(pccl_ctx *c)
     void *dst[IMG_PARTS] = {ly.lsrc,      ly.ldst,     ly.ltime,      ly.lrev,      ly.in_off,
                             ly.slot_link, ly.slot_src, ly.slot_time,  ly.slot_cum,  ly.dest_pairs,
                             ly.wave_dest, ly.wave_part, ly.group_masks, const_cast<uint32_t *>(ly.sw.grp),
-                            ly.poll_off,  ly.poll};
+                            ly.poll_off,  ly.poll,     ly.pub_off};
     for (int k = 0; k < IMG_PARTS; k++)
         if (c->img_len[k])
             HIP_OR_FAIL(c, hipMemcpyAsync(dst[k], c->pin_img + c->img_off[k], c->img_len[k], hipMemcpyHostToDevice, st));
@@ -1293,7 +1323,7 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
     } else if (c->sw_active) {
         HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, c->sw_grid));
     } else if (c->nbr) {
-        HIP_OR_FAIL(c, launch_match_nbr(c->ly, c->sz, st, c->grid, c->wpb, c->max_poll > 64, c->C > 4096, c->nbr_lds));
+        HIP_OR_FAIL(c, launch_match_nbr(c->ly, c->sz, st, c->grid, c->wpb, c->nbr_lds, c->nbr_spread));
     } else {
         HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
     }

@@ -42,6 +42,8 @@ constexpr uint8_t SW_NONE8 = 0xFF;
 
 // Neighbour-stepped matching kernel envelope (one wavefront per device).
 constexpr uint32_t NBR_MAX_CHUNKS = 1u << 18;  // two summary levels over rows of 64-bit words
+constexpr uint32_t NBR_TAG_SHIFT = 19;         // published entry, high word: window tag above the chunk rank
+constexpr uint32_t NBR_XCDS = 8;               // workgroups go to the XCDs in turn
 constexpr uint32_t NBR_MAX_POLL = 512;         // entries one device polls per window
 constexpr uint32_t NBR_MAX_RATIO = 64;         // largest link time over the smallest
 
@@ -164,14 +166,15 @@ struct Layout {
     uint32_t *wave_dest;      // [D + MATCH_WAVES * MAX_MATCH_GRID] destination of (pass, wave), NONE32 if none
     uint32_t *wave_part;      // [same] for a split destination: parts << 24 | part << 16 | first link << 8 | links; 0 = whole
     // neighbour-stepped matching kernel
-    uint64_t *pub;            // [4 * L] by slot: published link entries, four windows alternating
+    uint64_t *pub;            // [4 * Sizes::pub_n] published link entries, four windows alternating
+    uint32_t *pub_off;        // [D+1] a device's first entry (its in-links in slot order)
     uint64_t *cand;           // candidate rows: per device its in-links' rows of ceil(cols / 64) words, from cand_off
     uint64_t *cand_off;       // [D]
     uint32_t *need_pre;       // [D * Wp] columns of the device before each word of its needs row
     uint32_t *col_rank;       // chunk rank of every column, device d's from its send-log segment start
     uint32_t *dest_cols;      // [D] columns (chunks the device needs)
     uint32_t *rank_src;       // [C] priority position -> holder
-    uint32_t *poll_off, *poll; // [D+1], entries a device polls: slot << 8 | in-link fed (0xFF none)
+    uint32_t *poll_off, *poll; // [D+1], entries a device polls: entry << 8 | in-link fed (0xFF none)
     SwTab sw;                 // switch-model tables (null pointers without a switch model)
     // output
     void *out;                // pccl_send [2 * max_sends]
@@ -190,6 +193,7 @@ struct Sizes {
     uint32_t resident; // every wave of the matching kernel owns one destination (or part) for the whole run
     uint32_t sw_gate;  // both matching kernels are queued; Control::sw_binds picks the one that runs
     uint64_t cand_words;  // capacity of Layout::cand
+    uint32_t pub_n;    // published entries of one window
     uint32_t nbr;      // the neighbour-stepped matching kernel runs
     uint32_t sw_nbt;   // limited-switch rows of the switch tables (0: no switch model or no limited switch)
 };
@@ -205,11 +209,11 @@ hipError_t launch_match(const Layout &ly, const Sizes &sz, hipStream_t st, int g
                         bool split);
 int match_max_grid(int device, int waves_per_block, bool mirror, size_t dyn_lds, bool split);
 size_t match_static_lds();  // static LDS bytes of the matching kernel
-// wide: some device polls more than 64 entries; l3: more than 4,096 chunks;
-// dyn_lds bytes of LDS per workgroup
-hipError_t launch_match_nbr(const Layout &ly, const Sizes &sz, hipStream_t st, int grid, int waves_per_block, bool wide,
-                            bool l3, size_t dyn_lds);
-int match_nbr_max_grid(int device, int waves_per_block, bool wide, bool l3, size_t dyn_lds);
+// dyn_lds: bytes of LDS per workgroup; spread: the launch has that many
+// workgroups for each of the grid's, all but every spread-th end at once
+hipError_t launch_match_nbr(const Layout &ly, const Sizes &sz, hipStream_t st, int grid, int waves_per_block,
+                            size_t dyn_lds, uint32_t spread);
+int match_nbr_max_grid(int device, int waves_per_block, size_t dyn_lds);
 hipError_t launch_match_sw(const Layout &ly, const Sizes &sz, hipStream_t st, int grid);
 // sets Control::sw_binds when two out-neighbours of one of the n_uni unicast
 // switches need the same chunk

@@ -49,15 +49,21 @@ constexpr uint32_t NBR_THREADS = MATCH_THREADS;
 constexpr uint32_t NBR_WAVES = NBR_THREADS / 64;
 constexpr uint32_t NBR_SPIN_LIMIT = 1u << 24;
 
-// Published entry of an in-link: bit 63 the device is finished (the entry
-// holds for every later window), 12 bits window tag, 19 bits chunk rank
-// (NBR_IDLE: no transfer in flight), 32 bits end time.
-constexpr uint32_t NBR_IDLE = (1u << 19) - 1u;
-static_assert(NBR_MAX_CHUNKS < NBR_IDLE, "a chunk rank and the idle mark fit in 19 bits");
-constexpr uint64_t NBR_FINAL = 1ull << 63;
+// Published entry of an in-link, high word: bit 31 the device is finished
+// (the entry holds for every later window), 12 bits window tag, 19 bits chunk
+// rank; low word: end time of the transfer in flight, 0 if none (a transfer
+// takes at least 1 ns, so it never ends at 0).
+constexpr uint32_t NBR_RANK = (1u << 19) - 1u;
+static_assert(NBR_MAX_CHUNKS <= NBR_RANK, "a chunk rank fits in 19 bits");
+constexpr uint32_t NBR_TAG = 0xFFFu << NBR_TAG_SHIFT;
+constexpr uint32_t NBR_FINAL = 1u << 31;
+__device__ __forceinline__ uint32_t nbr_tag(uint32_t k) { return (k & 0xFFFu) << NBR_TAG_SHIFT; }
 
-__device__ __forceinline__ uint64_t nbr_tag(uint32_t k) { return (uint64_t)(k & 0xFFFu) << 51; }
-constexpr uint64_t NBR_TAG_MASK = 0xFFFull << 51;
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ uint32_t readlane(uint32_t v, uint32_t l)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+}
 
 template <class Op>
 __device__ __forceinline__ uint32_t dpp_reduce(uint32_t v, uint32_t id, Op op)
@@ -106,8 +112,10 @@ struct Tables {
     __device__ uint64_t *row() const { return reinterpret_cast<uint64_t *>(nbr_lds + row_at); }
     __device__ uint64_t *need() const { return reinterpret_cast<uint64_t *>(nbr_lds + need_at); }
     __device__ uint16_t *pre() const { return reinterpret_cast<uint16_t *>(nbr_lds + pre_at); }
-    __device__ uint32_t *rank() const { return reinterpret_cast<uint32_t *>(nbr_lds + rank_at); }
-    __device__ uint32_t rank_of(uint32_t col) const { return (in_lds & IN_RANK) ? rank()[col] : g_rank[col]; }
+    // [M] low 16 bits of the ranks, which ascend: those of the columns from
+    // step[i] on lie above (i + 1) * 65,536
+    __device__ uint16_t *rank() const { return reinterpret_cast<uint16_t *>(nbr_lds + rank_at); }
+    uint32_t step[3];
 };
 
 __device__ __forceinline__ void wave_sync()
@@ -117,268 +125,222 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The lowest live candidate column of this lane's in-link, NONE32 if none.
-// `want`: the lane's link is free.  A row word none of whose bits is live any
-// more leaves the summaries.
-template <bool L3>
-__device__ __forceinline__ uint32_t first_live(const Tables &tb, bool want, uint32_t &words)
+// A wait that has lasted: another wave's error ends it, and the spin limit
+// turns a wait that should not happen into an error.
+__device__ __attribute__((noinline)) bool give_up(Control *ctl, uint32_t spins, uint32_t d, uint32_t k)
+{
+    if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
+    if (spins <= NBR_SPIN_LIMIT) return false;
+    if ((threadIdx.x & 63u) == 0) {
+        atomicExch(&ctl->abort, 1u);
+        record_error(ctl, ST_EINTERNAL, 3, d, k);
+    }
+    return true;
+}
+
+// The best candidate of a lane's in-link: its column (NONE32 if none), and
+// where it was found: the live candidates of its row word and the summary
+// words above it.
+struct Pick {
+    uint32_t col;
+    uint64_t x, m, tp;
+};
+
+// The lowest live candidate column of this lane's in-link.  `want`: the
+// lane's link is free.  A row word none of whose bits is live any more leaves
+// the summaries.
+template <bool L3, bool ALL>
+__device__ __forceinline__ Pick first_live(const Tables &tb, bool want, uint32_t &words)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    uint32_t col = NONE32;
-    uint64_t tp = want ? tb.top()[lane] : 0ull;
-    while (__ballot(tp != 0ull)) {
-        if (tp) {
-            uint32_t w = low_bit(tp);
-            uint64_t m = 0;
+    Pick p{NONE32, 0, 0, 0};
+    bool go = false;
+    if (want) p.tp = tb.top()[lane];
+    go = p.tp != 0;
+    do {
+        if (go) {
+            uint32_t w = low_bit(p.tp);
             if (L3) {
-                m = tb.mid()[lane * tb.ms + w];
-                w = w * 64u + low_bit(m);
+                p.m = tb.mid()[lane * tb.ms + w];
+                w = w * 64u + low_bit(p.m);
             }
             uint64_t x;
             const uint64_t lv = tb.live()[w];
             // (rows in device memory are updated by atomics, which the L1
             // cache does not see: they are read past it)
-            if (tb.in_lds & IN_ROW) x = tb.row()[lane * tb.rs + w];
+            if (ALL || (tb.in_lds & IN_ROW)) x = tb.row()[lane * tb.rs + w];
             else x = __hip_atomic_load(&tb.g_row[(uint64_t)lane * tb.rs + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            x &= lv;
+            p.x = x & lv;
             words++;
-            if (x) {
-                col = w * 64u + low_bit(x);
-                tp = 0;
+            if (p.x) {
+                p.col = w * 64u + low_bit(p.x);
+                go = false;
             } else {
                 if (L3) {
-                    m &= m - 1ull;
-                    tb.mid()[lane * tb.ms + (w >> 6)] = m;
+                    p.m &= p.m - 1ull;
+                    tb.mid()[lane * tb.ms + (w >> 6)] = p.m;
                 }
-                if (!L3 || !m) {
-                    tp &= tp - 1ull;
-                    tb.top()[lane] = tp;
+                if (!L3 || !p.m) {
+                    p.tp &= p.tp - 1ull;
+                    tb.top()[lane] = p.tp;
+                    go = p.tp != 0;
                 }
             }
         }
-    }
-    return col;
+    } while (ballot(go));
+    return p;
 }
 
-// PPL: polled entries per lane.  L3: some destination may have more than
-// 4,096 columns (two summary levels).
-template <uint32_t PPL, bool L3>
-__device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, uint32_t d, uint32_t lds_at, uint32_t room)
+// The picked column leaves the row: its word leaves the summaries when the
+// column was its last live candidate, so that the link's next pick does not
+// meet an empty word.
+template <bool L3>
+__device__ __forceinline__ void drop_last(const Tables &tb, const Pick &p)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    if (p.x & (p.x - 1ull)) return;
+    if (L3) {
+        const uint64_t m = p.m & (p.m - 1ull);
+        tb.mid()[lane * tb.ms + low_bit(p.tp)] = m;
+        if (m) return;
+    }
+    tb.top()[lane] = p.tp & (p.tp - 1ull);
+}
+
+// All windows of device d.  PPL: polled entries per lane.  L3: two summary
+// levels (more than 4,096 columns).  ALL: every table is in LDS.
+template <uint32_t PPL, bool L3, bool ALL>
+__device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, const Tables &tb, uint32_t d, uint32_t M)
 {
     Control *ctl = ly.ctl;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t base = ly.in_off[d], n = ly.in_off[d + 1] - base;
     const bool mine = lane < n;
     const unsigned long long log0 = ly.dest_log[d];
-    const uint32_t M = ly.dest_cols[d], mw = (M + 63u) >> 6, mm = (mw + 63u) >> 6;
-    const uint32_t W = (uint32_t)sz.W;
-
-    // this wave's share of LDS
-    Tables tb{};
-    {
-        uint32_t at = lds_at;
-        const uint32_t end = lds_at + room;
-        auto take = [&](uint32_t bytes) {
-            const uint32_t p = at;
-            at += (bytes + 7u) & ~7u;
-            return p;
-        };
-        tb.live_at = take(mw * 8u);
-        tb.top_at = take(n * 8u);
-        tb.ms = mm | 1u;
-        if (L3) tb.mid_at = take(n * tb.ms * 8u);
-        tb.g_row = ly.cand + ly.cand_off[d];
-        tb.g_need = ly.needs + (uint64_t)d * sz.Wp;
-        tb.g_pre = ly.need_pre + (uint64_t)d * sz.Wp;
-        tb.g_rank = ly.col_rank + log0;
-        tb.rs = mw | 1u;
-        if (at + n * tb.rs * 8u <= end) {
-            tb.in_lds |= IN_ROW;
-            tb.row_at = take(n * tb.rs * 8u);
-        } else {
-            tb.rs = mw;
-        }
-        if (M <= 0xFFFFu && at + W * 10u + 8u <= end) {
-            tb.in_lds |= IN_NEED;
-            tb.need_at = take(W * 8u);
-            tb.pre_at = take(W * 2u);
-            for (uint32_t i = lane; i < W; i += 64) {
-                tb.need()[i] = tb.g_need[i];
-                tb.pre()[i] = (uint16_t)tb.g_pre[i];
-            }
-        }
-        if (at + M * 4u <= end) {
-            tb.in_lds |= IN_RANK;
-            tb.rank_at = take(M * 4u);
-            for (uint32_t i = lane; i < M; i += 64) tb.rank()[i] = tb.g_rank[i];
-        }
-        for (uint32_t i = lane; i < mw; i += 64)
-            tb.live()[i] = i + 1 < mw || (M & 63u) == 0 ? NONE64 : (1ull << (M & 63u)) - 1ull;
-        // rows and summaries, link by link (64 row words give one summary word)
-        for (uint32_t j = 0; j < n; j++) {
-            uint64_t tsum = 0;
-            for (uint32_t g = 0; g < mm; g++) {
-                const uint32_t w = g * 64u + lane;
-                uint64_t x = 0;
-                if (w < mw) {
-                    x = tb.g_row[(uint64_t)j * mw + w];
-                    if (tb.in_lds & IN_ROW) tb.row()[j * tb.rs + w] = x;
-                }
-                const uint64_t s = __ballot(x != 0);
-                if (L3) {
-                    if (lane == 0) tb.mid()[j * tb.ms + g] = s;
-                    if (s) tsum |= 1ull << g;
-                } else {
-                    tsum = s;
-                }
-            }
-            if (lane == 0) tb.top()[j] = tsum;
-        }
-        wave_sync();
-    }
     // this lane's in-link
     uint32_t tim = 0, lid = 0;
     if (mine) {
         tim = ly.slot_time[base + lane];
         lid = ly.slot_link[base + lane];
     }
-    // the entries this lane polls: slot << 8 | in-link they feed (0xFF: only
-    // the window tag counts, a reader of d that is no source of d)
+    // the entries this lane polls (a lane past the last one polls that again):
+    // their place; whether they feed an in-link (and where its row and summary
+    // lie) or only tell how far a reader of d is (`dep`)
     const uint32_t p0 = ly.poll_off[d], np = ly.poll_off[d + 1] - p0;
-    uint32_t pol[PPL];
+    const uint32_t W = (uint32_t)sz.W, L = sz.pub_n, tmin = sz.tmin, own = ly.pub_off[d] + lane;
+    uint32_t at[PPL], link[PPL];
+    bool dep[PPL], data[PPL];
 #pragma unroll
-    for (uint32_t u = 0; u < PPL; u++) pol[u] = np ? ly.poll[p0 + min(64u * u + lane, np - 1u)] : 0u;
-
-    const uint32_t tmin = sz.tmin;
-    const uint64_t L = sz.L;
-    uint32_t left = M, fin = 0;
-    uint32_t busy_end = 0, busy_rank = NBR_IDLE;  // the transfer in flight on this lane's link
-    uint32_t cstar = 0, words = 0;
-    uint32_t rounds = 0, clashes = 0;
+    for (uint32_t u = 0; u < PPL; u++) {
+        const uint32_t q = np ? ly.poll[p0 + min(64u * u + lane, np - 1u)] : 0u;
+        at[u] = q >> 8;
+        link[u] = q & 0xFFu;
+        dep[u] = link[u] == 0xFFu;
+        data[u] = 64u * u + lane < np && !dep[u];
+        if (!data[u]) link[u] = 0;
+    }
+    uint32_t left = M, fin = 0, k = 0;
+    uint32_t busy_end = 0, busy_rank = 0;  // the transfer in flight on this lane's link (end 0: none)
+    uint32_t cstar = 0, words = 0, rounds = 0, clashes = 0;
     unsigned long long log = log0;
-    uint64_t t0 = 0;
-    uint32_t k = 0;
-    bool bad = false;
-    for (;; k++, t0 += tmin) {
+    uint64_t t64 = 0;
+    for (;; k++, t64 += tmin) {
+        // the window is [t0, t0 + lim); past the last representable time lim
+        // is 0 (ends below t0, and the 0 of an idle entry, wrap to at least lim)
+        const uint32_t t0 = (uint32_t)t64;
+        const uint32_t lim = t64 >> 32 ? 0u : (uint32_t)min((uint64_t)tmin, (1ull << 32) - t64);
         uint32_t ra[PPL], ca[PPL];  // arrivals of this window: offset into the window (NONE32: none), column
-        uint32_t rb = NONE32;       // the end of this lane's transfer when inside the window
 #pragma unroll
-        for (uint32_t u = 0; u < PPL; u++) {
-            ra[u] = NONE32;
-            ca[u] = 0;
-        }
-        if (k) {
-            if (np) {
-                // sources: the state at the end of window k - 1; readers of d
-                // that are no sources: that they have read window k - 4
-                const uint64_t *b1 = ly.pub + (uint64_t)((k - 1u) & 3u) * L, *b3 = ly.pub + (uint64_t)((k - 3u) & 3u) * L;
-                const uint64_t tag1 = nbr_tag(k - 1u), tag3 = nbr_tag(k - 3u);
-                uint64_t e[PPL];
+        for (uint32_t u = 0; u < PPL; u++) ra[u] = NONE32;
+        if (k && np) {
+            // sources: the state at the end of window k - 1; readers of d
+            // that are no sources: that they have read window k - 4 (whose
+            // entries this window's replace)
+            const uint32_t o1 = ((k - 1u) & 3u) * L, o3 = ((k - 3u) & 3u) * L;
+            const uint32_t g1 = nbr_tag(k - 1u), g3 = nbr_tag(k - 3u);
+            uint64_t e[PPL];
+            uint32_t spins = 0;
+            bool stuck = false;
+            while (true) {
+                bool ok = true;
 #pragma unroll
-                for (uint32_t u = 0; u < PPL; u++) e[u] = 0;
-                uint32_t spins = 0;
-                while (true) {
-                    bool ok = true;
-#pragma unroll
-                    for (uint32_t u = 0; u < PPL; u++) {
-                        if (64u * u >= np) break;
-                        const bool dep = (pol[u] & 0xFFu) == 0xFFu;
-                        e[u] = __hip_atomic_load((dep ? b3 : b1) + (pol[u] >> 8), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < PPL; u++) {
-                        if (64u * u >= np) break;
-                        const bool dep = (pol[u] & 0xFFu) == 0xFFu;
-                        const uint64_t want = dep ? tag3 : tag1;
-                        ok = ok && ((int64_t)e[u] < 0 || (e[u] & NBR_TAG_MASK) == want || (dep && k < 3u));
-                    }
-                    if (__ballot(!ok) == 0) break;
-                    // (another wave's error ends the wait; the spin limit turns
-                    // a wait that should not happen into an error)
-                    if ((++spins & 15u) == 0) {
-                        if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                            bad = true;
-                            break;
-                        }
-                        if (spins > NBR_SPIN_LIMIT) {
-                            if (lane == 0) {
-                                atomicExch(&ctl->abort, 1u);
-                                record_error(ctl, ST_EINTERNAL, 3, d, k);
-                            }
-                            bad = true;
-                            break;
-                        }
-                    }
+                for (uint32_t u = 0; u < PPL; u++) {
+                    if (PPL > 2 && 64u * u >= np) break;
+                    e[u] = __hip_atomic_load(ly.pub + (at[u] + (dep[u] ? o3 : o1)), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
                 }
-                if (bad) break;
-                if (left && !(t0 >> 32)) {
-                    // arrivals inside the window, in d's columns, that d still needs
-                    bool in[PPL];
-                    bool any = false;
-                    const uint32_t t032 = (uint32_t)t0;
 #pragma unroll
-                    for (uint32_t u = 0; u < PPL; u++) in[u] = false;
+                for (uint32_t u = 0; u < PPL; u++) {
+                    if (PPL > 2 && 64u * u >= np) break;
+                    const uint32_t hi = (uint32_t)(e[u] >> 32);
+                    ok = ok && ((int32_t)hi < 0 || ((hi ^ (dep[u] ? g3 : g1)) & NBR_TAG) == 0);
+                }
+                if (ballot(!ok) == 0) break;
+                if ((++spins & 15u) == 0 && give_up(ctl, spins, d, k)) {
+                    stuck = true;
+                    break;
+                }
+            }
+            if (stuck) break;
+            bool in[PPL], any = false;
 #pragma unroll
-                    for (uint32_t u = 0; u < PPL; u++) {
-                        if (64u * u >= np) break;
-                        const uint32_t end = (uint32_t)e[u], r = (uint32_t)(e[u] >> 32) & NBR_IDLE;
-                        in[u] = 64u * u + lane < np && r != NBR_IDLE && (pol[u] & 0xFFu) != 0xFFu && end >= t032 &&
-                                end - t032 < tmin;
-                        any = any || in[u];
-                    }
-                    if (__ballot(any)) {
-                        uint64_t nw[PPL];
-                        uint32_t pr[PPL];
+            for (uint32_t u = 0; u < PPL; u++) in[u] = false;
 #pragma unroll
-                        for (uint32_t u = 0; u < PPL; u++) {
-                            nw[u] = 0;
-                            pr[u] = 0;
-                            if (in[u]) {
-                                const uint32_t w = ((uint32_t)(e[u] >> 32) & NBR_IDLE) >> 6;
-                                if (tb.in_lds & IN_NEED) {
-                                    nw[u] = tb.need()[w];
-                                    pr[u] = tb.pre()[w];
-                                } else {
-                                    nw[u] = tb.g_need[w];
-                                    pr[u] = tb.g_pre[w];
-                                }
-                            }
+            for (uint32_t u = 0; u < PPL; u++) {
+                if (PPL > 2 && 64u * u >= np) break;
+                in[u] = data[u] && (uint32_t)e[u] - t0 < lim;
+                any = any || in[u];
+            }
+            if (left && ballot(any)) {
+                // the arrivals in d's columns, those that d still needs
+#pragma unroll
+                for (uint32_t u = 0; u < PPL; u++) {
+                    if (PPL > 2 && 64u * u >= np) break;
+                    if (in[u]) {
+                        const uint32_t r = (uint32_t)(e[u] >> 32) & NBR_RANK, w = r >> 6, b = r & 63u;
+                        uint64_t nw;
+                        uint32_t pr;
+                        if (ALL || (tb.in_lds & IN_NEED)) {
+                            nw = tb.need()[w];
+                            pr = tb.pre()[w];
+                        } else {
+                            nw = tb.g_need[w];
+                            pr = tb.g_pre[w];
                         }
-#pragma unroll
-                        for (uint32_t u = 0; u < PPL; u++) {
-                            const uint32_t b = (uint32_t)(e[u] >> 32) & 63u;
-                            if (in[u] && ((nw[u] >> b) & 1ull)) {
-                                ca[u] = pr[u] + (uint32_t)__popcll(nw[u] & ((1ull << b) - 1ull));
-                                if ((tb.live()[ca[u] >> 6] >> (ca[u] & 63u)) & 1ull) ra[u] = (uint32_t)e[u] - t032;
-                            }
+                        if ((nw >> b) & 1ull) {
+                            ca[u] = pr + (uint32_t)__popcll(nw & ((1ull << b) - 1ull));
+                            if ((tb.live()[ca[u] >> 6] >> (ca[u] & 63u)) & 1ull) ra[u] = (uint32_t)e[u] - t0;
                         }
                     }
                 }
             }
-            if (busy_rank != NBR_IDLE && !(t0 >> 32) && busy_end - (uint32_t)t0 < tmin) rb = busy_end - (uint32_t)t0;
         }
+        // this lane's transfer, when it ends inside the window; at time 0
+        // every (idle) link counts as ending there
+        uint32_t rb = busy_end - t0 < lim ? busy_end - t0 : NONE32;
 
         // events of the window in time order
-        uint32_t newcol = NONE32;  // the column this lane's link committed in this window (at most one: Tmin)
-        bool first = k == 0;
+        uint32_t newcol = NONE32;  // the column this lane's link commits in this window (at most one: T >= Tmin)
         while (true) {
             uint32_t m = rb;
 #pragma unroll
             for (uint32_t u = 0; u < PPL; u++) m = min(m, ra[u]);
-            const uint32_t t = first ? 0u : dpp_reduce(m, NONE32, MinOp());
-            if (t == NONE32) break;
-            first = false;
+            const uint64_t pend = ballot(m != NONE32);
+            if (!pend) break;
+            // the earliest: mostly the first pending lane's
+            uint32_t t = readlane(m, low_bit(pend));
+            if (ballot(m < t)) t = dpp_reduce(m, NONE32, MinOp());
             if (rb == t) {
-                busy_rank = NBR_IDLE;
+                busy_end = 0;
                 rb = NONE32;
             }
 #pragma unroll
             for (uint32_t u = 0; u < PPL; u++) {
+                if (PPL > 2 && 64u * u >= np) break;
                 if (ra[u] == t) {
-                    const uint32_t j = pol[u] & 0xFFu, w = ca[u] >> 6;
+                    const uint32_t j = link[u], w = ca[u] >> 6;
                     const unsigned long long bit = 1ull << (ca[u] & 63u);
-                    if (tb.in_lds & IN_ROW) atomicOr((unsigned long long *)&tb.row()[j * tb.rs + w], bit);
+                    if (ALL || (tb.in_lds & IN_ROW)) atomicOr((unsigned long long *)&tb.row()[j * tb.rs + w], bit);
                     else __hip_atomic_fetch_or(&tb.g_row[(uint64_t)j * tb.rs + w], (uint64_t)bit, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
                     if (L3) {
@@ -391,55 +353,70 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, uint
                 }
             }
             // pick rounds
-            bool want = mine && busy_rank == NBR_IDLE && newcol == NONE32;
-            while (true) {
-                const uint32_t col = first_live<L3>(tb, want, words);
+            const uint32_t now = t0 + t;
+            bool want = mine && busy_end == 0;
+            uint64_t losers;
+            do {
+                const Pick pk = first_live<L3, ALL>(tb, want, words);
+                const uint32_t col = pk.col;
                 const bool act = col != NONE32;
-                if (__ballot(act) == 0) break;
-                // clear the picked columns; a lane that finds its column
-                // already cleared shares it with another lane
-                uint64_t old = 0;
-                if (act) old = atomicAnd((unsigned long long *)&tb.live()[col >> 6], ~(1ull << (col & 63u)));
-                bool win = act && ((old >> (col & 63u)) & 1ull);
-                uint64_t clash = __ballot(act && !win);
-                uint64_t losers = clash;
-                if (clash) {
-                    // fastest link, then lowest id, among the links that picked the column
-                    while (clash) {
-                        const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)col, __builtin_ctzll(clash));
-                        const bool in_g = act && col == v;
-                        const uint64_t g = __ballot(in_g);
-                        const uint32_t tm = dpp_reduce(in_g ? tim : NONE32, NONE32, MinOp());
-                        const uint32_t li = dpp_reduce(in_g && tim == tm ? lid : NONE32, NONE32, MinOp());
-                        if (in_g) win = tim == tm && lid == li;
-                        clash &= ~g;
+                const uint64_t actm = ballot(act);
+                losers = 0;
+                if (actm) {
+                    bool win = act;
+                    unsigned long long *lw = (unsigned long long *)&tb.live()[col >> 6];
+                    const uint64_t bit = 1ull << (col & 63u);
+                    if ((actm & (actm - 1ull)) == 0) {
+                        if (act) atomicAnd(lw, ~bit);
+                    } else {
+                        // clear the picked columns; a lane that finds its
+                        // column already cleared shares it with another lane
+                        if (act) win = (atomicAnd(lw, ~bit) & bit) != 0;
+                        uint64_t clash = ballot(act && !win);
+                        if (clash) {
+                            // fastest link, then lowest id, among the links that picked the column
+                            while (clash) {
+                                const uint32_t v = readlane(col, low_bit(clash));
+                                const bool in_g = col == v;
+                                const uint64_t g = ballot(in_g);
+                                const uint32_t tm = dpp_reduce(in_g ? tim : NONE32, NONE32, MinOp());
+                                const uint32_t li = dpp_reduce(in_g && tim == tm ? lid : NONE32, NONE32, MinOp());
+                                if (in_g) win = tim == tm && lid == li;
+                                clash &= ~g;
+                            }
+                            losers = ballot(act && !win);
+                            clashes += (uint32_t)__popcll(losers);
+                            want = act && !win;
+                        }
                     }
-                    losers = __ballot(act && !win);
-                    clashes += (uint32_t)__popcll(losers);
-                }
-                rounds++;
-                if (win) {
-                    newcol = col;
-                    const uint64_t end = t0 + t + tim;
-                    busy_end = (uint32_t)end;
-                    if (end > 0xFFFFFFFFull) {
-                        record_error(ctl, ST_ERANGE, tb.rank_of(col), d, 2);
-                        busy_end = 0xFFFFFFFFu;
+                    rounds++;
+                    if (win) {
+                        newcol = col;
+                        busy_end = now + tim;
+                        drop_last<L3>(tb, pk);
                     }
-                    cstar = max(cstar, busy_end);
                 }
-                if (!losers) break;
-                want = act && !win;
-            }
+            } while (losers);
         }
 
         // publish the state at the window's end, then log the commits
-        const uint64_t cm = __ballot(newcol != NONE32);
-        if (newcol != NONE32) busy_rank = tb.rank_of(newcol);
+        if (newcol != NONE32) {
+            if (ALL || (tb.in_lds & IN_RANK)) {
+                busy_rank = tb.rank()[newcol];
+                if (W > 1024u) {
+#pragma unroll
+                    for (uint32_t i = 0; i < 3; i++) busy_rank += newcol >= tb.step[i] ? 0x10000u : 0u;
+                }
+            } else {
+                busy_rank = tb.g_rank[newcol];
+            }
+        }
+        const uint64_t cm = ballot(newcol != NONE32);
+        if (newcol != NONE32) cstar = max(cstar, busy_end);
         left -= (uint32_t)__popcll(cm);
         if (mine)
-            __hip_atomic_store(ly.pub + (uint64_t)(k & 3u) * L + base + lane,
-                               (left ? 0ull : NBR_FINAL) | nbr_tag(k) | ((uint64_t)busy_rank << 32) | busy_end,
+            __hip_atomic_store(ly.pub + ((k & 3u) * L + own),
+                               ((uint64_t)((left ? 0u : NBR_FINAL) | nbr_tag(k) | busy_rank) << 32) | busy_end,
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (newcol != NONE32) {
             const unsigned long long q = log + lane_prefix(cm);
@@ -447,11 +424,13 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, uint
             ly.sval[0][q] = busy_rank;
         }
         log += (unsigned long long)__popcll(cm);
+        // an end beyond 32 bits ends the synthesis
+        if (newcol != NONE32 && busy_end < tim) record_error(ctl, ST_ERANGE, busy_rank, d, 2);
         // finished: the four copies of the entries all say so, then the wave ends
         if (!left && ++fin == 4u) break;
         // no event can follow the last representable time; by D windows later
         // an overflow met by any other device has been recorded first
-        if (left && t0 > 0xFFFFFFFFull + (uint64_t)(sz.D + 4u) * tmin) {
+        if (left && t64 > 0xFFFFFFFFull + (uint64_t)(sz.D + 4u) * tmin) {
             if (lane == 0) record_error(ctl, ST_EDEADLOCK, left, 0, 0);
             break;
         }
@@ -468,37 +447,119 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, uint
     }
 }
 
-template <uint32_t PPL, bool L3>
-__global__ void __launch_bounds__(NBR_THREADS) k_match_nbr(Layout ly, Sizes sz, uint32_t lds_bytes)
+// Places device d's tables in the LDS bytes [at, at + room) and fills them.
+__device__ __forceinline__ void fill_tables(const Layout &ly, const Sizes &sz, uint32_t d, uint32_t M, uint32_t at, uint32_t room,
+                                            Tables &tb)
 {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t n = ly.in_off[d + 1] - ly.in_off[d], W = (uint32_t)sz.W;
+    const uint32_t mw = (M + 63u) >> 6, mm = (mw + 63u) >> 6, end = at + room;
+    const bool l3 = mm > 1u;
+    auto take = [&](uint32_t bytes) {
+        const uint32_t p = at;
+        at += (bytes + 7u) & ~7u;
+        return p;
+    };
+    tb.live_at = take(mw * 8u);
+    tb.top_at = take(n * 8u);
+    tb.ms = mm | 1u;
+    if (l3) tb.mid_at = take(n * tb.ms * 8u);
+    tb.g_row = ly.cand + ly.cand_off[d];
+    tb.g_need = ly.needs + (uint64_t)d * sz.Wp;
+    tb.g_pre = ly.need_pre + (uint64_t)d * sz.Wp;
+    tb.g_rank = ly.col_rank + ly.dest_log[d];
+    tb.rs = mw | 1u;
+    if (at + n * tb.rs * 8u <= end) {
+        tb.in_lds |= IN_ROW;
+        tb.row_at = take(n * tb.rs * 8u);
+    } else {
+        tb.rs = mw;
+    }
+    if (M <= 0xFFFFu && at + W * 10u + 8u <= end) {
+        tb.in_lds |= IN_NEED;
+        tb.need_at = take(W * 8u);
+        tb.pre_at = take(W * 2u);
+        for (uint32_t i = lane; i < W; i += 64) {
+            tb.need()[i] = tb.g_need[i];
+            tb.pre()[i] = (uint16_t)tb.g_pre[i];
+        }
+    }
+    static_assert(NBR_MAX_CHUNKS <= 4u << 16, "ranks have at most two bits above 16");
+#pragma unroll
+    for (uint32_t i = 0; i < 3; i++) tb.step[i] = (i + 1u) * 1024u < W ? tb.g_pre[(i + 1u) * 1024u] : M;
+    if (at + M * 2u <= end) {
+        tb.in_lds |= IN_RANK;
+        tb.rank_at = take(M * 2u);
+        for (uint32_t i = lane; i < M; i += 64) tb.rank()[i] = (uint16_t)tb.g_rank[i];
+    }
+    for (uint32_t i = lane; i < mw; i += 64)
+        tb.live()[i] = i + 1 < mw || (M & 63u) == 0 ? NONE64 : (1ull << (M & 63u)) - 1ull;
+    // rows and summaries, link by link (64 row words give one summary word)
+    for (uint32_t j = 0; j < n; j++) {
+        uint64_t tsum = 0;
+        for (uint32_t g = 0; g < mm; g++) {
+            const uint32_t w = g * 64u + lane;
+            uint64_t x = 0;
+            if (w < mw) {
+                x = tb.g_row[(uint64_t)j * mw + w];
+                if (tb.in_lds & IN_ROW) tb.row()[j * tb.rs + w] = x;
+            }
+            const uint64_t s = ballot(x != 0);
+            if (l3) {
+                if (lane == 0) tb.mid()[j * tb.ms + g] = s;
+                if (s) tsum |= 1ull << g;
+            } else {
+                tsum = s;
+            }
+        }
+        if (lane == 0) tb.top()[j] = tsum;
+    }
+    wave_sync();
+}
+
+// Each wave takes the build of run_dest for its device: polled entries per
+// lane, summary levels, and whether every table found room in LDS.
+template <uint32_t PPL>
+__device__ __forceinline__ void run_built(const Layout &ly, const Sizes &sz, const Tables &tb, uint32_t d, uint32_t M)
+{
+    if (tb.in_lds != (IN_ROW | IN_NEED | IN_RANK)) {
+        if (M > 4096u) run_dest<PPL, true, false>(ly, sz, tb, d, M);
+        else run_dest<PPL, false, false>(ly, sz, tb, d, M);
+    } else if (M > 4096u) {
+        run_dest<PPL, true, true>(ly, sz, tb, d, M);
+    } else {
+        run_dest<PPL, false, true>(ly, sz, tb, d, M);
+    }
+}
+
+__global__ void __launch_bounds__(NBR_THREADS) k_match_nbr(Layout ly, Sizes sz, uint32_t lds_bytes, uint32_t spread)
+{
+    if (blockIdx.x % spread) return;
     Control *ctl = ly.ctl;
     if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
     if (ctl->needs_total == 0) return;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), wpb = blockDim.x >> 6;
-    const uint32_t *wd = ly.wave_dest + (uint64_t)blockIdx.x * wpb;
+    const uint32_t *wd = ly.wave_dest + (uint64_t)(blockIdx.x / spread) * wpb;
     const uint32_t d = (uint32_t)__builtin_amdgcn_readfirstlane((int)wd[wave]);
     if (d == NONE32) return;
     // a device alone in its workgroup has all of its LDS
     uint32_t act = 0;
     for (uint32_t w = 0; w < wpb; w++) act += wd[w] != NONE32 ? 1u : 0u;
     const uint32_t share = act > 1u ? (lds_bytes / wpb) & ~15u : lds_bytes;
-    run_dest<PPL, L3>(ly, sz, d, act > 1u ? wave * share : 0u, share);
-}
-
-const void *nbr_kernel(bool wide, bool l3)
-{
-    if (wide)
-        return l3 ? reinterpret_cast<const void *>(k_match_nbr<NBR_MAX_POLL / 64u, true>)
-                  : reinterpret_cast<const void *>(k_match_nbr<NBR_MAX_POLL / 64u, false>);
-    return l3 ? reinterpret_cast<const void *>(k_match_nbr<1, true>) : reinterpret_cast<const void *>(k_match_nbr<1, false>);
+    const uint32_t M = ly.dest_cols[d], np = ly.poll_off[d + 1] - ly.poll_off[d];
+    Tables tb{};
+    fill_tables(ly, sz, d, M, act > 1u ? wave * share : 0u, share, tb);
+    if (np <= 64u) run_built<1>(ly, sz, tb, d, M);
+    else if (np <= 128u) run_built<2>(ly, sz, tb, d, M);
+    else run_built<NBR_MAX_POLL / 64u>(ly, sz, tb, d, M);
 }
 
 }  // namespace
 
-int match_nbr_max_grid(int device, int waves_per_block, bool wide, bool l3, size_t dyn_lds)
+int match_nbr_max_grid(int device, int waves_per_block, size_t dyn_lds)
 {
     int per_cu = 0, cus = 0;
-    const void *kern = nbr_kernel(wide, l3);
+    const void *kern = reinterpret_cast<const void *>(k_match_nbr);
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * waves_per_block, dyn_lds) != hipSuccess)
         return 0;
@@ -506,18 +567,18 @@ int match_nbr_max_grid(int device, int waves_per_block, bool wide, bool l3, size
     return per_cu * cus;
 }
 
-hipError_t launch_match_nbr(const Layout &ly, const Sizes &sz, hipStream_t st, int grid, int waves_per_block, bool wide,
-                            bool l3, size_t dyn_lds)
+hipError_t launch_match_nbr(const Layout &ly, const Sizes &sz, hipStream_t st, int grid, int waves_per_block,
+                            size_t dyn_lds, uint32_t spread)
 {
     if (waves_per_block < 1 || waves_per_block > (int)NBR_WAVES) return hipErrorInvalidValue;
-    const void *kern = nbr_kernel(wide, l3);
+    const void *kern = reinterpret_cast<const void *>(k_match_nbr);
     const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds);
     if (e != hipSuccess) return e;
     Layout l = ly;
     Sizes s = sz;
     uint32_t b = (uint32_t)dyn_lds;
-    void *args[] = {&l, &s, &b};
-    return hipLaunchCooperativeKernel(kern, dim3(grid), dim3(64 * waves_per_block), args, (unsigned)dyn_lds, st);
+    void *args[] = {&l, &s, &b, &spread};
+    return hipLaunchCooperativeKernel(kern, dim3(grid * spread), dim3(64 * waves_per_block), args, (unsigned)dyn_lds, st);
 }
 
 }  // namespace pccl

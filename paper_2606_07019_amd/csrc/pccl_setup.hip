@@ -491,8 +491,9 @@ __global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
 {
     __shared__ uint8_t link_of[MAX_DEVICES_SP];  // in-link of d whose source is the device, 0xFF none
     const uint32_t d = blockIdx.x, tid = threadIdx.x;
-    // the published entries start with a window tag no early window uses
-    for (uint64_t i = (uint64_t)d * 1024u + tid; i < 4ull * sz.L; i += (uint64_t)gridDim.x * 1024u) ly.pub[i] = NONE64 >> 1;
+    // the published entries start as those of windows -4 to -1
+    for (uint32_t i = d * 1024u + tid; i < 4u * sz.pub_n; i += gridDim.x * 1024u)
+        ly.pub[i] = (uint64_t)((0xFFCu + i / sz.pub_n) << NBR_TAG_SHIFT) << 32;
     if (ly.ctl->error) return;
     const uint32_t M = ly.dest_cols[d];
     if (M == 0) return;
