@@ -206,8 +206,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     ly.chunk_dist = cv.take<uint64_t>(C);
     ly.rank = cv.take<uint32_t>(C);
     ly.order = cv.take<uint32_t>(C);
-    ly.src_index = cv.take<uint32_t>(N);
-    ly.src_list = cv.take<uint32_t>(N);
+    ly.is_src = cv.take<uint32_t>(N);
     ly.sp_dist = cv.take<uint64_t>(N * D);
     ly.sp_parent = cv.take<uint32_t>(N * D);
     ly.skey[0] = cv.take<uint64_t>(nsort);
@@ -1310,8 +1309,11 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
     }
     HIP_OR_FAIL(c, launch_setup(c->ly, c->sz, c->ly.pre, c->ly.post, c->ly.chunk_group, c->seed, st));
     // the setup's delivery count sizes the output stage; the host reads it
-    // while the matching kernel runs and queues the output kernels behind it
-    HIP_OR_FAIL(c, hipMemcpyAsync(&c->pin[0], c->ly.ctl, sizeof(Control), hipMemcpyDeviceToHost, st));
+    // while the matching kernel runs and queues the output kernels behind it.
+    // A log of one workgroup's size needs no such wait: its output kernel
+    // reads the count on the device.
+    const bool small = c->max_sends <= SMALL_SORT;
+    if (!small) HIP_OR_FAIL(c, hipMemcpyAsync(&c->pin[0], c->ly.ctl, sizeof(Control), hipMemcpyDeviceToHost, st));
     HIP_OR_FAIL(c, hipEventRecord(c->ev[1], st));
     const bool gate = c->sw_active && c->sw_gate;
     if (gate) {
@@ -1328,19 +1330,27 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
         HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
     }
     HIP_OR_FAIL(c, hipEventRecord(c->ev[2], st));
-    HIP_OR_FAIL(c, hipEventSynchronize(c->ev[1]));
-    const Control s0 = c->pin[0];
-    const bool out_queued = !s0.error && s0.needs_total <= c->max_sends;
-    if (out_queued) HIP_OR_FAIL(c, launch_output(c->ly, c->sz, c->op, s0.needs_total, st));
-    HIP_OR_FAIL(c, hipEventRecord(c->ev[3], st));
-    HIP_OR_FAIL(c, hipMemcpyAsync(&c->pin[1], c->ly.ctl, sizeof(Control), hipMemcpyDeviceToHost, st));
+    bool out_queued = true;
+    uint64_t expected = 0;
+    if (small) {
+        HIP_OR_FAIL(c, launch_output_small(c->ly, c->op, &c->pin[1], st));
+        HIP_OR_FAIL(c, hipEventRecord(c->ev[3], st));
+    } else {
+        HIP_OR_FAIL(c, hipEventSynchronize(c->ev[1]));
+        const Control s0 = c->pin[0];
+        expected = s0.needs_total;
+        out_queued = !s0.error && expected <= c->max_sends;
+        if (out_queued) HIP_OR_FAIL(c, launch_output(c->ly, c->sz, c->op, expected, st));
+        HIP_OR_FAIL(c, hipEventRecord(c->ev[3], st));
+        HIP_OR_FAIL(c, hipMemcpyAsync(&c->pin[1], c->ly.ctl, sizeof(Control), hipMemcpyDeviceToHost, st));
+    }
     HIP_OR_FAIL(c, hipStreamSynchronize(st));
     c->ctl_host = c->pin[1];
     const Control &h = c->ctl_host;
     c->ran_sw = c->sw_active && (!gate || h.sw_binds);
     if (h.abort) return fail(c, PCCL_EINTERNAL, "matching kernel barrier timed out");
     if (h.error) return device_error(c, h);
-    if (h.n_log != h.needs_total || !out_queued || h.needs_total != s0.needs_total)
+    if (h.n_log != h.needs_total || !out_queued || (!small && h.needs_total != expected))
         return fail(c, PCCL_EINTERNAL, "logged %llu transfers for %llu deliveries", (unsigned long long)h.n_log,
                     (unsigned long long)h.needs_total);
     const uint64_t n = h.n_log;

@@ -63,7 +63,6 @@ struct Control {
     unsigned long long max_sends;        // capacity of the send log
     unsigned long long rounds, clashes, windows;
     unsigned long long scan_words;       // words of each row read by the intersect
-    uint32_t n_sources;      // distinct chunk sources
     uint32_t abort;          // set when a window exchange wait times out
     uint32_t cstar;          // collective time of the copy schedule
     uint32_t sort_cur;       // radix sort: buffer holding the current order
@@ -148,9 +147,8 @@ struct Layout {
     uint64_t *chunk_dist;  // [C]
     uint32_t *rank;        // [C] chunk -> priority position
     uint32_t *order;       // [C] priority position -> chunk
-    uint32_t *src_index;   // [N] row of a source in the shortest-path tables
-    uint32_t *src_list;    // [N]
-    uint64_t *sp_dist;     // [N * D]
+    uint32_t *is_src;      // [N] the NPU holds a chunk
+    uint64_t *sp_dist;     // [N * D] by NPU, rows of holders only
     uint32_t *sp_parent;   // [N * D]
     // sort buffers (chunk order first, then the send log)
     uint64_t *skey[2];     // [max(C, 2*max_sends)]
@@ -219,6 +217,9 @@ hipError_t launch_match_sw(const Layout &ly, const Sizes &sz, hipStream_t st, in
 // switches need the same chunk
 hipError_t launch_unicast_check(const Layout &ly, const Sizes &sz, hipStream_t st, uint32_t n_uni);
 int match_sw_max_grid(int device);
+// the output stage when the log holds at most SMALL_SORT transfers, with the
+// control block copied to pinned host memory
+hipError_t launch_output_small(const Layout &ly, int op, Control *host_ctl, hipStream_t st);
 hipError_t launch_output(const Layout &ly, const Sizes &sz, int op, uint64_t n, hipStream_t st);
 // LSD radix sort of (key, value) pairs by key bytes [byte_lo, byte_hi), stable;
 // the sorted order ends up in buffer ly.ctl->sort_cur (read it on the device).
@@ -228,6 +229,38 @@ hipError_t radix_sort_pairs(const Layout &ly, uint64_t n, int byte_lo, int byte_
                             bool reset_cur, hipStream_t st, bool time_gate = false);
 constexpr uint32_t SORT_TILE = 4096;      // elements per radix-sort tile
 constexpr uint32_t SORT_THREADS = 256;
+// Elements one workgroup of 1,024 threads sorts in LDS.  The bitonic steps are
+// bound by that one compute unit's LDS bandwidth (2,048 elements 25 us), so
+// twice as many are quicker in the radix passes (4,225 chunks padded to 8,192:
+// 0.205 ms setup against 0.166).
+constexpr uint32_t SMALL_SORT = 4096;
+
+// Bitonic sort of m elements (a power of two) by one workgroup:
+// above(a, b) says that element a belongs after b, swap(a, b) exchanges them.
+// Starts and ends with a barrier.  A step of stride up to 64 stays inside the
+// 128 elements one wave works on, so only the wider ones (10 of the 66 steps
+// of 2,048 elements) need the workgroup's barrier.
+template <class Above, class Swap>
+__device__ __forceinline__ void bitonic_sort(uint32_t m, Above above, Swap swap)
+{
+    __syncthreads();
+    for (uint32_t k = 2; k <= m; k <<= 1)
+        for (uint32_t j = k >> 1; j; j >>= 1) {
+            for (uint32_t i = threadIdx.x; i < m / 2; i += blockDim.x) {
+                const uint32_t a = 2 * i - (i & (j - 1)), b = a + j;  // j's bit of a is clear
+                if (above(a, b) == ((a & k) == 0)) swap(a, b);
+            }
+            // (the next step's stride is j / 2, or k when j is 1)
+            if (j > 64 || (j == 1 && k > 64)) {
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+    __syncthreads();
+}
 // row length of the digit-major tile histogram, 16-bit counts (a multiple
 // of 8 tiles, so a row is read in 16-byte loads)
 inline __host__ __device__ uint32_t hist_stride(uint32_t tiles) { return (tiles + 7u) & ~7u; }

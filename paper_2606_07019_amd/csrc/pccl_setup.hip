@@ -13,24 +13,58 @@ constexpr uint32_t CNT_MASK = 0x7FFFFFFFu;
 // detail codes carried in error_arg[2] for PCCL_EINVAL
 enum : uint32_t { BAD_TAIL = 1, BAD_MEMBER = 2, BAD_GROUP = 3, TWO_HOLDERS = 4, NO_HOLDER = 5 };
 
-__global__ void k_fill32(uint32_t *p, uint64_t n, uint32_t v)
+// The start of a synthesis: the control block, the per-chunk arrays and the
+// bitmaps (one launch; a launch costs as much as clearing 16 MB).
+__global__ void __launch_bounds__(256) k_reset(Layout ly, Sizes sz)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+    const uint64_t i0 = (uint64_t)blockIdx.x * 256u + threadIdx.x, step = (uint64_t)gridDim.x * 256u;
+    if (i0 == 0) {
+        Control c = {};
+        c.max_sends = sz.max_sends;
+        *ly.ctl = c;
+    }
+    for (uint64_t i = i0; i < sz.C; i += step) {
+        ly.holder_cnt[i] = 0;
+        ly.chunk_src[i] = NONE32;
+        ly.chunk_dist[i] = 0;
+    }
+    for (uint64_t i = i0; i < sz.N; i += step) ly.is_src[i] = 0;
+    const uint4 z = make_uint4(0, 0, 0, 0);
+    const uint64_t bm = (uint64_t)sz.D * sz.Wp / 2;  // rows are whole 1 KiB lines
+    for (uint64_t i = i0; i < bm; i += step) {
+        reinterpret_cast<uint4 *>(ly.needs)[i] = z;
+        if (!sz.nbr) reinterpret_cast<uint4 *>(ly.holds)[i] = z;
+    }
 }
 
-__global__ void k_fill64(uint64_t *p, uint64_t n, uint64_t v)
+// Calls f(lane, bit) for every set bit of the 64 words that the lanes of a
+// wave hold (word `lane` is lane's x), bits shared out evenly over the lanes:
+// a dense word's work is a wave's and not one lane's (8x8 torus, 64 chunks:
+// the relay walks 77 -> 11 us).  `list`: room for 4,096 positions in LDS.
+template <class F>
+__device__ __forceinline__ void for_bits(uint64_t x, uint16_t *list, F f)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+    const uint32_t lane = threadIdx.x & 63u;
+    if (__builtin_amdgcn_ballot_w64(x != 0) == 0) return;
+    uint32_t inc = (uint32_t)__popcll(x);
+    for (uint32_t o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)inc, o);
+        if (lane >= o) inc += y;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    uint32_t at = inc - (uint32_t)__popcll(x);
+    for (; x; x &= x - 1) list[at++] = (uint16_t)(lane * 64u + (uint32_t)__builtin_ctzll(x));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t i = lane; i < total; i += 64) {
+        const uint32_t e = list[i];
+        f(e >> 6, e & 63u);
+    }
+    // (the next call's writes come after these reads)
+    __builtin_amdgcn_wave_barrier();
 }
-
-__global__ void k_ctl_reset(Control *ctl, unsigned long long max_sends)
-{
-    Control c = {};
-    c.max_sends = max_sends;
-    *ctl = c;
-}
+constexpr uint32_t BIT_LIST = 4096;  // 64 words
 
 // Mask of valid bits in word k of a chunk row.
 __device__ inline uint64_t tail_mask(uint64_t k, const Sizes &sz)
@@ -41,100 +75,67 @@ __device__ inline uint64_t tail_mask(uint64_t k, const Sizes &sz)
 
 // Conditions (Sec. 4.1): for every set bit of the NPU-centric bitmaps,
 // count precondition holders per chunk, mark chunks that are needed
-// somewhere, and check that pre/post bits sit on members of the chunk's
-// process group.  Grid: x over words, y over NPU rows.  The per-bit updates
-// are atomics whose results are not used (a second holder is found by
-// k_chunk_check), so a word's updates are in flight together; with a single
-// process group the membership of the row is checked once per word.
-__global__ void k_conditions(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t *post,
-                             const uint16_t *cg)
+// somewhere and NPUs that hold something, and check that pre/post bits sit on
+// members of the chunk's process group.  Grid: x over words, y over NPU rows.
+// The per-bit updates are atomics whose results are not used (a second holder
+// is found by the per-chunk check), so they are in flight together; with a
+// single process group the membership of the row is checked once per word.
+__global__ void __launch_bounds__(256) k_conditions(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t *post,
+                                                    const uint16_t *cg)
 {
-    const uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ uint16_t list[4][BIT_LIST];
+    const uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x, k0 = k & ~63ull;
     const uint32_t v = blockIdx.y;
-    if (k >= sz.W) return;
-    const uint64_t p = pre[(uint64_t)v * sz.W + k], q = post[(uint64_t)v * sz.W + k];
-    if (!(p | q)) return;
-    const uint64_t tm = tail_mask(k, sz);
-    if ((p | q) & ~tm) record_error(ly.ctl, ST_EINVAL, sz.C, v, BAD_TAIL);
-    const uint64_t bits = (p | q) & tm;
-    if (!cg) {
-        if (bits && !((ly.group_masks[v >> 6] >> (v & 63)) & 1ull))
-            record_error(ly.ctl, ST_EINVAL, (uint32_t)(k * 64 + __builtin_ctzll(bits)), v, BAD_MEMBER);
-    } else {
-        for (uint64_t x = bits; x; x &= x - 1) {
-            const uint32_t c = (uint32_t)(k * 64 + __builtin_ctzll(x));
-            const uint32_t g = cg[c];
-            if (g >= sz.G) {
-                record_error(ly.ctl, ST_EINVAL, c, v, BAD_GROUP);
-                continue;
-            }
-            if (!((ly.group_masks[(uint64_t)g * sz.WN + (v >> 6)] >> (v & 63)) & 1ull))
-                record_error(ly.ctl, ST_EINVAL, c, v, BAD_MEMBER);
-        }
+    uint64_t p = 0, q = 0;
+    if (k < sz.W) {
+        p = pre[(uint64_t)v * sz.W + k];
+        q = post[(uint64_t)v * sz.W + k];
     }
-    for (uint64_t x = p & tm; x; x &= x - 1) {
-        const uint32_t c = (uint32_t)(k * 64 + __builtin_ctzll(x));
+    if ((p | q) != 0) {
+        const uint64_t tm = tail_mask(k, sz);
+        if ((p | q) & ~tm) record_error(ly.ctl, ST_EINVAL, sz.C, v, BAD_TAIL);
+        p &= tm;
+        q &= tm;
+        if (p) ly.is_src[v] = 1u;
+        if (!cg && (p | q) && !((ly.group_masks[v >> 6] >> (v & 63)) & 1ull))
+            record_error(ly.ctl, ST_EINVAL, (uint32_t)(k * 64 + __builtin_ctzll(p | q)), v, BAD_MEMBER);
+    }
+    uint16_t *l = list[threadIdx.x >> 6];
+    if (cg) {
+        for_bits(p | q, l, [&](uint32_t w, uint32_t b) {
+            const uint32_t c = (uint32_t)(k0 + w) * 64u + b;
+            const uint32_t g = cg[c];
+            if (g >= sz.G) record_error(ly.ctl, ST_EINVAL, c, v, BAD_GROUP);
+            else if (!((ly.group_masks[(uint64_t)g * sz.WN + (v >> 6)] >> (v & 63)) & 1ull))
+                record_error(ly.ctl, ST_EINVAL, c, v, BAD_MEMBER);
+        });
+    }
+    for_bits(p, l, [&](uint32_t w, uint32_t b) {
+        const uint32_t c = (uint32_t)(k0 + w) * 64u + b;
         atomicAdd(&ly.holder_cnt[c], 1u);
         ly.chunk_src[c] = v;  // the one holder (several are an error, reported below)
-    }
-    for (uint64_t x = q & tm; x; x &= x - 1) {
-        const uint32_t c = (uint32_t)(k * 64 + __builtin_ctzll(x));
-        atomicOr(&ly.holder_cnt[c], FLAG_POST);
-    }
-}
-
-__global__ void k_chunk_check(Layout ly, Sizes sz)
-{
-    const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= sz.C) return;
-    const uint32_t h = ly.holder_cnt[c];
-    if ((h & FLAG_POST) && !(h & CNT_MASK)) record_error(ly.ctl, ST_EINVAL, (uint32_t)c, 0, NO_HOLDER);
-    if ((h & CNT_MASK) > 1u) record_error(ly.ctl, ST_EINVAL, (uint32_t)c, ly.chunk_src[c], TWO_HOLDERS);
-    if ((h & CNT_MASK) == 1u) ly.src_index[ly.chunk_src[c]] = 1u;
-}
-
-// Distinct sources -> dense rows of the shortest-path tables (one workgroup).
-__global__ void __launch_bounds__(1024) k_compact_sources(Layout ly, Sizes sz)
-{
-    __shared__ uint32_t part[1024];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t per = (sz.N + 1023) / 1024;
-    const uint32_t lo = tid * per, hi = min(lo + per, sz.N);
-    uint32_t s = 0;
-    for (uint32_t v = lo; v < hi; v++) s += ly.src_index[v];
-    part[tid] = s;
-    __syncthreads();
-    for (uint32_t off = 1; off < 1024; off <<= 1) {
-        uint32_t x = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += x;
-        __syncthreads();
-    }
-    uint32_t run = tid ? part[tid - 1] : 0;
-    for (uint32_t v = lo; v < hi; v++) {
-        if (ly.src_index[v]) {
-            ly.src_list[run] = v;
-            ly.src_index[v] = run++;
-        } else {
-            ly.src_index[v] = NONE32;
-        }
-    }
-    if (tid == 1023) ly.ctl->n_sources = part[1023];
+    });
+    for_bits(q, l, [&](uint32_t w, uint32_t b) { atomicOr(&ly.holder_cnt[(uint32_t)(k0 + w) * 64u + b], FLAG_POST); });
 }
 
 constexpr uint32_t SP_BATCH = 8;  // links whose loads one thread issues together
 
-// Shortest paths from one source per workgroup (Alg. 3 ShortestPath over
-// the alpha-beta link times): Bellman-Ford relaxation with the distances in
+// The per-chunk check of the conditions (shared out over the workgroups), and
+// shortest paths from one NPU per workgroup, those that hold a chunk (Alg. 3
+// ShortestPath over the alpha-beta link times): Bellman-Ford relaxation with the distances in
 // LDS, then the parent of each device = the smallest-id in-neighbour on a
 // shortest path (the tree the pruned BFS of Sec. 4.3 keeps).
 __global__ void __launch_bounds__(512) k_shortest_paths(Layout ly, Sizes sz)
 {
     extern __shared__ unsigned long long dist[];
     __shared__ uint32_t changed;
-    const uint32_t b = blockIdx.x, tid = threadIdx.x;
-    if (b >= ly.ctl->n_sources || ly.ctl->error) return;
-    const uint32_t s = ly.src_list[b];
+    const uint32_t s = blockIdx.x, tid = threadIdx.x;
+    for (uint64_t c = (uint64_t)s * blockDim.x + tid; c < sz.C; c += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t h = ly.holder_cnt[c];
+        if ((h & FLAG_POST) && !(h & CNT_MASK)) record_error(ly.ctl, ST_EINVAL, (uint32_t)c, 0, NO_HOLDER);
+        if ((h & CNT_MASK) > 1u) record_error(ly.ctl, ST_EINVAL, (uint32_t)c, ly.chunk_src[c], TWO_HOLDERS);
+    }
+    if (!ly.is_src[s]) return;
     for (uint32_t v = tid; v < sz.D; v += blockDim.x) dist[v] = v == s ? 0ull : NONE64;
     __syncthreads();
     for (uint32_t it = 0; it < sz.D; it++) {
@@ -170,7 +171,7 @@ __global__ void __launch_bounds__(512) k_shortest_paths(Layout ly, Sizes sz)
     }
     for (uint32_t v = tid; v < sz.D; v += blockDim.x) {
         const unsigned long long dv = dist[v];
-        ly.sp_dist[(uint64_t)b * sz.D + v] = dv;
+        ly.sp_dist[(uint64_t)s * sz.D + v] = dv;
         uint32_t par = NONE32;
         if (v != s && dv != NONE64) {
             const uint32_t i0 = ly.in_off[v], i1 = ly.in_off[v + 1];
@@ -190,30 +191,27 @@ __global__ void __launch_bounds__(512) k_shortest_paths(Layout ly, Sizes sz)
                 }
             }
         }
-        ly.sp_parent[(uint64_t)b * sz.D + v] = par;
+        ly.sp_parent[(uint64_t)s * sz.D + v] = par;
     }
 }
 
 // Condition distance = max over destinations of the shortest-path distance
 // (Alg. 3); destinations = postcondition and not precondition.
-__global__ void k_chunk_dist(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t *post)
+__global__ void __launch_bounds__(256) k_chunk_dist(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t *post)
 {
+    __shared__ uint16_t list[4][BIT_LIST];
     if (ly.ctl->error) return;
-    const uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x, k0 = k & ~63ull;
     const uint32_t v = blockIdx.y;
-    if (k >= sz.W) return;
-    const uint64_t x0 = post[(uint64_t)v * sz.W + k] & ~pre[(uint64_t)v * sz.W + k] & tail_mask(k, sz);
-    for (uint64_t x = x0; x; x &= x - 1) {
-        const uint32_t c = (uint32_t)(k * 64 + __builtin_ctzll(x));
-        const uint32_t row = ly.src_index[ly.chunk_src[c]];
-        const unsigned long long dv = ly.sp_dist[(uint64_t)row * sz.D + v];
-        if (dv == NONE64)
-            record_error(ly.ctl, ST_EUNREACHABLE, c, v, ly.chunk_src[c]);
-        else if (dv >= 0xFFFFFFFFull)
-            record_error(ly.ctl, ST_ERANGE, c, v, 1);
-        else
-            atomicMax(&ly.chunk_dist[c], dv);
-    }
+    uint64_t x = 0;
+    if (k < sz.W) x = post[(uint64_t)v * sz.W + k] & ~pre[(uint64_t)v * sz.W + k] & tail_mask(k, sz);
+    for_bits(x, list[threadIdx.x >> 6], [&](uint32_t w, uint32_t b) {
+        const uint32_t c = (uint32_t)(k0 + w) * 64u + b, s = ly.chunk_src[c];
+        const unsigned long long dv = ly.sp_dist[(uint64_t)s * sz.D + v];
+        if (dv == NONE64) record_error(ly.ctl, ST_EUNREACHABLE, c, v, s);
+        else if (dv >= 0xFFFFFFFFull) record_error(ly.ctl, ST_ERANGE, c, v, 1);
+        else atomicMax(&ly.chunk_dist[c], dv);
+    });
 }
 
 // Switch model: for every limited-switch row and chunk rank, how many of the
@@ -239,7 +237,7 @@ __global__ void k_adm_counts(Layout ly, Sizes sz)
 // Priority order (distance descending, then the SplitMix64 key ascending,
 // then chunk id): one stable sort of the bitwise-not of the distance (high
 // word) and the key's high word (low word), from chunk id order, then runs
-// of equal sort keys ordered by the key's low word (k_key_ties).
+// of equal sort keys ordered by the key's low word (k_rank).
 __global__ void k_keys_hash(Layout ly, Sizes sz, uint64_t seed)
 {
     const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -249,10 +247,18 @@ __global__ void k_keys_hash(Layout ly, Sizes sz, uint64_t seed)
     ly.sval[0][c] = (uint32_t)c;
 }
 
-// After the sort: the first thread of a run of equal sort keys (equal
+__device__ inline void set_rank(const Layout &ly, const Sizes &sz, uint32_t r, uint32_t c)
+{
+    ly.order[r] = c;
+    ly.rank[c] = r;
+    // (the counts of the array it shares are no longer read)
+    if (sz.nbr) ly.rank_src[r] = ly.chunk_src[c];
+}
+
+// After the sort: ranks.  The first thread of a run of equal sort keys (equal
 // distance and key high word; with random keys a run is rare and short)
-// orders the run by (key low word, chunk id), in place.
-__global__ void k_key_ties(Layout ly, Sizes sz, uint64_t seed)
+// orders the run by (key low word, chunk id), in place, and ranks it.
+__global__ void k_rank(Layout ly, Sizes sz, uint64_t seed)
 {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= sz.C) return;
@@ -260,8 +266,8 @@ __global__ void k_key_ties(Layout ly, Sizes sz, uint64_t seed)
     const uint64_t *k = ly.skey[cur];
     uint32_t *v = ly.sval[cur];
     const uint64_t ki = k[i];
-    if ((i > 0 && k[i - 1] == ki) || i + 1 >= sz.C || k[i + 1] != ki) return;
-    uint64_t j = i + 2;
+    if (i > 0 && k[i - 1] == ki) return;  // ranked by the run's first thread
+    uint64_t j = i + 1;
     while (j < sz.C && k[j] == ki) j++;
     // insertion sort; the stable sort left the run in chunk id order
     for (uint64_t a = i + 1; a < j; a++) {
@@ -275,17 +281,45 @@ __global__ void k_key_ties(Layout ly, Sizes sz, uint64_t seed)
         }
         v[b] = c;
     }
+    for (uint64_t a = i; a < j; a++) set_rank(ly, sz, (uint32_t)a, v[a]);
 }
 
-__global__ void k_rank(Layout ly, Sizes sz)
+// The same for at most SMALL_SORT chunks, in one workgroup and one launch from
+// the distances to the ranks: a bitonic sort in LDS by distance descending,
+// then the whole SplitMix64 key.
+__global__ void __launch_bounds__(1024) k_order_small(Layout ly, Sizes sz, uint64_t seed)
 {
-    const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= sz.C) return;
-    const uint32_t c = ly.sval[ly.ctl->sort_cur][r];
-    ly.order[r] = c;
-    ly.rank[c] = (uint32_t)r;
-    // (the counts of the array it shares are no longer read)
-    if (sz.nbr) ly.rank_src[r] = ly.chunk_src[c];
+    __shared__ uint64_t key[SMALL_SORT];
+    __shared__ uint32_t low[SMALL_SORT], val[SMALL_SORT];
+    const uint32_t tid = threadIdx.x;
+    uint32_t m = 64;
+    while (m < sz.C) m <<= 1;
+    for (uint32_t c = tid; c < m; c += 1024) {
+        uint64_t k = NONE64;
+        uint32_t lo = NONE32;
+        if (c < sz.C) {
+            const uint64_t h = splitmix64_key(seed, c);
+            k = ((uint64_t)(~(uint32_t)ly.chunk_dist[c]) << 32) | (h >> 32);
+            lo = (uint32_t)h;
+        }
+        key[c] = k;
+        low[c] = lo;
+        val[c] = c < sz.C ? c : NONE32;
+    }
+    bitonic_sort(m, [&](uint32_t a, uint32_t b) {
+        return key[a] != key[b] ? key[a] > key[b] : low[a] != low[b] ? low[a] > low[b] : val[a] > val[b];
+    }, [&](uint32_t a, uint32_t b) {
+        const uint64_t k = key[a];
+        key[a] = key[b];
+        key[b] = k;
+        uint32_t t = low[a];
+        low[a] = low[b];
+        low[b] = t;
+        t = val[a];
+        val[a] = val[b];
+        val[b] = t;
+    });
+    for (uint32_t r = tid; r < sz.C; r += 1024) set_rank(ly, sz, r, val[r]);
 }
 
 __global__ void k_holds(Layout ly, Sizes sz)
@@ -303,18 +337,19 @@ __global__ void k_holds(Layout ly, Sizes sz)
 // source.  A walk that meets a bit already set stops there: whoever set it
 // is a destination or a walk that continues upward.  Two walks may both
 // pass a device before either bit is visible; both then set it (harmless).
-__global__ void k_needs(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t *post)
+__global__ void __launch_bounds__(256) k_needs(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t *post)
 {
+    __shared__ uint16_t list[4][BIT_LIST];
     if (ly.ctl->error) return;
-    const uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x, k0 = k & ~63ull;
     const uint32_t v = blockIdx.y;
-    if (k >= sz.W) return;
-    const uint64_t x0 = post[(uint64_t)v * sz.W + k] & ~pre[(uint64_t)v * sz.W + k] & tail_mask(k, sz);
-    for (uint64_t x = x0; x; x &= x - 1) {
-        const uint32_t c = (uint32_t)(k * 64 + __builtin_ctzll(x));
-        const uint32_t s = ly.chunk_src[c], row = ly.src_index[s], r = ly.rank[c];
+    uint64_t x = 0;
+    if (k < sz.W) x = post[(uint64_t)v * sz.W + k] & ~pre[(uint64_t)v * sz.W + k] & tail_mask(k, sz);
+    for_bits(x, list[threadIdx.x >> 6], [&](uint32_t wo, uint32_t b) {
+        const uint32_t c = (uint32_t)(k0 + wo) * 64u + b;
+        const uint32_t s = ly.chunk_src[c], r = ly.rank[c];
         const uint64_t bit = 1ull << (r & 63);
-        const uint32_t *par = ly.sp_parent + (uint64_t)row * sz.D;
+        const uint32_t *par = ly.sp_parent + (uint64_t)s * sz.D;
         uint32_t u = v;
         for (uint32_t hop = 0; hop < sz.D && u != s && u < sz.D; hop++) {
             unsigned long long *w = (unsigned long long *)&ly.needs[(uint64_t)u * sz.Wp + (r >> 6)];
@@ -323,7 +358,7 @@ __global__ void k_needs(Layout ly, Sizes sz, const uint64_t *pre, const uint64_t
             if ((atomicOr(w, bit) & bit) && hop > 0) break;
             u = next;
         }
-    }
+    });
 }
 
 // Candidates of every link at the start (one wave per destination-major
@@ -412,109 +447,123 @@ __global__ void k_init_match(Layout ly, Sizes sz)
     }
 }
 
+// Inclusive scan of one value per thread over the workgroup (blockDim.x
+// threads, whole waves), `part`: a word of LDS per wave.
+__device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t *part)
+{
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    for (uint32_t o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)x, o);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    for (uint32_t w = 0; w < wave; w++) x += part[w];
+    return x;
+}
+
 // Neighbour-stepped matcher: the columns of device d are the chunks it needs
 // in priority order.  Their number before each word of the needs row, and in
-// all (one workgroup per device, a thread per run of adjacent words).
-__global__ void __launch_bounds__(256) k_need_prefix(Layout ly, Sizes sz)
+// all: one workgroup per device, four adjacent words per thread (at most
+// 2^18 chunks, so one pass), loaded and written as whole 16-byte pieces.
+__global__ void __launch_bounds__(1024) k_need_prefix(Layout ly, Sizes sz)
 {
-    __shared__ uint32_t part[256];
-    const uint32_t d = blockIdx.x, tid = threadIdx.x;
-    const uint32_t W = ly.ctl->error ? 0u : (uint32_t)sz.W;
+    static_assert(NBR_MAX_CHUNKS <= 1024u * 4u * 64u, "four words per thread hold a row");
+    __shared__ uint32_t part[16];
+    const uint32_t d = blockIdx.x, w = 4u * threadIdx.x;
     const uint64_t *row = ly.needs + (uint64_t)d * sz.Wp;
-    uint32_t *pre = ly.need_pre + (uint64_t)d * sz.Wp;
-    const uint32_t per = (W + 255u) / 256u, lo = min(tid * per, W), hi = min(lo + per, W);
-    uint32_t c = 0;
-    for (uint32_t w = lo; w < hi; w++) c += (uint32_t)__popcll(row[w]);
-    part[tid] = c;
-    __syncthreads();
-    for (uint32_t off = 1; off < 256; off <<= 1) {
-        const uint32_t x = tid >= off ? part[tid - off] : 0u;
-        __syncthreads();
-        part[tid] += x;
-        __syncthreads();
+    uint32_t c[4] = {0, 0, 0, 0};
+    const bool in = w < sz.Wp && !ly.ctl->error;  // (words past the last chunk's are zero)
+    if (in) {
+        const ulonglong2 a = *reinterpret_cast<const ulonglong2 *>(row + w), b = *reinterpret_cast<const ulonglong2 *>(row + w + 2);
+        c[0] = (uint32_t)__popcll(a.x);
+        c[1] = (uint32_t)__popcll(a.y);
+        c[2] = (uint32_t)__popcll(b.x);
+        c[3] = (uint32_t)__popcll(b.y);
     }
-    uint32_t run = part[tid] - c;
-    for (uint32_t w = lo; w < hi; w++) {
-        pre[w] = run;
-        run += (uint32_t)__popcll(row[w]);
-    }
-    if (tid == 255) ly.dest_cols[d] = part[255];
+    const uint32_t n = c[0] + c[1] + c[2] + c[3], inc = block_scan(n, part), p = inc - n;
+    if (in)
+        *reinterpret_cast<uint4 *>(ly.need_pre + (uint64_t)d * sz.Wp + w) =
+            make_uint4(p, p + c[0], p + c[0] + c[1], p + c[0] + c[1] + c[2]);
+    if (threadIdx.x == blockDim.x - 1u) ly.dest_cols[d] = inc;
 }
 
-// Send-log segments (a device's transfers are its columns) and candidate rows
-// of all devices: exclusive prefixes of cols and in-links * ceil(cols / 64).
-__global__ void __launch_bounds__(1024) k_nbr_offsets(Layout ly, Sizes sz, uint64_t cand_words)
-{
-    __shared__ unsigned long long pl[1024], pc[1024];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t per = (sz.D + 1023) / 1024;
-    const uint32_t lo = min(tid * per, sz.D), hi = min(lo + per, sz.D);
-    unsigned long long s = 0, r = 0;
-    for (uint32_t v = lo; v < hi; v++) {
-        const uint32_t m = ly.dest_cols[v];
-        s += m;
-        r += (unsigned long long)(ly.in_off[v + 1] - ly.in_off[v]) * ((m + 63u) >> 6);
-    }
-    pl[tid] = s;
-    pc[tid] = r;
-    __syncthreads();
-    for (uint32_t off = 1; off < 1024; off <<= 1) {
-        const unsigned long long x = tid >= off ? pl[tid - off] : 0, y = tid >= off ? pc[tid - off] : 0;
-        __syncthreads();
-        pl[tid] += x;
-        pc[tid] += y;
-        __syncthreads();
-    }
-    unsigned long long rl = pl[tid] - s, rc = pc[tid] - r;
-    for (uint32_t v = lo; v < hi; v++) {
-        const uint32_t m = ly.dest_cols[v];
-        ly.dest_log[v] = rl;
-        ly.cand_off[v] = rc;
-        rl += m;
-        rc += (unsigned long long)(ly.in_off[v + 1] - ly.in_off[v]) * ((m + 63u) >> 6);
-    }
-    if (tid == 1023) {
-        Control *ctl = ly.ctl;
-        ctl->needs_total = pl[1023];
-        if (!ctl->error && pl[1023] > ctl->max_sends)
-            record_error(ctl, ST_ENOMEM, (uint32_t)(pl[1023] >> 32), (uint32_t)pl[1023], 0);
-        else if (!ctl->error && pc[1023] > cand_words)
-            record_error(ctl, ST_EINTERNAL, 4, 0, 0);
-    }
-}
-
-// Column lists and initial candidate rows (one workgroup per device): a
-// thread per needs word writes the ranks of its columns, then a thread per
-// column looks up the chunk's holder and, when that is the source of an
-// in-link, sets the column's bit in the link's row.
+// Offsets, column lists and initial candidate rows (one workgroup per
+// device).  Every workgroup sums the columns of the devices before its own
+// (its send-log segment: a device's transfers are its columns) and their
+// candidate rows (in-links * ceil(cols / 64) words).  Then a thread per needs
+// word writes the ranks of its columns, and a thread per column looks up the
+// chunk's holder and, when that is the source of an in-link, sets the
+// column's bit in the link's row.
+constexpr uint32_t COL_BATCH = 4;  // columns whose lookups one thread has in flight
 __global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
 {
     __shared__ uint8_t link_of[MAX_DEVICES_SP];  // in-link of d whose source is the device, 0xFF none
+    __shared__ unsigned long long sums[4];       // columns and row words: before d, of all
     const uint32_t d = blockIdx.x, tid = threadIdx.x;
     // the published entries start as those of windows -4 to -1
     for (uint32_t i = d * 1024u + tid; i < 4u * sz.pub_n; i += gridDim.x * 1024u)
         ly.pub[i] = (uint64_t)((0xFFCu + i / sz.pub_n) << NBR_TAG_SHIFT) << 32;
-    if (ly.ctl->error) return;
+    if (tid < 4) sums[tid] = 0;
+    for (uint32_t v = tid; v < sz.D; v += 1024) link_of[v] = 0xFFu;
+    __syncthreads();
+    {
+        unsigned long long s[4] = {0, 0, 0, 0};
+        for (uint32_t v = tid; v < sz.D; v += 1024) {
+            const uint32_t m = ly.dest_cols[v];
+            const unsigned long long r = (unsigned long long)(ly.in_off[v + 1] - ly.in_off[v]) * ((m + 63u) >> 6);
+            s[0] += v < d ? m : 0u;
+            s[1] += v < d ? r : 0ull;
+            s[2] += m;
+            s[3] += r;
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+            for (int o = 32; o; o >>= 1) s[i] += __shfl_xor(s[i], o);
+            if ((tid & 63u) == 0) atomicAdd(&sums[i], s[i]);
+        }
+    }
+    __syncthreads();
+    const unsigned long long log0 = sums[0], off = sums[1], total = sums[2];
+    if (tid == 0) {
+        ly.dest_log[d] = log0;
+        ly.cand_off[d] = off;
+        if (d == 0) {
+            Control *ctl = ly.ctl;
+            ctl->needs_total = total;
+            if (!ctl->error && total > ctl->max_sends)
+                record_error(ctl, ST_ENOMEM, (uint32_t)(total >> 32), (uint32_t)total, 0);
+            else if (!ctl->error && sums[3] > sz.cand_words)
+                record_error(ctl, ST_EINTERNAL, 4, 0, 0);
+        }
+    }
     const uint32_t M = ly.dest_cols[d];
-    if (M == 0) return;
+    if (M == 0 || total > sz.max_sends || sums[3] > sz.cand_words) return;
     const uint32_t base = ly.in_off[d], n = ly.in_off[d + 1] - base, mw = (M + 63u) >> 6;
-    unsigned long long *rows = (unsigned long long *)(ly.cand + ly.cand_off[d]);
-    uint32_t *rank = ly.col_rank + ly.dest_log[d];
+    unsigned long long *rows = (unsigned long long *)(ly.cand + off);
+    uint32_t *rank = ly.col_rank + log0;
     const uint64_t *need = ly.needs + (uint64_t)d * sz.Wp;
     const uint32_t *pre = ly.need_pre + (uint64_t)d * sz.Wp;
-    for (uint32_t v = tid; v < sz.D; v += 1024) link_of[v] = 0xFFu;
     for (uint32_t i = tid; i < n * mw; i += 1024) rows[i] = 0ull;
+    for (uint32_t j = tid; j < n; j += 1024) link_of[ly.slot_src[base + j]] = (uint8_t)j;
     for (uint32_t w = tid; w < (uint32_t)sz.W; w += 1024) {
         uint32_t c = pre[w];
         for (uint64_t x = need[w]; x; x &= x - 1) rank[c++] = w * 64u + (uint32_t)__builtin_ctzll(x);
     }
     __syncthreads();
-    for (uint32_t j = tid; j < n; j += 1024) link_of[ly.slot_src[base + j]] = (uint8_t)j;
-    __syncthreads();
-    for (uint32_t c = tid; c < M; c += 1024) {
-        const uint32_t s = ly.rank_src[rank[c]];
-        const uint32_t j = s != NONE32 ? link_of[s] : 0xFFu;
-        if (j != 0xFFu) atomicOr(&rows[(uint64_t)j * mw + (c >> 6)], 1ull << (c & 63u));
+    for (uint32_t c0 = tid; c0 < M; c0 += 1024 * COL_BATCH) {
+        uint32_t r[COL_BATCH], s[COL_BATCH];
+#pragma unroll
+        for (uint32_t u = 0; u < COL_BATCH; u++) r[u] = rank[min(c0 + 1024u * u, M - 1u)];
+#pragma unroll
+        for (uint32_t u = 0; u < COL_BATCH; u++) s[u] = ly.rank_src[r[u]];
+#pragma unroll
+        for (uint32_t u = 0; u < COL_BATCH; u++) {
+            const uint32_t c = c0 + 1024u * u;
+            if (c >= M) continue;
+            const uint32_t j = s[u] != NONE32 ? link_of[s[u]] : 0xFFu;
+            if (j != 0xFFu) atomicOr(&rows[(uint64_t)j * mw + (c >> 6)], 1ull << (c & 63u));
+        }
     }
 }
 
@@ -526,35 +575,24 @@ hipError_t launch_setup(const Layout &ly, const Sizes &sz, const uint64_t *pre, 
                         const uint16_t *chunk_group, uint64_t seed, hipStream_t st)
 {
     const uint32_t T = 256;
-    k_ctl_reset<<<1, 1, 0, st>>>(ly.ctl, sz.max_sends);
-    const uint64_t C = sz.C;
-    if (C) {
-        k_fill32<<<min(blocks_for(C, T), 4096u), T, 0, st>>>(ly.holder_cnt, C, 0);
-        k_fill32<<<min(blocks_for(C, T), 4096u), T, 0, st>>>(ly.chunk_src, C, NONE32);
-        k_fill64<<<min(blocks_for(C, T), 4096u), T, 0, st>>>(ly.chunk_dist, C, 0);
-    }
-    k_fill32<<<blocks_for(sz.N, T), T, 0, st>>>(ly.src_index, sz.N, 0);
-    const uint64_t bm = (uint64_t)sz.D * sz.Wp;
-    if (!sz.nbr) k_fill64<<<min(blocks_for(bm, T), 8192u), T, 0, st>>>(ly.holds, bm, 0);
-    k_fill64<<<min(blocks_for(bm, T), 8192u), T, 0, st>>>(ly.needs, bm, 0);
+    const uint64_t C = sz.C, bm = (uint64_t)sz.D * sz.Wp / 2;
+    k_reset<<<std::max(1u, std::min(blocks_for(std::max(bm, C), T), 2048u)), T, 0, st>>>(ly, sz);
     const dim3 gw(blocks_for(sz.W ? sz.W : 1, T), sz.N);
     if (sz.W) k_conditions<<<gw, T, 0, st>>>(ly, sz, pre, post, chunk_group);
-    if (C) k_chunk_check<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
-    k_compact_sources<<<1, 1024, 0, st>>>(ly, sz);
     k_shortest_paths<<<sz.N, 512, sizeof(unsigned long long) * sz.D, st>>>(ly, sz);
     if (sz.W) k_chunk_dist<<<gw, T, 0, st>>>(ly, sz, pre, post);
-    if (C) {
+    if (C && C <= SMALL_SORT) {
+        k_order_small<<<1, 1024, 0, st>>>(ly, sz, seed);
+    } else if (C) {
         k_keys_hash<<<blocks_for(C, T), T, 0, st>>>(ly, sz, seed);
         const hipError_t e = radix_sort_pairs(ly, C, 0, 8, sz.max_tiles, true, st);
         if (e != hipSuccess) return e;
-        k_key_ties<<<blocks_for(C, T), T, 0, st>>>(ly, sz, seed);
-        k_rank<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
-        if (!sz.nbr) k_holds<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
+        k_rank<<<blocks_for(C, T), T, 0, st>>>(ly, sz, seed);
     }
+    if (C && !sz.nbr) k_holds<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
     if (sz.W) k_needs<<<gw, T, 0, st>>>(ly, sz, pre, post);
     if (sz.nbr) {
-        k_need_prefix<<<sz.D, 256, 0, st>>>(ly, sz);
-        k_nbr_offsets<<<1, 1024, 0, st>>>(ly, sz, sz.cand_words);
+        k_need_prefix<<<sz.D, (uint32_t)std::min<uint64_t>(1024, ((sz.W + 3) / 4 + 63) / 64 * 64 + (sz.W ? 0 : 64)), 0, st>>>(ly, sz);
         k_columns<<<sz.D, 1024, 0, st>>>(ly, sz);
         return hipGetLastError();
     }

@@ -386,7 +386,66 @@ __global__ void k_reverse_keys(Layout ly, uint64_t n)
     ly.skey[cur][i] = ((uint64_t)tr << 32) | ly.lrev[l];
 }
 
+// The whole output stage of at most SMALL_SORT transfers in one workgroup and
+// one launch: bitonic sorts of the log in LDS (its keys are unique, so no
+// stability is needed), the schedule, and the control block written to the
+// host's copy.  The number of transfers is read here, so the launch need not
+// wait for the host to learn it.
+__global__ void __launch_bounds__(1024) k_out_small(Layout ly, int op, uint32_t *host_ctl)
+{
+    __shared__ uint64_t key[SMALL_SORT];
+    __shared__ uint32_t val[SMALL_SORT];
+    const uint32_t tid = threadIdx.x;
+    const Control *ctl = ly.ctl;
+    const uint32_t n = log_complete(ly) && ctl->needs_total <= SMALL_SORT ? (uint32_t)ctl->needs_total : 0u;
+    uint32_t m = 64;
+    while (m < n) m <<= 1;
+    auto above = [&](uint32_t a, uint32_t b) { return key[a] > key[b]; };
+    auto swap = [&](uint32_t a, uint32_t b) {
+        const uint64_t k = key[a];
+        key[a] = key[b];
+        key[b] = k;
+        const uint32_t v = val[a];
+        val[a] = val[b];
+        val[b] = v;
+    };
+    uint4 *out = reinterpret_cast<uint4 *>(ly.out);
+    if (n) {
+        const uint32_t cstar = ctl->cstar;
+        for (uint32_t i = tid; i < m; i += 1024) {
+            key[i] = i < n ? ly.skey[0][i] : NONE64;
+            val[i] = i < n ? ly.sval[0][i] : 0u;
+        }
+        if (op != 1) {
+            // the forward schedule, after the reversed one in an All-Reduce
+            bitonic_sort(m, above, swap);
+            for (uint32_t i = tid; i < n; i += 1024)
+                out[(op == 2 ? n : 0u) + i] = make_uint4((uint32_t)key[i], ly.order[val[i]],
+                                                         (uint32_t)(key[i] >> 32) + (op == 2 ? cstar : 0u), 0u);
+        }
+        if (op != 0) {
+            // (l, c, t) -> (reverse(l), c, C* - t - T[l])
+            for (uint32_t i = tid; i < n; i += 1024) {
+                const uint32_t l = (uint32_t)key[i], t = (uint32_t)(key[i] >> 32);
+                key[i] = ((uint64_t)(cstar - t - ly.ltime[l]) << 32) | ly.lrev[l];
+            }
+            bitonic_sort(m, above, swap);
+            for (uint32_t i = tid; i < n; i += 1024)
+                out[i] = make_uint4((uint32_t)key[i], ly.order[val[i]], (uint32_t)(key[i] >> 32), 1u);
+        }
+    }
+    if (tid < sizeof(Control) / 4)
+        __hip_atomic_store(&host_ctl[tid], reinterpret_cast<const uint32_t *>(ctl)[tid], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace
+
+hipError_t launch_output_small(const Layout &ly, int op, Control *host_ctl, hipStream_t st)
+{
+    k_out_small<<<1, 1024, 0, st>>>(ly, op, reinterpret_cast<uint32_t *>(host_ctl));
+    return hipGetLastError();
+}
 
 hipError_t radix_sort_pairs(const Layout &ly, uint64_t n, int byte_lo, int byte_hi, uint32_t max_tiles,
                             bool reset_cur, hipStream_t st, bool time_gate)
