@@ -55,7 +55,7 @@ constexpr uint32_t NBR_SPIN_LIMIT = 1u << 24;
 // takes at least 1 ns, so it never ends at 0).
 constexpr uint32_t NBR_RANK = (1u << 19) - 1u;
 static_assert(NBR_MAX_CHUNKS <= NBR_RANK, "a chunk rank fits in 19 bits");
-constexpr uint32_t NBR_TAG = 0xFFFu << NBR_TAG_SHIFT;
+constexpr uint32_t NBR_BEHIND = 0x800u << NBR_TAG_SHIFT;  // top bit of a tag difference
 constexpr uint32_t NBR_FINAL = 1u << 31;
 __device__ __forceinline__ uint32_t nbr_tag(uint32_t k) { return (k & 0xFFFu) << NBR_TAG_SHIFT; }
 
@@ -273,7 +273,10 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
                 for (uint32_t u = 0; u < PPL; u++) {
                     if (PPL > 2 && 64u * u >= np) break;
                     const uint32_t hi = (uint32_t)(e[u] >> 32);
-                    ok = ok && ((int32_t)hi < 0 || ((hi ^ (dep[u] ? g3 : g1)) & NBR_TAG) == 0);
+                    // the tag has reached the wanted one (modulo 4,096): a
+                    // source is never ahead of it, but a reader that does not
+                    // read this device's entries in turn may be
+                    ok = ok && ((int32_t)hi < 0 || ((hi - (dep[u] ? g3 : g1)) & NBR_BEHIND) == 0);
                 }
                 if (ballot(!ok) == 0) break;
                 if ((++spins & 15u) == 0 && give_up(ctl, spins, d, k)) {
