@@ -37,6 +37,8 @@ struct pccl_ctx {
     std::vector<uint32_t> pub_off;         // where each device's published link entries start
     std::vector<uint32_t> poll_off, poll;  // entries each device polls in the neighbour-stepped matcher
     bool poll_built = false;               // the lists match the topology
+    std::vector<uint32_t> out_off, out_dst, slot_out;  // out-links by device: their destinations; a slot's index among them
+    uint32_t max_out = 0;                  // most out-links of one device
     uint32_t max_poll = 0, max_in = 0;     // most polled entries / in-links of one device
     std::vector<uint32_t> wave_dest;  // destination of (pass, wave) in the matching kernel
     std::vector<uint32_t> wave_part;  // its part when the destination is split over a workgroup's waves
@@ -77,11 +79,12 @@ struct pccl_ctx {
     // built by the plan; IMG_PARTS pieces at img_off[k], img_len[k] bytes
     char *pin_img = nullptr;
     size_t pin_img_cap = 0;
-    size_t img_off[17] = {}, img_len[17] = {};
+    size_t img_off[20] = {}, img_len[20] = {};
     // neighbour-stepped matching kernel: chosen by the plan (nbr_ok: not
     // ruled out by a workspace only the windowed kernel fits in)
     bool nbr_ok = true, nbr = false;
     size_t nbr_lds = 0;            // LDS per workgroup
+    bool nbr_prune = false;        // the setup drops polled entries no needed chunk can come through
     uint32_t nbr_spread = 1;       // every how many workgroups of the launch one holds devices
     uint64_t serial = 0;           // unique per context
     uint64_t static_call = 0;      // the static-scratch call whose result this context holds
@@ -212,9 +215,13 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     ly.skey[0] = cv.take<uint64_t>(nsort);
     // the neighbour-stepped matcher keeps its candidate rows and column list
     // in the second sort buffers, which no sort uses between the priority
-    // order and the output: in-links * ceil(cols / 64) words per device
+    // order and the output: per device in-links * (w + ceil(w / 64)) words,
+    // w = ceil(cols / 64)
     uint64_t cand = 0;
-    if (c->nbr) cand = std::min<uint64_t>(L * sz.W, (uint64_t)c->max_in * ((max_sends + 63) / 64) + L);
+    if (c->nbr) {
+        cand = std::min<uint64_t>(L * sz.W, (uint64_t)c->max_in * ((max_sends + 63) / 64) + L);
+        cand += cand / 64 + L;
+    }
     sz.cand_words = cand;
     ly.skey[1] = cv.take<uint64_t>(std::max(nsort, cand));
     ly.sval[0] = cv.take<uint32_t>(nsort);
@@ -236,6 +243,17 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
         ly.dest_cols = cv.take<uint32_t>(D);
         ly.poll_off = cv.take<uint32_t>(D + 1);
         ly.poll = cv.take<uint32_t>(c->poll.size());
+        sz.nbr_prune = c->nbr_prune ? 1u : 0u;
+        if (c->nbr_prune) {
+            ly.out_off = cv.take<uint32_t>(D + 1);
+            ly.out_dst = cv.take<uint32_t>(L);
+            ly.slot_out = cv.take<uint32_t>(L);
+            ly.rel = cv.take<uint64_t>(L);
+            ly.feeds = cv.take<uint64_t>(L);
+            ly.back = cv.take<uint32_t>(L);
+            ly.poll_cnt = cv.take<uint32_t>(D);
+            ly.poll_use = cv.take<uint32_t>(c->poll.size() + L);
+        }
     } else {
         ly.holds = cv.take<uint64_t>(D * sz.Wp);
         ly.busy = cv.take<uint32_t>(L);
@@ -601,7 +619,7 @@ pccl_status ensure_pinned(pccl_ctx *c, char **buf, size_t *cap, size_t bytes)
     return PCCL_OK;
 }
 
-constexpr int IMG_PARTS = 17;
+constexpr int IMG_PARTS = 20;
 
 // Parts of destination d for a split over the waves of a workgroup:
 // consecutive in-links, at most `target` links and MAX_PAIRS arrival pairs
@@ -650,10 +668,24 @@ void build_poll(pccl_ctx *c)
     c->pub_off[0] = 0;
     for (uint32_t d = 0; d < D; d++)
         c->pub_off[d + 1] = c->pub_off[d] + ((c->in_off[d + 1] - c->in_off[d] + 15u) & ~15u);
-    std::vector<uint32_t> out_off(D + 2, 0), out_slot(L), polled(D, NONE32);
+    std::vector<uint32_t> out_slot(L), polled(D, NONE32), &out_off = c->out_off;
+    out_off.assign(D + 2, 0);
     for (uint32_t sl = 0; sl < L; sl++) out_off[c->slot_src[sl] + 2]++;
-    for (uint32_t v = 0; v < D; v++) out_off[v + 2] += out_off[v + 1];
-    for (uint32_t sl = 0; sl < L; sl++) out_slot[out_off[c->slot_src[sl] + 1]++] = sl;
+    c->max_out = 0;
+    for (uint32_t v = 0; v < D; v++) {
+        c->max_out = std::max(c->max_out, out_off[v + 2]);
+        out_off[v + 2] += out_off[v + 1];
+    }
+    c->out_dst.resize(L);
+    c->slot_out.resize(L);
+    for (uint32_t sl = 0; sl < L; sl++) {
+        const uint32_t k = out_off[c->slot_src[sl] + 1]++;
+        out_slot[k] = sl;
+        c->out_dst[k] = c->dst[c->slot_link[sl]];
+    }
+    out_off.resize(D + 1);
+    for (uint32_t v = 0; v < D; v++)
+        for (uint32_t k = out_off[v]; k < out_off[v + 1]; k++) c->slot_out[out_slot[k]] = k - out_off[v];
     c->poll_off.resize(D + 1);
     c->poll.resize(most);
     uint32_t *q = c->poll.data();
@@ -670,7 +702,7 @@ void build_poll(pccl_ctx *c)
                 }
         }
         for (uint32_t k = out_off[d]; k < out_off[d + 1]; k++) {
-            const uint32_t sl = out_slot[k], v = c->dst[c->slot_link[sl]];
+            const uint32_t sl = out_slot[k], v = c->out_dst[k];
             if (polled[v] != d) *q++ = ((c->pub_off[v] + sl - in_off[v]) << 8) | 0xFFu;
         }
         c->max_poll = std::max<uint32_t>(c->max_poll, (uint32_t)(q - first));
@@ -691,6 +723,7 @@ void build_poll(pccl_ctx *c)
 // with the windowed kernel.
 bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
 {
+    c->nbr_prune = false;
     if (!c->nbr_ok || c->sw_active || c->D == 0 || c->L == 0 || c->C > NBR_MAX_CHUNKS) return false;
     uint32_t tmax = 0;
     for (uint32_t t : c->T) tmax = std::max(tmax, t);
@@ -746,6 +779,9 @@ bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
     }
     if (!spread) return false;
     c->nbr_spread = spread;
+    // worth its setup (0.03-0.06 ms) where some device polls several entries
+    // per lane; the relations are masks over a device's out-links
+    c->nbr_prune = c->max_poll > 64 && c->max_out <= 64;
     c->wpb = (int)w;
     c->grid = (int)grid;
     c->alone = alone;
@@ -881,6 +917,7 @@ pccl_status plan(pccl_ctx *c)
     }
     int lds_cu = 0;
     HIP_OR_FAIL(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, c->device));
+    c->nbr_prune = false;
     c->nbr = must.empty() && plan_nbr(c, (size_t)lds_cu, n_heavy);
     if (!c->nbr) {
         st = plan_windowed(c, must, need_w, n_heavy, desc_ok, (size_t)lds_cu, Wp);
@@ -907,7 +944,10 @@ pccl_status plan(pccl_ctx *c)
         {c->swt.data(), c->sw_active ? 4ull * c->swt.size() : 0ull},
         {c->poll_off.data(), c->nbr ? 4ull * c->poll_off.size() : 0ull},
         {c->poll.data(), c->nbr ? 4ull * c->poll.size() : 0ull},
-        {c->pub_off.data(), c->nbr ? 4ull * c->pub_off.size() : 0ull}};
+        {c->pub_off.data(), c->nbr ? 4ull * c->pub_off.size() : 0ull},
+        {c->out_off.data(), c->nbr_prune ? 4ull * c->out_off.size() : 0ull},
+        {c->out_dst.data(), c->nbr_prune ? 4ull * c->out_dst.size() : 0ull},
+        {c->slot_out.data(), c->nbr_prune ? 4ull * c->slot_out.size() : 0ull}};
     size_t total = 0;
     for (int k = 0; k < IMG_PARTS; k++) {
         c->img_off[k] = total;
@@ -1255,7 +1295,8 @@ static pccl_status upload(pccl_ctx *c)
     void *dst[IMG_PARTS] = {ly.lsrc,      ly.ldst,     ly.ltime,      ly.lrev,      ly.in_off,
                             ly.slot_link, ly.slot_src, ly.slot_time,  ly.slot_cum,  ly.dest_pairs,
                             ly.wave_dest, ly.wave_part, ly.group_masks, const_cast<uint32_t *>(ly.sw.grp),
-                            ly.poll_off,  ly.poll,     ly.pub_off};
+                            ly.poll_off,  ly.poll,     ly.pub_off,    ly.out_off,   ly.out_dst,
+                            ly.slot_out};
     for (int k = 0; k < IMG_PARTS; k++)
         if (c->img_len[k])
             HIP_OR_FAIL(c, hipMemcpyAsync(dst[k], c->pin_img + c->img_off[k], c->img_len[k], hipMemcpyHostToDevice, st));

@@ -44,8 +44,18 @@ constexpr uint8_t SW_NONE8 = 0xFF;
 constexpr uint32_t NBR_MAX_CHUNKS = 1u << 18;  // two summary levels over rows of 64-bit words
 constexpr uint32_t NBR_TAG_SHIFT = 19;         // published entry, high word: window tag above the chunk rank
 constexpr uint32_t NBR_XCDS = 8;               // workgroups go to the XCDs in turn
+constexpr uint32_t NBR_COUNT_SHIFT = 20;       // column list: above the rank, the in-neighbours that ever hold the chunk
+constexpr uint32_t NBR_RANK_MASK = (1u << NBR_COUNT_SHIFT) - 1u;
 constexpr uint32_t NBR_MAX_POLL = 512;         // entries one device polls per window
 constexpr uint32_t NBR_MAX_RATIO = 64;         // largest link time over the smallest
+
+// Candidate words of a device with n in-links and m columns: the rows' words
+// and their summary words.
+inline __host__ __device__ uint64_t cand_size(uint64_t n, uint64_t m)
+{
+    const uint64_t mw = (m + 63) >> 6;
+    return n * (mw + ((mw + 63) >> 6));
+}
 
 // Status codes mirrored from the public header.
 enum : uint32_t {
@@ -166,13 +176,20 @@ struct Layout {
     // neighbour-stepped matching kernel
     uint64_t *pub;            // [4 * Sizes::pub_n] published link entries, four windows alternating
     uint32_t *pub_off;        // [D+1] a device's first entry (its in-links in slot order)
-    uint64_t *cand;           // candidate rows: per device its in-links' rows of ceil(cols / 64) words, from cand_off
+    uint64_t *cand;           // per device, from cand_off: candidate rows (word by word, in-links adjacent) and their summaries
     uint64_t *cand_off;       // [D]
     uint32_t *need_pre;       // [D * Wp] columns of the device before each word of its needs row
     uint32_t *col_rank;       // chunk rank of every column, device d's from its send-log segment start
     uint32_t *dest_cols;      // [D] columns (chunks the device needs)
     uint32_t *rank_src;       // [C] priority position -> holder
     uint32_t *poll_off, *poll; // [D+1], entries a device polls: entry << 8 | in-link fed (0xFF none)
+    // when polled entries are pruned: out-links by device (their destinations,
+    // a slot's index among its source's); per slot the mask of the out-links
+    // of its destination that what comes in there may go on over; the lists
+    uint32_t *out_off, *out_dst, *slot_out;
+    uint64_t *rel, *feeds;    // [L] by slot; the destination's out-links whose destinations feed the source
+    uint32_t *back;           // [L] by slot: 1 if the destination feeds the source
+    uint32_t *poll_cnt, *poll_use;  // [D], device d's list from poll_off[d] + out_off[d]
     SwTab sw;                 // switch-model tables (null pointers without a switch model)
     // output
     void *out;                // pccl_send [2 * max_sends]
@@ -191,6 +208,7 @@ struct Sizes {
     uint32_t resident; // every wave of the matching kernel owns one destination (or part) for the whole run
     uint32_t sw_gate;  // both matching kernels are queued; Control::sw_binds picks the one that runs
     uint64_t cand_words;  // capacity of Layout::cand
+    uint32_t nbr_prune; // the polled entries are pruned by the setup
     uint32_t pub_n;    // published entries of one window
     uint32_t nbr;      // the neighbour-stepped matching kernel runs
     uint32_t sw_nbt;   // limited-switch rows of the switch tables (0: no switch model or no limited switch)

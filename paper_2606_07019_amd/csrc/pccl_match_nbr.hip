@@ -96,9 +96,9 @@ extern __shared__ __attribute__((aligned(16))) unsigned char nbr_lds[];
 constexpr uint32_t IN_ROW = 1, IN_NEED = 2, IN_RANK = 4;
 struct Tables {
     uint32_t live_at, top_at, mid_at, row_at, need_at, pre_at, rank_at;
-    uint32_t ms, rs;        // strides of mid and row
+    uint32_t ms, n;         // stride of mid; in-links, the stride of the rows
     uint32_t in_lds;
-    uint64_t *g_row;        // [n * mw] candidate rows
+    uint64_t *g_row;        // [mw * n] candidate rows, word by word
     const uint64_t *g_need; // [W] the columns as a chunk bitmap
     const uint32_t *g_pre;  // [W] columns before each word
     const uint32_t *g_rank; // [M] chunk rank of each column
@@ -168,8 +168,8 @@ __device__ __forceinline__ Pick first_live(const Tables &tb, bool want, uint32_t
             const uint64_t lv = tb.live()[w];
             // (rows in device memory are updated by atomics, which the L1
             // cache does not see: they are read past it)
-            if (ALL || (tb.in_lds & IN_ROW)) x = tb.row()[lane * tb.rs + w];
-            else x = __hip_atomic_load(&tb.g_row[(uint64_t)lane * tb.rs + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (ALL || (tb.in_lds & IN_ROW)) x = tb.row()[w * tb.n + lane];
+            else x = __hip_atomic_load(&tb.g_row[w * tb.n + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             p.x = x & lv;
             words++;
             if (p.x) {
@@ -210,7 +210,7 @@ __device__ __forceinline__ void drop_last(const Tables &tb, const Pick &p)
 // All windows of device d.  PPL: polled entries per lane.  L3: two summary
 // levels (more than 4,096 columns).  ALL: every table is in LDS.
 template <uint32_t PPL, bool L3, bool ALL>
-__device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, const Tables &tb, uint32_t d, uint32_t M)
+__device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, const Tables &tb, uint32_t d, uint32_t M, uint32_t np)
 {
     Control *ctl = ly.ctl;
     const uint32_t lane = threadIdx.x & 63u;
@@ -226,13 +226,13 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
     // the entries this lane polls (a lane past the last one polls that again):
     // their place; whether they feed an in-link (and where its row and summary
     // lie) or only tell how far a reader of d is (`dep`)
-    const uint32_t p0 = ly.poll_off[d], np = ly.poll_off[d + 1] - p0;
+    const uint32_t *poll = sz.nbr_prune ? ly.poll_use + ly.poll_off[d] + ly.out_off[d] : ly.poll + ly.poll_off[d];
     const uint32_t W = (uint32_t)sz.W, L = sz.pub_n, tmin = sz.tmin, own = ly.pub_off[d] + lane;
     uint32_t at[PPL], link[PPL];
     bool dep[PPL], data[PPL];
 #pragma unroll
     for (uint32_t u = 0; u < PPL; u++) {
-        const uint32_t q = np ? ly.poll[p0 + min(64u * u + lane, np - 1u)] : 0u;
+        const uint32_t q = np ? poll[min(64u * u + lane, np - 1u)] : 0u;
         at[u] = q >> 8;
         link[u] = q & 0xFFu;
         dep[u] = link[u] == 0xFFu;
@@ -343,8 +343,8 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
                 if (ra[u] == t) {
                     const uint32_t j = link[u], w = ca[u] >> 6;
                     const unsigned long long bit = 1ull << (ca[u] & 63u);
-                    if (ALL || (tb.in_lds & IN_ROW)) atomicOr((unsigned long long *)&tb.row()[j * tb.rs + w], bit);
-                    else __hip_atomic_fetch_or(&tb.g_row[(uint64_t)j * tb.rs + w], (uint64_t)bit, __ATOMIC_RELAXED,
+                    if (ALL || (tb.in_lds & IN_ROW)) atomicOr((unsigned long long *)&tb.row()[w * tb.n + j], bit);
+                    else __hip_atomic_fetch_or(&tb.g_row[w * tb.n + j], (uint64_t)bit, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
                     if (L3) {
                         atomicOr((unsigned long long *)&tb.mid()[j * tb.ms + (w >> 6)], 1ull << (w & 63u));
@@ -411,7 +411,7 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
                     for (uint32_t i = 0; i < 3; i++) busy_rank += newcol >= tb.step[i] ? 0x10000u : 0u;
                 }
             } else {
-                busy_rank = tb.g_rank[newcol];
+                busy_rank = tb.g_rank[newcol] & NBR_RANK_MASK;
             }
         }
         const uint64_t cm = ballot(newcol != NONE32);
@@ -450,6 +450,22 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
     }
 }
 
+// Calls f(i, load(i)) for the i < n that are this lane's, eight loads in
+// flight together (one memory round trip per 512 elements, not per 64).
+template <class Load, class F>
+__device__ __forceinline__ void copy_batched(uint32_t n, Load load, F f)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t i0 = lane; i0 < n; i0 += 512) {
+        decltype(load(0u)) v[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8; k++) v[k] = load(min(i0 + 64u * k, n - 1u));
+#pragma unroll
+        for (uint32_t k = 0; k < 8; k++)
+            if (i0 + 64u * k < n) f(i0 + 64u * k, v[k]);
+    }
+}
+
 // Places device d's tables in the LDS bytes [at, at + room) and fills them.
 __device__ __forceinline__ void fill_tables(const Layout &ly, const Sizes &sz, uint32_t d, uint32_t M, uint32_t at, uint32_t room,
                                             Tables &tb)
@@ -466,26 +482,44 @@ __device__ __forceinline__ void fill_tables(const Layout &ly, const Sizes &sz, u
     tb.live_at = take(mw * 8u);
     tb.top_at = take(n * 8u);
     tb.ms = mm | 1u;
+    tb.n = n;
     if (l3) tb.mid_at = take(n * tb.ms * 8u);
     tb.g_row = ly.cand + ly.cand_off[d];
     tb.g_need = ly.needs + (uint64_t)d * sz.Wp;
     tb.g_pre = ly.need_pre + (uint64_t)d * sz.Wp;
     tb.g_rank = ly.col_rank + ly.dest_log[d];
-    tb.rs = mw | 1u;
-    if (at + n * tb.rs * 8u <= end) {
+    // the summaries follow the rows: lane j's words of every group
+    uint64_t top = 0;
+    if (lane < n && mm) {
+        const uint64_t *g_mid = tb.g_row + (uint64_t)mw * n + lane;
+        for (uint32_t g0 = 0; g0 < mm; g0 += 8) {
+            uint64_t v[8];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++) v[k] = g_mid[min(g0 + k, mm - 1u) * n];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++) {
+                if (g0 + k >= mm) continue;
+                if (l3) {
+                    tb.mid()[lane * tb.ms + g0 + k] = v[k];
+                    if (v[k]) top |= 1ull << (g0 + k);
+                } else {
+                    top = v[k];
+                }
+            }
+        }
+    }
+    if (lane < n) tb.top()[lane] = top;
+    if (at + n * mw * 8u <= end) {
         tb.in_lds |= IN_ROW;
-        tb.row_at = take(n * tb.rs * 8u);
-    } else {
-        tb.rs = mw;
+        tb.row_at = take(n * mw * 8u);
+        copy_batched(n * mw, [&](uint32_t i) { return tb.g_row[i]; }, [&](uint32_t i, uint64_t v) { tb.row()[i] = v; });
     }
     if (M <= 0xFFFFu && at + W * 10u + 8u <= end) {
         tb.in_lds |= IN_NEED;
         tb.need_at = take(W * 8u);
         tb.pre_at = take(W * 2u);
-        for (uint32_t i = lane; i < W; i += 64) {
-            tb.need()[i] = tb.g_need[i];
-            tb.pre()[i] = (uint16_t)tb.g_pre[i];
-        }
+        copy_batched(W, [&](uint32_t i) { return tb.g_need[i]; }, [&](uint32_t i, uint64_t v) { tb.need()[i] = v; });
+        copy_batched(W, [&](uint32_t i) { return tb.g_pre[i]; }, [&](uint32_t i, uint32_t v) { tb.pre()[i] = (uint16_t)v; });
     }
     static_assert(NBR_MAX_CHUNKS <= 4u << 16, "ranks have at most two bits above 16");
 #pragma unroll
@@ -493,45 +527,26 @@ __device__ __forceinline__ void fill_tables(const Layout &ly, const Sizes &sz, u
     if (at + M * 2u <= end) {
         tb.in_lds |= IN_RANK;
         tb.rank_at = take(M * 2u);
-        for (uint32_t i = lane; i < M; i += 64) tb.rank()[i] = (uint16_t)tb.g_rank[i];
+        // (a count may lie above the rank)
+        copy_batched(M, [&](uint32_t i) { return tb.g_rank[i]; }, [&](uint32_t i, uint32_t v) { tb.rank()[i] = (uint16_t)v; });
     }
     for (uint32_t i = lane; i < mw; i += 64)
         tb.live()[i] = i + 1 < mw || (M & 63u) == 0 ? NONE64 : (1ull << (M & 63u)) - 1ull;
-    // rows and summaries, link by link (64 row words give one summary word)
-    for (uint32_t j = 0; j < n; j++) {
-        uint64_t tsum = 0;
-        for (uint32_t g = 0; g < mm; g++) {
-            const uint32_t w = g * 64u + lane;
-            uint64_t x = 0;
-            if (w < mw) {
-                x = tb.g_row[(uint64_t)j * mw + w];
-                if (tb.in_lds & IN_ROW) tb.row()[j * tb.rs + w] = x;
-            }
-            const uint64_t s = ballot(x != 0);
-            if (l3) {
-                if (lane == 0) tb.mid()[j * tb.ms + g] = s;
-                if (s) tsum |= 1ull << g;
-            } else {
-                tsum = s;
-            }
-        }
-        if (lane == 0) tb.top()[j] = tsum;
-    }
     wave_sync();
 }
 
 // Each wave takes the build of run_dest for its device: polled entries per
 // lane, summary levels, and whether every table found room in LDS.
 template <uint32_t PPL>
-__device__ __forceinline__ void run_built(const Layout &ly, const Sizes &sz, const Tables &tb, uint32_t d, uint32_t M)
+__device__ __forceinline__ void run_built(const Layout &ly, const Sizes &sz, const Tables &tb, uint32_t d, uint32_t M, uint32_t np)
 {
     if (tb.in_lds != (IN_ROW | IN_NEED | IN_RANK)) {
-        if (M > 4096u) run_dest<PPL, true, false>(ly, sz, tb, d, M);
-        else run_dest<PPL, false, false>(ly, sz, tb, d, M);
+        if (M > 4096u) run_dest<PPL, true, false>(ly, sz, tb, d, M, np);
+        else run_dest<PPL, false, false>(ly, sz, tb, d, M, np);
     } else if (M > 4096u) {
-        run_dest<PPL, true, true>(ly, sz, tb, d, M);
+        run_dest<PPL, true, true>(ly, sz, tb, d, M, np);
     } else {
-        run_dest<PPL, false, true>(ly, sz, tb, d, M);
+        run_dest<PPL, false, true>(ly, sz, tb, d, M, np);
     }
 }
 
@@ -549,12 +564,12 @@ __global__ void __launch_bounds__(NBR_THREADS) k_match_nbr(Layout ly, Sizes sz, 
     uint32_t act = 0;
     for (uint32_t w = 0; w < wpb; w++) act += wd[w] != NONE32 ? 1u : 0u;
     const uint32_t share = act > 1u ? (lds_bytes / wpb) & ~15u : lds_bytes;
-    const uint32_t M = ly.dest_cols[d], np = ly.poll_off[d + 1] - ly.poll_off[d];
+    const uint32_t M = ly.dest_cols[d], np = sz.nbr_prune ? ly.poll_cnt[d] : ly.poll_off[d + 1] - ly.poll_off[d];
     Tables tb{};
     fill_tables(ly, sz, d, M, act > 1u ? wave * share : 0u, share, tb);
-    if (np <= 64u) run_built<1>(ly, sz, tb, d, M);
-    else if (np <= 128u) run_built<2>(ly, sz, tb, d, M);
-    else run_built<NBR_MAX_POLL / 64u>(ly, sz, tb, d, M);
+    if (np <= 64u) run_built<1>(ly, sz, tb, d, M, np);
+    else if (np <= 128u) run_built<2>(ly, sz, tb, d, M, np);
+    else run_built<NBR_MAX_POLL / 64u>(ly, sz, tb, d, M, np);
 }
 
 }  // namespace

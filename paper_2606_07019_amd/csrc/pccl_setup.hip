@@ -37,6 +37,13 @@ __global__ void __launch_bounds__(256) k_reset(Layout ly, Sizes sz)
     }
 }
 
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Calls f(lane, bit) for every set bit of the 64 words that the lanes of a
 // wave hold (word `lane` is lane's x), bits shared out evenly over the lanes:
 // a dense word's work is a wave's and not one lane's (8x8 torus, 64 chunks:
@@ -54,9 +61,7 @@ __device__ __forceinline__ void for_bits(uint64_t x, uint16_t *list, F f)
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     uint32_t at = inc - (uint32_t)__popcll(x);
     for (; x; x &= x - 1) list[at++] = (uint16_t)(lane * 64u + (uint32_t)__builtin_ctzll(x));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_fence();
     for (uint32_t i = lane; i < total; i += 64) {
         const uint32_t e = list[i];
         f(e >> 6, e & 63u);
@@ -491,17 +496,25 @@ __global__ void __launch_bounds__(1024) k_need_prefix(Layout ly, Sizes sz)
 // Offsets, column lists and initial candidate rows (one workgroup per
 // device).  Every workgroup sums the columns of the devices before its own
 // (its send-log segment: a device's transfers are its columns) and their
-// candidate rows (in-links * ceil(cols / 64) words).  Then a thread per needs
-// word writes the ranks of its columns, and a thread per column looks up the
-// chunk's holder and, when that is the source of an in-link, sets the
-// column's bit in the link's row.
-constexpr uint32_t COL_BATCH = 4;  // columns whose lookups one thread has in flight
+// candidate words.  Then a thread per needs word writes the ranks of its
+// columns, and a wave per 64 columns looks up the chunks' holders and, where
+// a holder is the source of an in-link, sets the column's bit in the link's
+// row: the 64 columns' words of all rows are put together in LDS and written
+// as one piece (rows are stored word by word, in-links adjacent).  A scattered
+// atomic per column kept the one workgroup of a rail switch busy for 100 us.
+// Behind the rows lie, group by group of 64 row words, the rows' summary
+// words (which words hold a bit).
+constexpr uint32_t COL_BATCH = 4;   // 64-column groups one wave has in flight
 __global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
 {
     __shared__ uint8_t link_of[MAX_DEVICES_SP];  // in-link of d whose source is the device, 0xFF none
-    __shared__ unsigned long long sums[4];       // columns and row words: before d, of all
-    const uint32_t d = blockIdx.x, tid = threadIdx.x;
+    __shared__ unsigned long long sums[4];       // columns and candidate words: before d, of all
+    __shared__ unsigned long long word[16][MAX_IN_LINKS];  // per wave: one row word of every in-link
+    __shared__ unsigned long long mid[MAX_IN_LINKS * 64];  // summary words
+    const uint32_t d = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     // the published entries start as those of windows -4 to -1
+    if (sz.nbr_prune)
+        for (uint32_t i = d * 1024u + tid; i < sz.L; i += gridDim.x * 1024u) ly.rel[i] = 0;
     for (uint32_t i = d * 1024u + tid; i < 4u * sz.pub_n; i += gridDim.x * 1024u)
         ly.pub[i] = (uint64_t)((0xFFCu + i / sz.pub_n) << NBR_TAG_SHIFT) << 32;
     if (tid < 4) sums[tid] = 0;
@@ -511,7 +524,7 @@ __global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
         unsigned long long s[4] = {0, 0, 0, 0};
         for (uint32_t v = tid; v < sz.D; v += 1024) {
             const uint32_t m = ly.dest_cols[v];
-            const unsigned long long r = (unsigned long long)(ly.in_off[v + 1] - ly.in_off[v]) * ((m + 63u) >> 6);
+            const unsigned long long r = cand_size(ly.in_off[v + 1] - ly.in_off[v], m);
             s[0] += v < d ? m : 0u;
             s[1] += v < d ? r : 0ull;
             s[2] += m;
@@ -520,7 +533,7 @@ __global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
 #pragma unroll
         for (uint32_t i = 0; i < 4; i++) {
             for (int o = 32; o; o >>= 1) s[i] += __shfl_xor(s[i], o);
-            if ((tid & 63u) == 0) atomicAdd(&sums[i], s[i]);
+            if (lane == 0) atomicAdd(&sums[i], s[i]);
         }
     }
     __syncthreads();
@@ -539,32 +552,225 @@ __global__ void __launch_bounds__(1024) k_columns(Layout ly, Sizes sz)
     }
     const uint32_t M = ly.dest_cols[d];
     if (M == 0 || total > sz.max_sends || sums[3] > sz.cand_words) return;
-    const uint32_t base = ly.in_off[d], n = ly.in_off[d + 1] - base, mw = (M + 63u) >> 6;
-    unsigned long long *rows = (unsigned long long *)(ly.cand + off);
+    const uint32_t base = ly.in_off[d], n = ly.in_off[d + 1] - base, mw = (M + 63u) >> 6, mm = (mw + 63u) >> 6;
+    uint64_t *rows = ly.cand + off;
     uint32_t *rank = ly.col_rank + log0;
     const uint64_t *need = ly.needs + (uint64_t)d * sz.Wp;
     const uint32_t *pre = ly.need_pre + (uint64_t)d * sz.Wp;
-    for (uint32_t i = tid; i < n * mw; i += 1024) rows[i] = 0ull;
+    for (uint32_t i = tid; i < n * mm; i += 1024) mid[i] = 0ull;
     for (uint32_t j = tid; j < n; j += 1024) link_of[ly.slot_src[base + j]] = (uint8_t)j;
     for (uint32_t w = tid; w < (uint32_t)sz.W; w += 1024) {
         uint32_t c = pre[w];
         for (uint64_t x = need[w]; x; x &= x - 1) rank[c++] = w * 64u + (uint32_t)__builtin_ctzll(x);
     }
     __syncthreads();
-    for (uint32_t c0 = tid; c0 < M; c0 += 1024 * COL_BATCH) {
+    unsigned long long *mine = word[wave];
+    for (uint32_t w0 = wave; w0 < mw; w0 += 16 * COL_BATCH) {
         uint32_t r[COL_BATCH], s[COL_BATCH];
 #pragma unroll
-        for (uint32_t u = 0; u < COL_BATCH; u++) r[u] = rank[min(c0 + 1024u * u, M - 1u)];
+        for (uint32_t k = 0; k < COL_BATCH; k++) r[k] = rank[min((w0 + 16u * k) * 64u + lane, M - 1u)];
 #pragma unroll
-        for (uint32_t u = 0; u < COL_BATCH; u++) s[u] = ly.rank_src[r[u]];
+        for (uint32_t k = 0; k < COL_BATCH; k++) s[k] = ly.rank_src[r[k]];
 #pragma unroll
-        for (uint32_t u = 0; u < COL_BATCH; u++) {
-            const uint32_t c = c0 + 1024u * u;
-            if (c >= M) continue;
-            const uint32_t j = s[u] != NONE32 ? link_of[s[u]] : 0xFFu;
-            if (j != 0xFFu) atomicOr(&rows[(uint64_t)j * mw + (c >> 6)], 1ull << (c & 63u));
+        for (uint32_t k = 0; k < COL_BATCH; k++) {
+            const uint32_t w = w0 + 16u * k;
+            if (w >= mw) break;
+            const uint32_t j = w * 64u + lane < M && s[k] != NONE32 ? link_of[s[k]] : 0xFFu;
+            if (lane < n) mine[lane] = 0ull;
+            wave_fence();
+            if (j != 0xFFu) atomicOr(&mine[j], 1ull << lane);
+            wave_fence();
+            if (lane < n) {
+                const unsigned long long x = mine[lane];
+                rows[(uint64_t)w * n + lane] = x;
+                if (x) atomicOr(&mid[(w >> 6) * n + lane], 1ull << (w & 63u));
+            }
+            wave_fence();
         }
     }
+    __syncthreads();
+    for (uint32_t i = tid; i < n * mm; i += 1024) rows[(uint64_t)mw * n + i] = mid[i];
+}
+
+// Which polled entries matter (run where some device polls many).  A transfer
+// of chunk c over link q->u concerns u's out-neighbour d only if d needs c and
+// q can offer c to u before d has it: q holds c from the start, or q needs c
+// and some in-neighbour of q other than u and d ever holds c (holds it from
+// the start or needs it; a device receives a chunk once, so what q had from u
+// or d comes too late).  A relay switch polls none of its NPUs' in-links this
+// way: what they receive came through it.
+//
+// First, per column of q: how many in-neighbours of q ever hold the chunk,
+// kept above the rank in the column list.
+constexpr uint32_t REL_COLS = 256;   // columns a workgroup takes at a time
+constexpr uint32_t REL_BATCH = 8;    // in-links whose lookups are in flight together
+__global__ void __launch_bounds__(REL_COLS) k_col_counts(Layout ly, Sizes sz)
+{
+    __shared__ uint32_t src[MAX_IN_LINKS];
+    const uint32_t q = blockIdx.x, tid = threadIdx.x, M = ly.dest_cols[q];
+    if (blockIdx.y * REL_COLS >= M || ly.ctl->error) return;
+    const uint32_t base = ly.in_off[q], n = ly.in_off[q + 1] - base;
+    if (tid < n) src[tid] = ly.slot_src[base + tid];
+    __syncthreads();
+    if (blockIdx.y == 0) {
+        // per in-link x->q (a wave each): whether x is fed by q, and by which
+        // of q's out-neighbours
+        const uint32_t lane = tid & 63u, o0 = ly.out_off[q], m = ly.out_off[q + 1] - o0;
+        const uint32_t dst = lane < m ? ly.out_dst[o0 + lane] : NONE32;
+        for (uint32_t j = tid >> 6; j < n; j += REL_COLS / 64) {
+            const uint32_t b = ly.in_off[src[j]], e = ly.in_off[src[j] + 1];
+            const uint32_t s = b + lane < e ? ly.slot_src[b + lane] : NONE32;  // (at most 64 in-links)
+            bool f = false;
+            for (uint32_t p = 0; p < e - b; p++) f = f || (uint32_t)__builtin_amdgcn_readlane((int)s, (int)p) == dst;
+            const uint64_t fm = __builtin_amdgcn_ballot_w64(f && lane < m), bk = __builtin_amdgcn_ballot_w64(s == q);
+            if (lane == 0) {
+                ly.feeds[base + j] = fm;
+                ly.back[base + j] = bk ? 1u : 0u;
+            }
+        }
+    }
+    uint32_t *cols = ly.col_rank + ly.dest_log[q];
+    for (uint32_t c = blockIdx.y * REL_COLS + tid; c < M; c += gridDim.y * REL_COLS) {
+        const uint32_t r = cols[c], h = ly.rank_src[r], w = r >> 6;
+        uint32_t cnt = 0;
+        for (uint32_t j0 = 0; j0 < n; j0 += REL_BATCH) {
+            uint64_t x[REL_BATCH];
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++) x[k] = ly.needs[(uint64_t)src[min(j0 + k, n - 1u)] * sz.Wp + w];
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++)
+                if (j0 + k < n) cnt += (((x[k] >> (r & 63u)) & 1ull) || src[j0 + k] == h) ? 1u : 0u;
+        }
+        cols[c] = r | (cnt << NBR_COUNT_SHIFT);
+    }
+}
+
+// Then, for every in-link q->u and out-link u->d of a device u, whether some
+// column of u can come in over the one and concern the other's destination:
+// bit rows over 256 columns at a time (offers of the in-links, without and
+// with d among the excluded holders; needs of the out-neighbours), and an AND
+// per pair of links.
+__global__ void __launch_bounds__(REL_COLS) k_relevant(Layout ly, Sizes sz)
+{
+    constexpr uint32_t NW = REL_COLS / 64;
+    __shared__ uint64_t offer[2][MAX_IN_LINKS][NW], wants[MAX_IN_LINKS][NW];
+    __shared__ uint64_t feeds[MAX_IN_LINKS];  // per in-link q->u: out-neighbours d with a link d->q
+    __shared__ uint32_t src[MAX_IN_LINKS], dst[MAX_IN_LINKS], back[MAX_IN_LINKS], log[MAX_IN_LINKS];
+    const uint32_t u = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u, M = ly.dest_cols[u];
+    if (blockIdx.y * REL_COLS >= M || ly.ctl->error) return;
+    const uint32_t base = ly.in_off[u], n = ly.in_off[u + 1] - base;
+    const uint32_t o0 = ly.out_off[u], m = ly.out_off[u + 1] - o0;
+    if (m == 0) return;
+    if (tid < n) {
+        src[tid] = ly.slot_src[base + tid];
+        log[tid] = (uint32_t)ly.dest_log[src[tid]];
+        feeds[tid] = ly.feeds[base + tid];
+        back[tid] = ly.back[base + tid];
+    }
+    if (tid < m) dst[tid] = ly.out_dst[o0 + tid];
+    __syncthreads();
+    const uint32_t *cols = ly.col_rank + ly.dest_log[u];
+    for (uint32_t c0 = blockIdx.y * REL_COLS; c0 < M; c0 += gridDim.y * REL_COLS) {
+        const uint32_t c = c0 + tid, r = cols[min(c, M - 1u)] & NBR_RANK_MASK, h = ly.rank_src[r], w = r >> 6, b = r & 63u;
+        const bool in = c < M;
+        for (uint32_t j0 = 0; j0 < n; j0 += REL_BATCH) {
+            uint64_t x[REL_BATCH];
+            uint32_t pre[REL_BATCH], col[REL_BATCH];
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++) {
+                const uint64_t at = (uint64_t)src[min(j0 + k, n - 1u)] * sz.Wp + w;
+                x[k] = ly.needs[at];
+                pre[k] = ly.need_pre[at];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++) {
+                // (for a chunk q does not need the list's first entry, ignored)
+                const bool nb = (x[k] >> b) & 1ull;
+                col[k] = ly.col_rank[nb ? log[min(j0 + k, n - 1u)] + pre[k] + (uint32_t)__popcll(x[k] & ((1ull << b) - 1ull)) : 0u];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++) {
+                const uint32_t j = j0 + k;
+                if (j >= n) break;
+                const bool nb = (x[k] >> b) & 1ull, init = src[j] == h;
+                const uint32_t cnt = nb ? col[k] >> NBR_COUNT_SHIFT : 0u;
+                const uint64_t a0 = __builtin_amdgcn_ballot_w64(in && (init || cnt > back[j]));
+                const uint64_t a1 = __builtin_amdgcn_ballot_w64(in && (init || cnt > back[j] + 1u));
+                if (lane == 0) {
+                    offer[0][j][wave] = a0;
+                    offer[1][j][wave] = a1;
+                }
+            }
+        }
+        for (uint32_t k0 = 0; k0 < m; k0 += REL_BATCH) {
+            uint64_t x[REL_BATCH];
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++) x[k] = ly.needs[(uint64_t)dst[min(k0 + k, m - 1u)] * sz.Wp + w];
+#pragma unroll
+            for (uint32_t k = 0; k < REL_BATCH; k++) {
+                if (k0 + k >= m) break;
+                const uint64_t v = __builtin_amdgcn_ballot_w64(in && ((x[k] >> b) & 1ull));
+                if (lane == 0) wants[k0 + k][wave] = v;
+            }
+        }
+        __syncthreads();
+        for (uint32_t j = wave; j < n; j += NW) {
+            bool any = false;
+            if (lane < m && src[j] != dst[lane]) {  // (not what d itself sends)
+                const uint64_t *a = offer[(feeds[j] >> lane) & 1ull][j];
+#pragma unroll
+                for (uint32_t i = 0; i < NW; i++) any = any || (a[i] & wants[lane][i]) != 0;
+            }
+            const uint64_t am = __builtin_amdgcn_ballot_w64(any);
+            if (am && lane == 0) atomicOr((unsigned long long *)&ly.rel[base + j], (unsigned long long)am);
+        }
+        __syncthreads();
+    }
+}
+
+// Each device's list of polled entries: the relevant ones, and one in-link of
+// every out-neighbour that reads its entries without being polled itself (a
+// wave per device).
+__global__ void __launch_bounds__(64) k_poll_lists(Layout ly, Sizes sz)
+{
+    if (ly.ctl->error) return;
+    const uint32_t d = blockIdx.x, lane = threadIdx.x;
+    const uint32_t p0 = ly.poll_off[d], np = ly.poll_off[d + 1] - p0, o0 = ly.out_off[d], m = ly.out_off[d + 1] - o0;
+    const uint32_t base = ly.in_off[d], n = ly.in_off[d + 1] - base;
+    uint32_t *out = ly.poll_use + p0 + o0;
+    __shared__ uint32_t polled[MAX_IN_LINKS];  // in-link j's source has a polled entry
+    if (lane < n) polled[lane] = 0;
+    __syncthreads();
+    uint32_t cnt = 0;
+    for (uint32_t i0 = 0; i0 < np; i0 += 64) {
+        const uint32_t i = i0 + lane, e = ly.poll[p0 + min(i, np - 1u)], j = e & 0xFFu;
+        bool keep = false;
+        if (i < np && j != 0xFFu) {
+            const uint32_t sl = base + j, s = ly.slot_src[sl];
+            keep = (ly.rel[ly.in_off[s] + ((e >> 8) - ly.pub_off[s])] >> ly.slot_out[sl]) & 1ull;
+            if (keep) polled[j] = 1u;
+        }
+        const uint64_t km = __builtin_amdgcn_ballot_w64(keep);
+        if (keep) out[cnt + (uint32_t)__popcll(km & ((1ull << lane) - 1ull))] = e;
+        cnt += (uint32_t)__popcll(km);
+    }
+    __syncthreads();
+    // which out-links' destinations read d's entries
+    uint64_t readers = 0;
+    for (uint32_t j = 0; j < n; j++) readers |= ly.rel[base + j];
+    bool dep = lane < m && ((readers >> lane) & 1ull);
+    uint32_t entry = 0;
+    if (dep) {
+        const uint32_t x = ly.out_dst[o0 + lane], xb = ly.in_off[x], xn = ly.in_off[x + 1] - xb;
+        for (uint32_t j = 0; j < n; j++)
+            if (polled[j] && ly.slot_src[base + j] == x) dep = false;
+        for (uint32_t p = 0; p < xn; p++)
+            if (ly.slot_src[xb + p] == d) entry = ((ly.pub_off[x] + p) << 8) | 0xFFu;
+    }
+    const uint64_t dm = __builtin_amdgcn_ballot_w64(dep);
+    if (dep) out[cnt + (uint32_t)__popcll(dm & ((1ull << lane) - 1ull))] = entry;
+    cnt += (uint32_t)__popcll(dm);
+    if (lane == 0) ly.poll_cnt[d] = cnt;
 }
 
 inline uint32_t blocks_for(uint64_t n, uint32_t t) { return (uint32_t)((n + t - 1) / t); }
@@ -594,6 +800,12 @@ hipError_t launch_setup(const Layout &ly, const Sizes &sz, const uint64_t *pre, 
     if (sz.nbr) {
         k_need_prefix<<<sz.D, (uint32_t)std::min<uint64_t>(1024, ((sz.W + 3) / 4 + 63) / 64 * 64 + (sz.W ? 0 : 64)), 0, st>>>(ly, sz);
         k_columns<<<sz.D, 1024, 0, st>>>(ly, sz);
+        if (sz.nbr_prune && C) {
+            const dim3 g(sz.D, std::min(blocks_for(C, REL_COLS), 64u));
+            k_col_counts<<<g, REL_COLS, 0, st>>>(ly, sz);
+            k_relevant<<<g, REL_COLS, 0, st>>>(ly, sz);
+            k_poll_lists<<<sz.D, 64, 0, st>>>(ly, sz);
+        }
         return hipGetLastError();
     }
     if (sz.sw_nbt && C) k_adm_counts<<<dim3(blocks_for(C, T), sz.sw_nbt), T, 0, st>>>(ly, sz);

@@ -53,6 +53,13 @@ CASES = {
     # 56 and 72 polled entries per device: one and several per lane
     "complete 9": lambda: _generic("complete9", _complete(9), 200, 10000, 8, 5),
     "complete 10": lambda: _generic("complete10", _complete(10), 200, 10000, 9, 6),
+    # more than 64 polled entries, pruned to those a needed chunk can come through: one-way and switched networks,
+    # chunks with one and with many destinations, a chunk that several neighbours can offer
+    "digraph 40 degree 9": lambda: _generic("digraph40", _digraph(40, 9, 18), 1200, 20000, 30, 18),
+    "digraph 90 degree 9": lambda: _generic("digraph90", _digraph(90, 9, 19), 2500, 20000, 2, 19),
+    "rail 12x6 all-gather": lambda: W.Workload("rail12ag", W.switch2level(12, 6), W.all_gather(72, range(72), 5, 9000), 20),
+    "rail 12x8 generic": lambda: _generic("rail12g", W.switch2level(12, 8), 3000, 7000, 9, 21),
+    "rail 13x8": lambda: W.Workload("rail13x8", W.switch2level(13, 8), W.a2a_bitmaps(104, 8192), 22),
     # 64 and 65 chunks (one and two row words), 4,096 and 4,160 (one and two summary levels), all needed everywhere
     "ring 4 x 16": lambda: W.Workload("r4", W.ring(4), W.all_gather(4, range(4), 16, 1 << 14), 7),
     "ring 5 x 13": lambda: W.Workload("r5", W.ring(5), W.all_gather(5, range(5), 13, 1 << 14), 8),
