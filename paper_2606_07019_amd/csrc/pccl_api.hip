@@ -71,6 +71,8 @@ struct pccl_ctx {
     bool ran_sw = false;           // the last synthesis ran the switch-group kernel
     uint32_t sw_groups = 0, sw_pool = 0, sw_nbt = 0;
     int sw_grid = 0;
+    bool sw_cols = false;          // the switch groups are matched over columns
+    std::vector<uint32_t> sw_mem, sw_mem_off;  // the groups' devices
     // plan (made once per collective and switch model, before any workspace)
     bool planned = false;
     uint64_t plan_gen = 0;         // changes with every plan (static scratch ownership)
@@ -180,7 +182,9 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     sz.resident = c->resident ? 1u : 0u;
     sz.sw_gate = c->sw_active && c->sw_gate ? 1u : 0u;
     sz.sw_nbt = c->sw_active ? c->sw_nbt : 0u;
-    sz.nbr = c->nbr ? 1u : 0u;
+    const bool cols = c->nbr || c->sw_cols;
+    sz.cols = cols ? 1u : 0u;
+    sz.sw_cols = c->sw_cols ? 1u : 0u;
     const uint64_t hb = (uint64_t)sz.D * sz.Wp * sizeof(uint64_t);
     sz.hbytes = hb < (1ull << 31) ? (uint32_t)hb : 0u;
     const uint64_t nsort = std::max<uint64_t>(c->C, max_sends);
@@ -213,14 +217,15 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     ly.sp_dist = cv.take<uint64_t>(N * D);
     ly.sp_parent = cv.take<uint32_t>(N * D);
     ly.skey[0] = cv.take<uint64_t>(nsort);
-    // the neighbour-stepped matcher keeps its candidate rows and column list
+    // the matchers over columns keep their candidate rows and column list
     // in the second sort buffers, which no sort uses between the priority
-    // order and the output: per device in-links * (w + ceil(w / 64)) words,
-    // w = ceil(cols / 64)
+    // order and the output: per device in-links * (w + ceil(w / 64)) + w
+    // words, w = ceil(cols / 64)
     uint64_t cand = 0;
-    if (c->nbr) {
+    if (cols) {
         cand = std::min<uint64_t>(L * sz.W, (uint64_t)c->max_in * ((max_sends + 63) / 64) + L);
         cand += cand / 64 + L;
+        cand += std::min<uint64_t>(D * sz.W, (max_sends + 63) / 64 + D);
     }
     sz.cand_words = cand;
     ly.skey[1] = cv.take<uint64_t>(std::max(nsort, cand));
@@ -231,7 +236,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     ly.dest_log = cv.take<unsigned long long>(D);
     ly.wave_dest = cv.take<uint32_t>(D + (uint64_t)MATCH_WAVES * MAX_MATCH_GRID);
     ly.wave_part = cv.take<uint32_t>(D + (uint64_t)MATCH_WAVES * MAX_MATCH_GRID);
-    if (c->nbr) {
+    if (cols) {
         ly.cand = ly.skey[1];
         ly.col_rank = ly.sval[1];
         ly.rank_src = ly.holder_cnt;  // the counts are read before the ranks are known
@@ -254,6 +259,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
             ly.poll_cnt = cv.take<uint32_t>(D);
             ly.poll_use = cv.take<uint32_t>(c->poll.size() + L);
         }
+        if (c->sw_cols) ly.xslot = cv.take<uint64_t>(2ull * MAX_MATCH_GRID * XSLOT_WORDS);
     } else {
         ly.holds = cv.take<uint64_t>(D * sz.Wp);
         ly.busy = cv.take<uint32_t>(L);
@@ -277,7 +283,8 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
         ly.sw.pool_c = cv.take<uint32_t>(c->sw_pool);
         ly.sw.pool_n = cv.take<uint32_t>(c->sw_pool);
         ly.sw.occ = cv.take<uint32_t>(c->sw_nbt);
-        ly.sw.acnt = cv.take<uint32_t>((uint64_t)c->sw_nbt * std::max<uint64_t>(C, 1));
+        if (c->sw_cols) ly.sw.amask = cv.take<uint64_t>((uint64_t)c->sw_nbt * C);
+        else ly.sw.acnt = cv.take<uint32_t>((uint64_t)c->sw_nbt * std::max<uint64_t>(C, 1));
     }
     total = (cv.off + 255) & ~size_t(255);
 }
@@ -299,6 +306,8 @@ pccl_status build_switch_tables(pccl_ctx *c)
     c->sw_nuni = 0;
     c->swt.clear();
     c->sw_links.clear();
+    c->sw_mem.clear();
+    c->sw_mem_off.assign(1, 0u);
     if (!c->sw_model) return PCCL_OK;
     const uint32_t N = c->N, S = c->S, D = c->D, L = c->L;
     std::vector<uint32_t> cap(S);
@@ -457,6 +466,8 @@ pccl_status build_switch_tables(pccl_ctx *c)
         std::copy(h, h + 16, grp.begin() + 16ull * g);
         pool += pl;
         c->sw_links.push_back(nl);
+        c->sw_mem.insert(c->sw_mem.end(), mem.begin(), mem.end());
+        c->sw_mem_off.push_back((uint32_t)c->sw_mem.size());
     }
     // the matcher indexes its snapshot entries by group link position (each
     // link is an in-link of exactly one group's destination): a pair names
@@ -793,6 +804,44 @@ bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
     return true;
 }
 
+// Whether the switch groups are matched over columns: every group has a
+// workgroup of its own (the group's state stays in LDS), every device at most
+// 64 in-links (a lane each in the column tables), at most 2^18 chunks (two
+// summary levels), a limited switch at most 64 out-links (a mask per chunk), a
+// group at most GRP_MAX_ITEMS polled entries (registers), and a buffer limit
+// binds: where only the no-multicast rule may, the plain kernel over bitmap
+// rows is queued beside the group kernel and both read one layout.  Within
+// these bounds the columns were the faster side wherever both were measured
+// (rail clusters of 128 and 512 NPUs: 18.8 and 11.3 ms, 57.5 and 25.6).
+bool plan_switch_columns(pccl_ctx *c)
+{
+    if (!c->nbr_ok || !c->sw_active || c->sw_gate || c->C == 0 || c->C > NBR_MAX_CHUNKS) return false;
+    if ((int)c->sw_groups > std::min<int>(match_cols_max_grid(c->device), (int)MAX_MATCH_GRID)) return false;
+    for (uint32_t d = 0; d < c->D; d++)
+        if (c->in_off[d + 1] - c->in_off[d] > MAX_IN_LINKS) return false;
+    auto limited = [&](uint32_t v) { return v >= c->N && c->sw_buf[v - c->N] && c->sw_buf[v - c->N] < c->C; };
+    uint64_t pairs = 0;
+    for (uint32_t d = 0; d < c->D; d++) pairs += c->dest_pairs[d];
+    if (pairs > GRP_MAX_PAIRS) return false;
+    // (at most; the setup may find some without use)
+    for (uint32_t g = 0; g < c->sw_groups; g++) {
+        uint64_t n = 0;
+        for (uint32_t k = c->sw_mem_off[g]; k < c->sw_mem_off[g + 1]; k++)
+            for (uint32_t d = c->sw_mem[k], sl = c->in_off[d]; sl < c->in_off[d + 1]; sl++) {
+                const uint32_t v = c->slot_src[sl];
+                if (!limited(v)) n += c->in_off[v + 1] - c->in_off[v];
+            }
+        if (n > GRP_MAX_ITEMS) return false;
+    }
+    if (!c->poll_built) build_poll(c);
+    std::vector<uint32_t> n_out(c->D, 0);
+    for (uint32_t v : c->src) n_out[v]++;
+    for (uint32_t i = 0; i < c->S; i++)
+        if (limited(c->N + i) && n_out[c->N + i] > 64) return false;
+    c->nbr_prune = c->max_poll > 64 && c->max_out <= 64;
+    return c->pub_off[c->D] < (1u << 22);
+}
+
 // The windowed kernel's launch shape: waves per workgroup, needs rows in
 // LDS, grid, split and lone destinations.
 pccl_status plan_windowed(pccl_ctx *c, const std::vector<uint32_t> &must, uint32_t need_w, uint32_t n_heavy, bool desc_ok,
@@ -917,7 +966,7 @@ pccl_status plan(pccl_ctx *c)
     }
     int lds_cu = 0;
     HIP_OR_FAIL(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, c->device));
-    c->nbr_prune = false;
+    c->nbr_prune = c->sw_cols = false;
     c->nbr = must.empty() && plan_nbr(c, (size_t)lds_cu, n_heavy);
     if (!c->nbr) {
         st = plan_windowed(c, must, need_w, n_heavy, desc_ok, (size_t)lds_cu, Wp);
@@ -925,12 +974,15 @@ pccl_status plan(pccl_ctx *c)
     }
     deal_destinations(c);
     if (c->sw_active) {
-        c->sw_grid = std::min<int>(std::min<int>(match_sw_max_grid(c->device), (int)MAX_MATCH_GRID),
-                                   (int)c->sw_groups);
+        c->sw_cols = plan_switch_columns(c);
+        c->sw_grid = c->sw_cols ? (int)c->sw_groups
+                                : std::min<int>(std::min<int>(match_sw_max_grid(c->device), (int)MAX_MATCH_GRID),
+                                                (int)c->sw_groups);
         if (c->sw_grid <= 0) return fail(c, PCCL_EDEVICE, "switch-model matching kernel cannot be resident");
         st = deal_switch_groups(c);
         if (st != PCCL_OK) return st;
     }
+    const bool cols = c->nbr || c->sw_cols;
     // the pinned image, in the order upload() copies it
     const std::pair<const void *, size_t> parts[IMG_PARTS] = {
         {c->src.data(), 4ull * c->L},         {c->dst.data(), 4ull * c->L},
@@ -942,9 +994,9 @@ pccl_status plan(pccl_ctx *c)
         {c->wave_part.data(), 4ull * c->wave_part.size()},
         {c->gmask.data(), 8ull * c->gmask.size()},
         {c->swt.data(), c->sw_active ? 4ull * c->swt.size() : 0ull},
-        {c->poll_off.data(), c->nbr ? 4ull * c->poll_off.size() : 0ull},
-        {c->poll.data(), c->nbr ? 4ull * c->poll.size() : 0ull},
-        {c->pub_off.data(), c->nbr ? 4ull * c->pub_off.size() : 0ull},
+        {c->poll_off.data(), cols ? 4ull * c->poll_off.size() : 0ull},
+        {c->poll.data(), cols ? 4ull * c->poll.size() : 0ull},
+        {c->pub_off.data(), cols ? 4ull * c->pub_off.size() : 0ull},
         {c->out_off.data(), c->nbr_prune ? 4ull * c->out_off.size() : 0ull},
         {c->out_dst.data(), c->nbr_prune ? 4ull * c->out_dst.size() : 0ull},
         {c->slot_out.data(), c->nbr_prune ? 4ull * c->slot_out.size() : 0ull}};
@@ -971,13 +1023,15 @@ pccl_status bind_workspace(pccl_ctx *c, char *ptr, size_t bytes, uint64_t ms, hi
     Sizes sz{};
     size_t need = 0;
     carve(c, nullptr, ms, ly, sz, need);
-    if (bytes < need && c->nbr) {
-        // the windowed kernel's layout may still fit (it lacks the column
-        // and poll tables): plan for that kernel instead
-        c->nbr = false;
+    if (bytes < need && (c->nbr || c->sw_cols)) {
+        // the layout of the kernels over bitmap rows may still fit (it lacks
+        // the column and poll tables): plan for those instead
+        const bool nbr = c->nbr, sw_cols = c->sw_cols;
+        c->nbr = c->sw_cols = false;
         size_t alt = 0;
         carve(c, nullptr, ms, ly, sz, alt);
-        c->nbr = true;
+        c->nbr = nbr;
+        c->sw_cols = sw_cols;
         if (bytes >= alt) {
             c->nbr_ok = false;
             const pccl_status ps = plan(c);
@@ -1363,6 +1417,8 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
         if (c->sw_nuni) HIP_OR_FAIL(c, launch_unicast_check(c->ly, c->sz, st, c->sw_nuni));
         HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, c->sw_grid));
         HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
+    } else if (c->sw_cols) {
+        HIP_OR_FAIL(c, launch_match_cols(c->ly, c->sz, st, c->sw_grid));
     } else if (c->sw_active) {
         HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, c->sw_grid));
     } else if (c->nbr) {

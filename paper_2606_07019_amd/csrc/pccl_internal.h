@@ -49,12 +49,17 @@ constexpr uint32_t NBR_RANK_MASK = (1u << NBR_COUNT_SHIFT) - 1u;
 constexpr uint32_t NBR_MAX_POLL = 512;         // entries one device polls per window
 constexpr uint32_t NBR_MAX_RATIO = 64;         // largest link time over the smallest
 
-// Candidate words of a device with n in-links and m columns: the rows' words
-// and their summary words.
+// Switch groups over columns: entries the devices of one group poll, those
+// that reach a limited switch aside (a few registers per thread each).
+constexpr uint32_t GRP_MAX_ITEMS = 6u * SW_THREADS;
+constexpr uint64_t GRP_MAX_PAIRS = 1u << 22;  // and all entries (16 MiB of poll lists)
+
+// Candidate words of a device with n in-links and m columns: the rows' words,
+// their summary words and (used by the switch-group kernel) its live set.
 inline __host__ __device__ uint64_t cand_size(uint64_t n, uint64_t m)
 {
     const uint64_t mw = (m + 63) >> 6;
-    return n * (mw + ((mw + 63) >> 6));
+    return n * (mw + ((mw + 63) >> 6)) + mw;
 }
 
 // Status codes mirrored from the public header.
@@ -134,6 +139,7 @@ struct SwTab {
     uint32_t *pool_c, *pool_n;  // buffer places: chunk, out-neighbours still needing it (0 = free)
     uint32_t *occ;              // [nB + 1] per group: occupied places
     uint32_t *acnt;             // [nBt C] per limited-switch row and chunk rank: out-links whose destination still needs it
+    uint64_t *amask;         // over columns instead: the out-links (b_out order) that lead to devices that need it
 };
 
 // Pointers into the caller's workspace (all device memory).
@@ -210,7 +216,8 @@ struct Sizes {
     uint64_t cand_words;  // capacity of Layout::cand
     uint32_t nbr_prune; // the polled entries are pruned by the setup
     uint32_t pub_n;    // published entries of one window
-    uint32_t nbr;      // the neighbour-stepped matching kernel runs
+    uint32_t cols;     // the matching kernel works over columns
+    uint32_t sw_cols;  // and it is the switch-group one
     uint32_t sw_nbt;   // limited-switch rows of the switch tables (0: no switch model or no limited switch)
 };
 
@@ -231,6 +238,9 @@ hipError_t launch_match_nbr(const Layout &ly, const Sizes &sz, hipStream_t st, i
                             size_t dyn_lds, uint32_t spread);
 int match_nbr_max_grid(int device, int waves_per_block, size_t dyn_lds);
 hipError_t launch_match_sw(const Layout &ly, const Sizes &sz, hipStream_t st, int grid);
+// the switch-group kernel over columns (one group per workgroup)
+hipError_t launch_match_cols(const Layout &ly, const Sizes &sz, hipStream_t st, int grid);
+int match_cols_max_grid(int device);
 // sets Control::sw_binds when two out-neighbours of one of the n_uni unicast
 // switches need the same chunk
 hipError_t launch_unicast_check(const Layout &ly, const Sizes &sz, hipStream_t st, uint32_t n_uni);

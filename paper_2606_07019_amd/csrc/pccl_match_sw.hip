@@ -35,6 +35,13 @@
 // event is skipped, so the early fold never shows a chunk before its time.
 // The barrier at the window's end publishes the next window's entries and
 // finds the next event time.
+//
+// Two kernels do this.  k_match_cols works over the columns each destination
+// needs; it takes the networks whose switch groups each have a workgroup of
+// their own (the rest of its rule stands at plan_switch_columns).  k_match_sw,
+// described above, scans bitmap rows and takes everything else: several groups
+// per workgroup, devices with more than 64 in-links, and the networks where
+// only the no-multicast rule may act.
 #include "pccl_internal.h"
 
 namespace pccl {
@@ -168,7 +175,8 @@ __device__ inline bool need_bit(const uint64_t *row, uint32_t c)
     return (w >> (c & 63u)) & 1ull;
 }
 
-__device__ inline uint64_t link_key(const SwShared &sh, uint32_t i)
+template <class S>
+__device__ inline uint64_t link_key(const S &sh, uint32_t i)
 {
     return ((uint64_t)sh.ltim[i] << 32) | sh.llink[i];
 }
@@ -177,7 +185,8 @@ __device__ inline uint32_t adm_hash(uint32_t c) { return (c * 2654435761u) >> 18
 
 // one of the pick round's winners delivers chunk c to group destination dl
 // (read after the round's winners are final)
-__device__ inline bool delivered_now(const SwShared &sh, uint32_t dl, uint32_t c)
+template <class S>
+__device__ inline bool delivered_now(const S &sh, uint32_t dl, uint32_t c)
 {
     for (uint32_t j = sh.doff[dl], je = sh.doff[dl + 1]; j < je; j++)
         if (sh.pick[j] == c && ((sh.winf[j] >> 2) & 1u)) return true;
@@ -243,7 +252,8 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v)
 
 static_assert(MAX_MATCH_GRID <= (1u << 13), "the window exchange sums 19-bit counts in 32 bits");
 
-__device__ uint32_t block_min(SwShared &sh, uint32_t v)
+template <class S>
+__device__ uint32_t block_min(S &sh, uint32_t v)
 {
     v = wave_min(v);
     if ((threadIdx.x & 63) == 0) sh.red[here(threadIdx.x) >> 6] = v;
@@ -261,8 +271,12 @@ __device__ uint32_t block_min(SwShared &sh, uint32_t v)
 // tmin, sent and err are each thread's own: every wave reduces its threads'
 // values into an LDS slot before the workgroup barrier, and the thread that
 // publishes combines the waves' slots after it.
+// COHERENT: what other workgroups write is read with coherent loads only, so
+// the caches need no invalidation.
+// `between` runs in every wave after the workgroup's arrival is out.
+template <bool COHERENT, class S, class F>
 __device__ bool sw_sync(Control *ctl, uint64_t *xslot, uint32_t gen, uint32_t tmin, uint32_t sent, uint32_t err,
-                        SwShared &sh)
+                        S &sh, F between)
 {
     const uint32_t nb = gridDim.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t tag = (uint64_t)(gen & 0xFFFu) << 52;
@@ -289,6 +303,7 @@ __device__ bool sw_sync(Control *ctl, uint64_t *xslot, uint32_t gen, uint32_t tm
                            tag | ((uint64_t)(be ? 1u : 0u) << 51) | ((uint64_t)(bs & 0x7FFFFu) << 32) | bt,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    between();
     if (threadIdx.x < 64) {
         uint32_t spins = 0, ok = 1, tn = NONE32, e = 0;
         unsigned long long s = 0;
@@ -323,7 +338,8 @@ __device__ bool sw_sync(Control *ctl, uint64_t *xslot, uint32_t gen, uint32_t tm
             __builtin_amdgcn_s_sleep(1);
         }
         // acquire: drop cached lines that other workgroups wrote
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if constexpr (COHERENT) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         // (a slot's count has 19 bits and there are at most MAX_MATCH_GRID
         // slots: the sum fits in 32 bits)
         tn = wave_min(tn);
@@ -464,7 +480,8 @@ __device__ void load_group_state(const Layout &ly, const Sizes &sz, const SwGrou
 
 // A unicast switch keeps one copy of a chunk in flight: is chunk c in flight
 // on one of switch u's out-links at time t?
-__device__ inline bool sending(const SwShared &sh, uint32_t u, uint32_t c, uint32_t t)
+template <class S>
+__device__ inline bool sending(const S &sh, uint32_t u, uint32_t c, uint32_t t)
 {
     for (uint32_t q = sh.uoff[u]; q < sh.uoff[u + 1]; q++) {
         const uint32_t j = sh.ulist[q];
@@ -496,7 +513,8 @@ __device__ inline uint32_t filter_bit(uint32_t u, uint32_t c, uint32_t fl)
 
 // Is chunk c in flight on an out-link of unicast switch u at time t?  The
 // filter answers "no" for most chunks without walking the links.
-__device__ inline bool sent_by(const SwShared &sh, uint32_t u, uint32_t c, uint32_t t, uint32_t fl)
+template <class S>
+__device__ inline bool sent_by(const S &sh, uint32_t u, uint32_t c, uint32_t t, uint32_t fl)
 {
     const uint32_t b = filter_bit(u, c, fl);
     return ((sh.filt[b >> 5] >> (b & 31u)) & 1u) && sending(sh, u, c, t);
@@ -1284,6 +1302,652 @@ __device__ void match_group(const Layout &ly, const Sizes &sz, const SwGroup &gp
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same matching over columns (k_match_cols): one group per workgroup, each
+// device with at most 64 in-links.  Column i of a destination is the i-th
+// chunk it needs, in priority order; every in-link has its candidates (held by
+// its source, needed by its destination) as a bit row over the columns with
+// summaries above it, and a `live` set per destination masks what has been
+// delivered: a pick is a few dependent reads, a commit clears one bit.  Rows,
+// live sets and mid summaries lie in device memory, but only this workgroup
+// touches them: they are read and updated at workgroup scope, in the XCD's own
+// L2, and the top summaries are in LDS.
+//
+// What bounds it is the length of a window's chain (one event and 1.6 rounds
+// of barriers between exchanges), so the stages were shortened one by one.
+// 512-NPU rail cluster (8 switches of 64 places, no multicast, all-to-all,
+// 1,957 windows) and 128-NPU one (4 places), matching ms:
+//   57.5 / 18.8  row scans (k_match_sw)
+//   59.5 / 15.6  columns, every arrival into a group's sources polled
+//   37.5 / 14.0  arrivals at a limited switch seen in its own group (a mask of
+//                the out-links that want the chunk, one word per switch and
+//                chunk), the others pruned to what can matter
+//   32.7 / 15.3  buffer places looked up a lane per place; the count of a new
+//                place read off the mask after the round's commits
+//   32.4 / 15.6  entries tagged with their window, polled and looked up while
+//                the exchange is under way; log entries written at its end
+//   25.6 / 11.3  six polled entries per thread and one copy of the arrival
+//                code (27 KB of code with registers in scratch before, 21 KB
+//                and none now)
+constexpr uint32_t GC_ITEMS = 6;  // polled entries per thread
+static_assert(GRP_MAX_ITEMS == GC_ITEMS * ST, "the host's limit");
+
+struct ColShared {
+    uint64_t top[SW_MAX_LINKS];       // per link: which mid words (over 4,096 columns) or row words hold candidates
+    unsigned long long coff[SW_MAX_LINKS];  // per destination: its candidate block
+    uint32_t dcols[SW_MAX_LINKS];     // and its columns
+    uint32_t ipre[SW_MAX_LINKS + 1];  // listed entries of the destinations before it
+    uint32_t item[GRP_MAX_ITEMS], items;  // polled entries: place << 10 | group link they feed
+    uint16_t blink[SW_MAX_LINKS];         // per out-link of the limited switches (booff order): the group link
+    uint16_t snext[SW_MAX_LINKS], sfirst[SW_MAX_LINKS];  // the in-links of a destination that come from limited switches
+    uint8_t lq[SW_MAX_LINKS];             // per such link: its place among the switch's out-links
+    uint32_t busy[SW_MAX_LINKS], infl[SW_MAX_LINKS], pick[SW_MAX_LINKS];
+    uint32_t ldst[SW_MAX_LINKS], ltim[SW_MAX_LINKS], llink[SW_MAX_LINKS];
+    uint16_t ldl[SW_MAX_LINKS];
+    uint8_t luni[SW_MAX_LINKS], ldbuf[SW_MAX_LINKS], lsbuf[SW_MAX_LINKS], winf[SW_MAX_LINKS];
+    uint16_t doff[SW_MAX_LINKS + 1];
+    uint16_t uoff[SW_MAX_SW + 1], ulist[SW_MAX_LINKS];
+    uint32_t bcap[SW_MAX_SW];
+    uint16_t bpoff[SW_MAX_SW + 1], booff[SW_MAX_SW + 1];
+    uint32_t bout[SW_MAX_LINKS];
+    uint32_t pc[SW_MAX_POOL], pn[SW_MAX_POOL], occ[SW_MAX_SW];
+    uint32_t filt[SW_FILTER_WORDS];
+    uint16_t uwin[SW_MAX_LINKS];
+    uint32_t ucnt[SW_MAX_SW];
+    uint32_t hd[SW_HASH_WORDS], hu[SW_HASH_WORDS], dpk[SW_MAX_LINKS / 32];
+    uint32_t rflag[2];
+    uint32_t dord[SW_MAX_LINKS / 32];
+    unsigned long long lcur[SW_MAX_LINKS];
+    uint32_t red[SWAVES];
+    uint32_t xr_t[SWAVES], xr_s[SWAVES], xr_e[SWAVES];
+    uint32_t x_tmin, x_err, x_ok, x_late;
+    unsigned long long x_sent;
+};
+
+__device__ __forceinline__ uint64_t wg_load(const uint64_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// position of the x-th set bit (from 0; x less than their number)
+__device__ __forceinline__ uint32_t nth_bit(uint64_t f, uint32_t x)
+{
+    uint32_t at = 0;
+#pragma unroll
+    for (uint32_t w = 32; w; w >>= 1) {
+        const uint32_t c = (uint32_t)__popcll(f & ((1ull << w) - 1ull));
+        if (x >= c) {
+            x -= c;
+            f >>= w;
+            at += w;
+        }
+    }
+    return at;
+}
+
+// The group's static tables and starting state; a thread per link (nL <= ST).
+__device__ void load_columns_group(const Layout &ly, const Sizes &sz, const SwGroup &gp, ColShared &sh)
+{
+    const SwTab &sw = ly.sw;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    if (tid < gp.nL) {
+        const uint32_t x = gp.lbase + tid, sl = sw.lk_slot[x], l = ly.slot_link[sl];
+        sh.llink[tid] = l;
+        sh.ldst[tid] = ly.ldst[l];
+        sh.ltim[tid] = ly.slot_time[sl];
+        sh.ldl[tid] = (uint16_t)sw.lk_dl[x];
+        sh.luni[tid] = small_index(sw.lk_uni[x]);
+        sh.ldbuf[tid] = small_index(sw.lk_dbuf[x]);
+        sh.lsbuf[tid] = small_index(sw.lk_sbuf[x]);
+        sh.busy[tid] = 0u;
+        sh.infl[tid] = NONE32;
+    }
+    for (uint32_t x = tid; x <= gp.nD; x += ST) sh.doff[x] = (uint16_t)sw.d_off[gp.dbase + x];
+    for (uint32_t x = tid; x <= gp.nU; x += ST) sh.uoff[x] = (uint16_t)sw.u_off[gp.ubase + x];
+    for (uint32_t x = tid; x <= gp.nB; x += ST) {
+        sh.bpoff[x] = (uint16_t)sw.b_poff[gp.bbase + x];
+        sh.booff[x] = (uint16_t)sw.b_ooff[gp.bbase + x];
+        if (x < gp.nB) {
+            sh.bcap[x] = sw.b_cap[gp.bbase + x];
+            sh.occ[x] = 0u;
+        }
+    }
+    for (uint32_t x = tid; x < gp.pool_n; x += ST) {
+        sh.pc[x] = 0u;
+        sh.pn[x] = 0u;
+    }
+    __syncthreads();
+    const uint32_t nul = gp.nU ? sh.uoff[gp.nU] : 0u;
+    for (uint32_t x = tid; x < nul; x += ST) sh.ulist[x] = (uint16_t)sw.u_list[gp.ulbase + x];
+    const uint32_t nbo = gp.nB ? sh.booff[gp.nB] : 0u;
+    for (uint32_t x = tid; x < nbo; x += ST) sh.bout[x] = sw.b_out[gp.bobase + x];
+    __syncthreads();
+    // (every group destination has an in-link)
+    uint32_t items = 0;
+    if (tid < gp.nD) {
+        const uint32_t d = sh.ldst[sh.doff[tid]];
+        sh.lcur[tid] = ly.dest_log[d];
+        sh.coff[tid] = ly.cand_off[d];
+        sh.dcols[tid] = ly.dest_cols[d];
+        items = sz.nbr_prune ? ly.poll_cnt[d] : ly.poll_off[d + 1] - ly.poll_off[d];
+    }
+    if (tid == 0) sh.items = 0u;
+    // in-links from limited switches: the chain of each destination's, and
+    // each one's place among its switch's out-links (the k-th parallel link
+    // takes the k-th entry)
+    if (tid < gp.nL) {
+        const uint32_t dl = sh.ldl[tid], b = sh.lsbuf[tid];
+        uint32_t nx = tid + 1;
+        while (nx < sh.doff[dl + 1] && sh.lsbuf[nx] == SW_NONE8) nx++;
+        sh.snext[tid] = (uint16_t)nx;
+        if (tid == sh.doff[dl]) sh.sfirst[dl] = (uint16_t)(b != SW_NONE8 ? tid : nx);
+        if (b != SW_NONE8) {
+            uint32_t dup = 0;
+            for (uint32_t i = sh.doff[dl]; i < tid; i++) dup += sh.lsbuf[i] == b ? 1u : 0u;
+            for (uint32_t q = sh.booff[b]; q < sh.booff[b + 1]; q++)
+                if ((sh.bout[q] >> 16) == dl && dup-- == 0u) {
+                    sh.lq[tid] = (uint8_t)(q - sh.booff[b]);
+                    sh.blink[q] = (uint16_t)tid;
+                    break;
+                }
+        }
+    }
+    // polled entries before each destination (block prefix)
+    {
+        uint32_t inc = items;
+        for (uint32_t o = 1; o < 64; o <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)inc, o);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) sh.red[wave] = inc;
+        __syncthreads();
+        for (uint32_t w = 0; w < wave; w++) inc += sh.red[w];
+        if (tid < gp.nD) sh.ipre[tid + 1] = inc;
+        if (tid == 0) sh.ipre[0] = 0u;
+    }
+    __syncthreads();
+    // the polled entries: not those whose transfers reach a limited switch
+    // (that switch is in this group: its arrivals are seen here)
+    const uint32_t listed = sh.ipre[gp.nD];
+    for (uint32_t x0 = 0; x0 < listed; x0 += ST) {
+        const uint32_t x = x0 + tid;
+        uint32_t it = NONE32;
+        if (x < listed) {
+            uint32_t lo = 0, hi = gp.nD;
+            while (hi - lo > 1) {
+                const uint32_t m = (lo + hi) >> 1;
+                if (sh.ipre[m] <= x) lo = m;
+                else hi = m;
+            }
+            const uint32_t d = sh.ldst[sh.doff[lo]], y = x - sh.ipre[lo], p = ly.poll_off[d];
+            const uint32_t e = sz.nbr_prune ? ly.poll_use[p + ly.out_off[d] + y] : ly.poll[p + y];
+            const uint32_t i = sh.doff[lo] + (e & 0xFFu);
+            if ((e & 0xFFu) != 0xFFu && sh.lsbuf[i] == SW_NONE8) it = ((e >> 8) << 10) | i;
+        }
+        const uint64_t m = __ballot(it != NONE32);
+        uint32_t at = 0;
+        if (lane == 0 && m) at = atomicAdd(&sh.items, (uint32_t)__popcll(m));
+        at = (uint32_t)__shfl((int)at, 0);
+        if (it != NONE32) sh.item[at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = it;
+    }
+    for (uint32_t x0 = 0; x0 < gp.nD; x0 += ST) {
+        const uint32_t x = x0 + tid;
+        bool ok = false;
+        if (x < gp.nD) {
+            const uint32_t a = sh.doff[x], e = sh.doff[x + 1];
+            ok = e > a && (a >> 6) == ((e - 1u) >> 6);
+            for (uint32_t j = a; ok && j + 1 < e; j++) ok = link_key(sh, j) < link_key(sh, j + 1);
+        }
+        const uint64_t m = __ballot(ok);
+        if ((tid & 63u) == 0 && x < gp.nD) {
+            sh.dord[x >> 5] = (uint32_t)m;
+            if (x + 32 < gp.nD) sh.dord[(x >> 5) + 1] = (uint32_t)(m >> 32);
+        }
+    }
+    // live sets (behind each destination's rows and summaries), and the top
+    // summaries
+    for (uint32_t dl = wave; dl < gp.nD; dl += SWAVES) {
+        const uint32_t M = sh.dcols[dl], mw = (M + 63u) >> 6, mm = (mw + 63u) >> 6, n = sh.doff[dl + 1] - sh.doff[dl];
+        uint64_t *live = ly.cand + sh.coff[dl] + (uint64_t)n * (mw + mm);
+        for (uint32_t w = lane; w < mw; w += 64)
+            live[w] = w + 1 < mw || (M & 63u) == 0 ? NONE64 : (1ull << (M & 63u)) - 1ull;
+    }
+    if (tid < gp.nL) {
+        const uint32_t dl = sh.ldl[tid], M = sh.dcols[dl], mw = (M + 63u) >> 6, mm = (mw + 63u) >> 6;
+        const uint32_t n = sh.doff[dl + 1] - sh.doff[dl], j = tid - sh.doff[dl];
+        const uint64_t *mid = ly.cand + sh.coff[dl] + (uint64_t)n * mw + j;
+        uint64_t top = 0;
+        for (uint32_t g = 0; g < mm; g++) {
+            const uint64_t m = mid[(uint64_t)g * n];
+            if (mm > 1u) top |= m ? 1ull << g : 0ull;
+            else top = m;
+        }
+        sh.top[tid] = top;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the live sets are written
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
+{
+    __shared__ ColShared sh;
+    Control *ctl = ly.ctl;
+    if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    const uint32_t tid = threadIdx.x;
+    if (ctl->needs_total == 0) return;
+    const SwGroup gp = load_group(ly.sw, ly.sw.blk_list[ly.sw.blk[blockIdx.x]]);
+    load_columns_group(ly, sz, gp, sh);
+    // this thread's link
+    const bool mine_l = tid < gp.nL;
+    const uint32_t dl = mine_l ? sh.ldl[tid] : 0u, M = mine_l ? sh.dcols[dl] : 0u, mw = (M + 63u) >> 6, mm = (mw + 63u) >> 6;
+    const uint32_t n = mine_l ? sh.doff[dl + 1] - sh.doff[dl] : 1u, j0 = mine_l ? tid - sh.doff[dl] : 0u;
+    const bool l3 = mm > 1u;
+    uint64_t *const block = ly.cand + (mine_l ? sh.coff[dl] : 0ull);
+    uint64_t *const row = block + j0, *const mid = row + (uint64_t)n * mw, *const live = block + (uint64_t)n * (mw + mm);
+    const uint32_t *const rank = ly.col_rank + (mine_l ? ly.dest_log[sh.ldst[tid]] : 0ull);
+    const uint32_t u = mine_l && sh.luni[tid] != SW_NONE8 ? sh.luni[tid] : NONE32;
+    const uint32_t db = mine_l ? sh.ldbuf[tid] : SW_NONE8;
+    const uint32_t pub = mine_l ? ly.pub_off[sh.ldst[tid]] + j0 : 0u;
+    // the entries this thread polls
+    const uint32_t tot = sh.items;
+    uint32_t item[GC_ITEMS];
+#pragma unroll
+    for (uint32_t k = 0; k < GC_ITEMS; k++) item[k] = tid + k * ST < tot ? sh.item[tid + k * ST] : NONE32;
+    const uint32_t nk = (tot + ST - 1) / ST;
+    const uint32_t fl = filter_log2(gp.nU);
+    const uint32_t nfw = gp.nU ? (gp.nU << fl) >> 5 : 0u;
+    const unsigned long long max_windows = ctl->needs_total + 2ull;
+    unsigned long long remaining = ctl->needs_total, k = 0;
+    SwAcc acc = {NONE32, 0u, 0u, 0u, 0ull, 0ull, 0ull};
+    uint32_t t0 = 0, gen = 0;
+    bool logged = true;    // this link's last transfer is in the log
+    uint64_t am = 0;       // limited switch: the out-links that want the chunk in flight to it
+    uint32_t ea[GC_ITEMS], ca[GC_ITEMS];  // polled arrivals of needed chunks, and their columns
+#pragma unroll
+    for (uint32_t q = 0; q < GC_ITEMS; q++) {
+        ea[q] = NONE32;
+        ca[q] = 0;
+    }
+    for (;; k++) {
+        const uint64_t t1 = (uint64_t)t0 + sz.tmin;
+        acc.sent = 0;
+        // arrivals inside the window, in their destinations' columns, that
+        // are still needed
+        uint32_t ra[GC_ITEMS];
+#pragma unroll
+        for (uint32_t q = 0; q < GC_ITEMS; q++) ra[q] = ea[q] >= t0 && (uint64_t)ea[q] < t1 ? ea[q] : NONE32;
+        // the sending filter, from the transfers in flight at t0 (a superset
+        // at every later event of the window); the round tables start empty
+        for (uint32_t x = tid; x < nfw; x += ST) sh.filt[x] = 0u;
+        for (uint32_t x = tid; x < SW_HASH_WORDS; x += ST) {
+            sh.hd[x] = 0u;
+            sh.hu[x] = 0u;
+        }
+        for (uint32_t x = tid; x < SW_MAX_LINKS / 32; x += ST) sh.dpk[x] = 0u;
+        if (tid < 2) sh.rflag[tid] = 0u;
+        __syncthreads();
+        if (u != NONE32 && sh.infl[tid] != NONE32 && sh.busy[tid] > t0) {
+            const uint32_t b = filter_bit(u, sh.infl[tid], fl);
+            atomicOr(&sh.filt[b >> 5], 1u << (b & 31u));
+        }
+        uint32_t par = 0;
+        int64_t t_prev = k == 0 ? -1 : (int64_t)t0 - 1;
+        for (;;) {
+            // next event of the group
+            uint32_t m = k == 0 && t_prev < 0 ? 0u : NONE32;
+            if (mine_l && sh.infl[tid] != NONE32 && (int64_t)sh.busy[tid] > t_prev && (uint64_t)sh.busy[tid] < t1)
+                m = min(m, sh.busy[tid]);
+#pragma unroll
+            for (uint32_t q = 0; q < GC_ITEMS; q++) m = min(m, ra[q]);
+            const uint32_t t = block_min(sh, m);
+            if (t == NONE32) break;
+            // chunks arriving now become candidates of the links they feed
+            bool hit = false;
+            auto offer = [&](uint32_t i, uint32_t c) {
+                const uint32_t dq = sh.ldl[i], w = c >> 6, nq = sh.doff[dq + 1] - sh.doff[dq];
+                const uint32_t mwq = (sh.dcols[dq] + 63u) >> 6;
+                uint64_t *const blk = ly.cand + sh.coff[dq] + (i - sh.doff[dq]);
+                __hip_atomic_fetch_or(&blk[(uint64_t)w * nq], 1ull << (c & 63u), __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (mwq > 64u) {
+                    __hip_atomic_fetch_or(&blk[(uint64_t)(mwq + (w >> 6)) * nq], 1ull << (w & 63u), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+                    atomicOr((unsigned long long *)&sh.top[i], 1ull << (w >> 6));
+                } else {
+                    atomicOr((unsigned long long *)&sh.top[i], 1ull << w);
+                }
+                hit = true;
+            };
+            for (;;) {
+                uint32_t i = NONE32, c = 0, at = 0;
+#pragma unroll
+                for (uint32_t q = 0; q < GC_ITEMS; q++)
+                    if (ra[q] == t) {
+                        i = item[q] & 1023u;
+                        c = ca[q];
+                        at = q;
+                    }
+                if (i == NONE32) break;
+#pragma unroll
+                for (uint32_t q = 0; q < GC_ITEMS; q++)
+                    if (at == q) ra[q] = NONE32;
+                offer(i, c);
+            }
+            if (am && sh.busy[tid] == t) {
+                const uint32_t r = sh.infl[tid], bit = r & 63u;
+                for (; am; am &= am - 1) {
+                    const uint32_t i = sh.blink[sh.booff[db] + (uint32_t)__builtin_ctzll(am)];
+                    const uint64_t at = (uint64_t)sh.ldst[i] * sz.Wp + (r >> 6);
+                    offer(i, ly.need_pre[at] + (uint32_t)__popcll(ly.needs[at] & ((1ull << bit) - 1ull)));
+                }
+            }
+            if (__ballot(hit)) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the bits are set
+            __syncthreads();
+            for (;;) {
+                // picks: the first live candidate of a free link whose
+                // unicast source is not sending it (a full buffer admits
+                // nothing); row words without live bits leave the summaries
+                uint32_t pk = NONE32, col = 0;
+                uint64_t px = 0;
+                bool free = false;
+                if (mine_l && sh.busy[tid] <= t) {
+                    free = db == SW_NONE8 || sh.occ[db] < sh.bcap[db];
+                    if (!free) atomicOr(&sh.rflag[par], 2u);
+                }
+                if (free) {
+                    uint64_t tp = sh.top[tid];
+                    while (tp && pk == NONE32) {
+                        uint32_t w = (uint32_t)__builtin_ctzll(tp);
+                        uint64_t md = 1ull;
+                        if (l3) md = wg_load(&mid[(uint64_t)w * n]);
+                        const uint32_t g = w;
+                        bool kept = false;  // some word of the mid word keeps candidates
+                        while (md && pk == NONE32) {
+                            if (l3) w = g * 64u + (uint32_t)__builtin_ctzll(md);
+                            const uint64_t x = wg_load(&row[(uint64_t)w * n]) & wg_load(&live[w]);
+                            acc.words++;
+                            for (uint64_t y = x; y && pk == NONE32; y &= y - 1) {
+                                const uint32_t cc = w * 64u + (uint32_t)__builtin_ctzll(y);
+                                const uint32_t r = rank[cc] & NBR_RANK_MASK;
+                                if (u != NONE32 && sent_by(sh, u, r, t, fl)) continue;
+                                pk = r;
+                                col = cc;
+                                px = x;
+                            }
+                            if (pk != NONE32) break;
+                            if (x) kept = true;
+                            else if (l3)
+                                __hip_atomic_fetch_and(&mid[(uint64_t)g * n], ~(1ull << (w & 63u)), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                            md &= md - 1ull;
+                        }
+                        if (pk != NONE32) break;
+                        if (!kept) sh.top[tid] &= ~(1ull << g);
+                        tp &= tp - 1ull;
+                    }
+                }
+                if (tid < gp.nU) sh.ucnt[tid] = 0u;
+                if (mine_l) sh.pick[tid] = pk;
+                if (pk != NONE32) {
+                    clash_mark(sh.hd, clash_slot(dl, pk));
+                    if (!(atomicOr(&sh.dpk[dl >> 5], 1u << (dl & 31u)) & (1u << (dl & 31u)))) acc.rounds++;
+                }
+                __syncthreads();
+                // clash on (destination, chunk): fastest link, then lowest id
+                uint32_t win = pk != NONE32;
+                const uint64_t key = win ? link_key(sh, tid) : 0ull;
+                if (win && !clash_alone(sh.hd, clash_slot(dl, pk)))
+                    for (uint32_t i = sh.doff[dl], ie = sh.doff[dl + 1]; i < ie; i++)
+                        if (i != tid && sh.pick[i] == pk && link_key(sh, i) < key) win = 0;
+                if (win && u != NONE32) {
+                    sh.uwin[sh.uoff[u] + atomicAdd(&sh.ucnt[u], 1u)] = (uint16_t)tid;
+                    clash_mark(sh.hu, clash_slot(u, pk));
+                }
+                __syncthreads();
+                // clash on (unicast switch, chunk) among the destination winners
+                if (win && u != NONE32 && !clash_alone(sh.hu, clash_slot(u, pk)))
+                    for (uint32_t q = sh.uoff[u], qe = q + sh.ucnt[u]; q < qe; q++) {
+                        const uint32_t i = sh.uwin[q];
+                        if (i != tid && sh.pick[i] == pk && link_key(sh, i) < key) win = 0;
+                    }
+                if (mine_l) sh.winf[tid] = win ? 3u : 0u;
+                __syncthreads();
+                // free places of a limited switch, in (link time, link id) order
+                bool adm = false;  // takes a place of its limited switch
+                {
+                    const uint64_t w2m = __ballot(win != 0u);
+                    if (win && db != SW_NONE8) {
+                        uint32_t ahead = 0;
+                        if ((sh.dord[dl >> 5] >> (dl & 31u)) & 1u) {
+                            const uint32_t lo = sh.doff[dl] & 63u, me = tid & 63u;
+                            ahead = (uint32_t)__popcll(w2m & ((1ull << me) - 1ull) & ~((1ull << lo) - 1ull));
+                        } else {
+                            for (uint32_t i = sh.doff[dl], ie = sh.doff[dl + 1]; i < ie; i++)
+                                if (i != tid && ((sh.winf[i] >> 1) & 1u) && link_key(sh, i) < key) ahead++;
+                        }
+                        if (ahead >= sh.bcap[db] - sh.occ[db]) win = 0;
+                    }
+                    adm = win && db != SW_NONE8;
+                }
+                __syncthreads();
+                // commit, and clear the round's clash tables for the next one
+                for (uint32_t x = tid; x < SW_HASH_WORDS; x += ST) {
+                    sh.hd[x] = 0u;
+                    sh.hu[x] = 0u;
+                }
+                for (uint32_t x = tid; x < SW_MAX_LINKS / 32; x += ST) sh.dpk[x] = 0u;
+                if (tid == 0) sh.rflag[par ^ 1u] = 0u;
+                if (pk != NONE32 && !win) {
+                    acc.clashes++;
+                    atomicOr(&sh.rflag[par], 1u);
+                }
+                if (win) {
+                    __hip_atomic_fetch_and(&live[col >> 6], ~(1ull << (col & 63u)), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (!l3 && !(px & (px - 1ull))) sh.top[tid] &= ~(1ull << (col >> 6));
+                    const uint64_t end = (uint64_t)t + sh.ltim[tid];
+                    if (end > 0xFFFFFFFFull) {
+                        record_error(ctl, ST_ERANGE, pk, sh.ldst[tid], 2);
+                        acc.err = 1;
+                    }
+                    const uint32_t e32 = end > 0xFFFFFFFFull ? NONE32 - 1u : (uint32_t)end;
+                    sh.busy[tid] = e32;
+                    sh.infl[tid] = pk;
+                    if (u != NONE32) {
+                        const uint32_t fb = filter_bit(u, pk, fl);
+                        atomicOr(&sh.filt[fb >> 5], 1u << (fb & 31u));
+                    }
+                    acc.cstar = max(acc.cstar, e32);
+                    logged = false;
+                    acc.sent++;
+                }
+                // what was delivered leaves the limited switches that feed
+                // the destination: one out-link less leads to a device that
+                // needs the chunk, and the place that holds it counts one
+                // less.  The wave looks a place up together, a lane per
+                // place (places change hands in the next stage only).
+                {
+                    uint32_t i = win ? sh.sfirst[dl] : 0u, have = NONE32, hc = 0, hn = 0;
+                    const uint32_t ie = win ? sh.doff[dl + 1] : 0u, lane = tid & 63u;
+                    for (uint64_t m; (m = __ballot(i < ie)) != 0;) {
+                        const uint32_t who = (uint32_t)__builtin_ctzll(m);
+                        const uint32_t li = (uint32_t)__builtin_amdgcn_readlane((int)i, (int)who);
+                        const uint32_t lc = (uint32_t)__builtin_amdgcn_readlane((int)pk, (int)who);
+                        const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.lsbuf[li]);
+                        const uint32_t s0 = sh.bpoff[b], cap = sh.bpoff[b + 1] - s0;
+                        for (uint32_t o = 0; o < cap; o += 64) {
+                            if (have != s0 + o) {
+                                have = s0 + o;
+                                hc = o + lane < cap ? sh.pc[have + lane] : 0u;
+                                hn = o + lane < cap ? sh.pn[have + lane] : 0u;
+                            }
+                            if (hn && hc == lc) {
+                                if (atomicSub(&sh.pn[have + lane], 1u) == 1u) {
+                                    atomicSub(&sh.occ[b], 1u);
+                                    atomicOr(&sh.rflag[par], 4u);
+                                }
+                            }
+                        }
+                        if (lane == who) {
+                            __hip_atomic_fetch_and(&ly.sw.amask[(uint64_t)(gp.bbase + b) * sz.C + pk], ~(1ull << sh.lq[i]),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            i = sh.snext[i];
+                        }
+                    }
+                }
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the masks are up to date
+                __syncthreads();
+                // a limited switch that took a chunk buffers it while an
+                // out-link leads to a device that still needs it
+                {
+                    uint32_t cnt = 0, o = 0;
+                    if (adm) {
+                        am = wg_load(&ly.sw.amask[(uint64_t)(gp.bbase + db) * sz.C + pk]);
+                        cnt = (uint32_t)__popcll(am);
+                    }
+                    const uint32_t lane = tid & 63u, s0 = cnt ? sh.bpoff[db] : 0u;
+                    // free places, a lane per place: the j-th lane that wants
+                    // one of a switch takes the j-th free one (counted from a
+                    // place of the wave's own); one that another wave took
+                    // meanwhile is tried again.  Places only fill in this
+                    // stage, and there is one for every admission.
+                    uint32_t tries = 0;
+                    for (uint64_t m; (m = __ballot(cnt != 0u)) != 0;) {
+                        if (++tries > 16u * SW_MAX_POOL) {
+                            if (cnt) record_error(ctl, ST_EINTERNAL, 5, 0, 0);
+                            acc.err |= cnt ? 1u : 0u;
+                            break;
+                        }
+                        const uint32_t who = (uint32_t)__builtin_ctzll(m);
+                        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)db, (int)who);
+                        const uint32_t ws = (uint32_t)__builtin_amdgcn_readlane((int)s0, (int)who);
+                        const uint32_t wo = (uint32_t)__builtin_amdgcn_readlane((int)o, (int)who);
+                        const uint32_t cap = sh.bpoff[b + 1] - ws;
+                        const bool same = cnt != 0u && db == b && o == wo;
+                        const uint64_t sm = __ballot(same);
+                        const uint32_t want = (uint32_t)__popcll(sm & ((1ull << lane) - 1ull));
+                        const uint64_t fr = __ballot(wo + lane < cap && sh.pn[min(ws + wo + lane, ws + cap - 1u)] == 0u);
+                        const uint32_t nf = (uint32_t)__popcll(fr);
+                        if (same) {
+                            if (nf == 0u) {
+                                o = wo + 64u < cap ? wo + 64u : 0u;
+                            } else if (want < nf) {
+                                const uint32_t s = ws + wo + nth_bit(fr, (want + (tid >> 6) * 11u) % nf);
+                                if (atomicCAS(&sh.pn[s], 0u, cnt) == 0u) {
+                                    sh.pc[s] = pk;
+                                    atomicAdd(&sh.occ[db], 1u);
+                                    cnt = 0u;
+                                }
+                            }
+                        }
+                    }
+                }
+                // the commits' updates are done before the next round's picks
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+                __syncthreads();
+                const uint32_t f = sh.rflag[par];
+                par ^= 1u;
+                if (!(f & 1u) && (f & 6u) != 6u) break;
+            }
+            t_prev = t;
+        }
+        // the next window's entries, tagged with the window: the transfers
+        // still in flight at its start.  A link sends at most once per
+        // window, so its log entry waits for this place.
+        uint32_t tm = NONE32;
+        const uint32_t tag = (uint32_t)k & 0xFFFu;
+        if (mine_l) {
+            const uint32_t c = sh.infl[tid], e = sh.busy[tid];
+            const bool on = c != NONE32 && (uint64_t)e >= t1;
+            __hip_atomic_store(&ly.pub[(k & 1) * sz.pub_n + pub],
+                               ((uint64_t)((tag << NBR_TAG_SHIFT) | (on ? c : 0u)) << 32) | (on ? e : 0u),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (on) tm = e;
+            if (!logged) {
+                const unsigned long long q = atomicAdd(&sh.lcur[dl], 1ull);
+                ly.skey[0][q] = ((uint64_t)(e - sh.ltim[tid]) << 32) | sh.llink[tid];
+                ly.sval[0][q] = c;
+                logged = true;
+            }
+        }
+        if (tid == 0) sh.x_late = 0u;
+        const uint64_t *rd = ly.pub + (k & 1) * sz.pub_n;
+        // while the exchange is under way the polled entries are read as
+        // soon as they are out, and whether their chunks are needed is looked
+        // up for all of them together
+        if (!sw_sync<true>(ctl, ly.xslot, ++gen, tm, acc.sent, acc.err ? 1u : 0u, sh, [&] {
+                uint64_t e[GC_ITEMS], nw[GC_ITEMS];
+                for (uint32_t spins = 0;;) {
+                    bool all = true;
+#pragma unroll
+                    for (uint32_t q = 0; q < GC_ITEMS; q++) {
+                        e[q] = 0;
+                        if (q < nk)
+                            e[q] = __hip_atomic_load(&rd[item[q] == NONE32 ? pub : item[q] >> 10], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                    for (uint32_t q = 0; q < GC_ITEMS; q++)
+                        if (q < nk && item[q] != NONE32 && (uint32_t)(e[q] >> (32 + NBR_TAG_SHIFT)) != tag) all = false;
+                    if (__ballot(!all) == 0) break;
+                    if (++spins > SW_SPIN_LIMIT ||
+                        __hip_atomic_load(&ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                        atomicExch(&ctl->abort, 1u);
+                        sh.x_late = 1u;
+                        break;
+                    }
+                }
+#pragma unroll
+                for (uint32_t q = 0; q < GC_ITEMS; q++) {
+                    nw[q] = 0;
+                    if (q >= nk) continue;
+                    if (item[q] == NONE32) e[q] = 0;
+                    const uint32_t r = (uint32_t)(e[q] >> 32) & ((1u << NBR_TAG_SHIFT) - 1u);
+                    const uint64_t at = (uint32_t)e[q] ? (uint64_t)sh.ldst[item[q] & 1023u] * sz.Wp + (r >> 6) : 0ull;
+                    nw[q] = ly.needs[at];
+                    ca[q] = ly.need_pre[at];
+                }
+#pragma unroll
+                for (uint32_t q = 0; q < GC_ITEMS; q++) {
+                    const uint32_t bit = (uint32_t)(e[q] >> 32) & 63u;
+                    const bool need = (uint32_t)e[q] != 0u && ((nw[q] >> bit) & 1ull);
+                    ea[q] = need ? (uint32_t)e[q] : NONE32;
+                    ca[q] += (uint32_t)__popcll(nw[q] & ((1ull << bit) - 1ull));
+                }
+            }))
+            break;
+        if (sh.x_late) break;
+        remaining -= sh.x_sent;
+        if (sh.x_err || remaining == 0) break;
+        if (sh.x_tmin == NONE32) {
+            record_error(ctl, ST_EDEADLOCK, (uint32_t)remaining, 0, 0);
+            break;
+        }
+        if (k + 1 >= max_windows) {
+            record_error(ctl, ST_EINTERNAL, 1, 0, 0);
+            break;
+        }
+        t0 = sh.x_tmin;
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        ctl->needs_remaining = remaining;
+        ctl->windows = k + 1;
+        ctl->n_log = ctl->needs_total - remaining;
+    }
+    for (int off = 32; off; off >>= 1) {
+        acc.cstar = max(acc.cstar, (uint32_t)__shfl_xor(acc.cstar, off));
+        acc.rounds += (unsigned long long)__shfl_xor(acc.rounds, off);
+        acc.clashes += (unsigned long long)__shfl_xor(acc.clashes, off);
+        acc.words += (unsigned long long)__shfl_xor(acc.words, off);
+    }
+    if ((tid & 63) == 0) {
+        atomicMax(&ctl->cstar, acc.cstar);
+        if (acc.clashes) atomicAdd(&ctl->clashes, acc.clashes);
+        if (acc.words) atomicAdd(&ctl->scan_words, acc.words);
+        if (acc.rounds) atomicAdd(&ctl->rounds, acc.rounds);
+    }
+}
+
 // Can the no-multicast rule change the schedule?  Only when two
 // out-neighbours of one unicast switch need the same chunk (the needs rows as
 // set up, relay marks included, over the whole run: needs only shrink).
@@ -1351,7 +2015,7 @@ __global__ void __launch_bounds__(ST) k_match_sw(Layout ly, Sizes sz)
         for (uint32_t q = q0; q < q1; q++)
             match_group(ly, sz, load_group(sw, sw.blk_list[q]), sh, t0, t1, k == 0, resident, acc, plane[k & 1],
                         plane[(k + 1) & 1]);
-        if (!sw_sync(ctl, ly.xslot, ++gen, acc.tmin, acc.sent, acc.err ? 1u : 0u, sh)) break;
+        if (!sw_sync<false>(ctl, ly.xslot, ++gen, acc.tmin, acc.sent, acc.err ? 1u : 0u, sh, [] {})) break;
         remaining -= sh.x_sent;
         if (sh.x_err || remaining == 0) break;
         if (sh.x_tmin == NONE32) {
@@ -1403,6 +2067,23 @@ hipError_t launch_unicast_check(const Layout &ly, const Sizes &sz, hipStream_t s
     if (bx > 0x7FFFFFFFull) return hipErrorInvalidValue;
     k_unicast_check<<<dim3((uint32_t)bx, n_uni), 256, 0, st>>>(ly, sz);
     return hipGetLastError();
+}
+
+int match_cols_max_grid(int device)
+{
+    int per_cu = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_match_cols, ST, 0) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
+    return per_cu * cus;
+}
+
+hipError_t launch_match_cols(const Layout &ly, const Sizes &sz, hipStream_t st, int grid)
+{
+    if (grid < 1 || grid > (int)MAX_MATCH_GRID) return hipErrorInvalidValue;
+    Layout l = ly;
+    Sizes s = sz;
+    void *args[] = {&l, &s};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_match_cols), dim3(grid), dim3(ST), args, 0, st);
 }
 
 hipError_t launch_match_sw(const Layout &ly, const Sizes &sz, hipStream_t st, int grid)

@@ -29,11 +29,13 @@ __global__ void __launch_bounds__(256) k_reset(Layout ly, Sizes sz)
         ly.chunk_dist[i] = 0;
     }
     for (uint64_t i = i0; i < sz.N; i += step) ly.is_src[i] = 0;
+    if (sz.sw_cols)
+        for (uint64_t i = i0; i < 2ull * MAX_MATCH_GRID; i += step) ly.xslot[i * XSLOT_WORDS] = 0;
     const uint4 z = make_uint4(0, 0, 0, 0);
     const uint64_t bm = (uint64_t)sz.D * sz.Wp / 2;  // rows are whole 1 KiB lines
     for (uint64_t i = i0; i < bm; i += step) {
         reinterpret_cast<uint4 *>(ly.needs)[i] = z;
-        if (!sz.nbr) reinterpret_cast<uint4 *>(ly.holds)[i] = z;
+        if (!sz.cols) reinterpret_cast<uint4 *>(ly.holds)[i] = z;
     }
 }
 
@@ -232,11 +234,16 @@ __global__ void k_adm_counts(Layout ly, Sizes sz)
     if (c >= sz.C) return;
     const uint32_t o0 = ly.sw.b_abs[2 * row], no = ly.sw.b_abs[2 * row + 1];
     uint32_t n = 0;
+    uint64_t mask = 0;
     for (uint32_t q = 0; q < no; q++) {
         const uint32_t o = ly.sw.b_out[o0 + q] & 0xFFFFu;
-        n += (uint32_t)((ly.needs[(uint64_t)o * sz.Wp + (c >> 6)] >> (c & 63u)) & 1ull);
+        const uint64_t x = (ly.needs[(uint64_t)o * sz.Wp + (c >> 6)] >> (c & 63u)) & 1ull;
+        n += (uint32_t)x;
+        mask |= x << (q & 63u);
     }
-    ly.sw.acnt[(uint64_t)row * sz.C + c] = n;
+    // (a column plan's switches have at most 64 out-links)
+    if (sz.sw_cols) ly.sw.amask[(uint64_t)row * sz.C + c] = mask;
+    else ly.sw.acnt[(uint64_t)row * sz.C + c] = n;
 }
 
 // Priority order (distance descending, then the SplitMix64 key ascending,
@@ -257,7 +264,7 @@ __device__ inline void set_rank(const Layout &ly, const Sizes &sz, uint32_t r, u
     ly.order[r] = c;
     ly.rank[c] = r;
     // (the counts of the array it shares are no longer read)
-    if (sz.nbr) ly.rank_src[r] = ly.chunk_src[c];
+    if (sz.cols) ly.rank_src[r] = ly.chunk_src[c];
 }
 
 // After the sort: ranks.  The first thread of a run of equal sort keys (equal
@@ -795,9 +802,10 @@ hipError_t launch_setup(const Layout &ly, const Sizes &sz, const uint64_t *pre, 
         if (e != hipSuccess) return e;
         k_rank<<<blocks_for(C, T), T, 0, st>>>(ly, sz, seed);
     }
-    if (C && !sz.nbr) k_holds<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
+    if (C && !sz.cols) k_holds<<<blocks_for(C, T), T, 0, st>>>(ly, sz);
     if (sz.W) k_needs<<<gw, T, 0, st>>>(ly, sz, pre, post);
-    if (sz.nbr) {
+    if (sz.sw_nbt && C) k_adm_counts<<<dim3(blocks_for(C, T), sz.sw_nbt), T, 0, st>>>(ly, sz);
+    if (sz.cols) {
         k_need_prefix<<<sz.D, (uint32_t)std::min<uint64_t>(1024, ((sz.W + 3) / 4 + 63) / 64 * 64 + (sz.W ? 0 : 64)), 0, st>>>(ly, sz);
         k_columns<<<sz.D, 1024, 0, st>>>(ly, sz);
         if (sz.nbr_prune && C) {
@@ -808,7 +816,6 @@ hipError_t launch_setup(const Layout &ly, const Sizes &sz, const uint64_t *pre, 
         }
         return hipGetLastError();
     }
-    if (sz.sw_nbt && C) k_adm_counts<<<dim3(blocks_for(C, T), sz.sw_nbt), T, 0, st>>>(ly, sz);
     if (sz.L) k_link_counts<<<blocks_for(sz.L, 4), 256, 0, st>>>(ly, sz);
     k_needs_count<<<sz.D, 256, 0, st>>>(ly, sz);
     k_log_offsets<<<1, 1024, 0, st>>>(ly, sz);
