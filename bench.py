@@ -26,16 +26,18 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBPS = 8000.0
 # Algorithmic bytes of the matching kernel, per launch: 16 B per scanned
-# word position (one 8-byte word of the source's holds row and one of the
-# destination's needs row) plus 96 B per committed transfer (the two words
-# holding its bit, the needs-word read-modify-write, the holds-word set at
-# arrival, link state, the send record and one atomic).
+# word position (one 8-byte word of a link's candidates and one of the set it
+# is masked with: the live columns, or the source's holds row and the
+# destination's needs row in the kernels over bitmap rows) plus 96 B per
+# committed transfer (the two words holding its bit, the needs-word
+# read-modify-write, the holds-word set at arrival, link state, the send
+# record and one atomic).
 BYTES_PER_SCANNED_WORD = 16
 BYTES_PER_MATCH = 96
 
 
-COUNTERS = os.path.join(ROOT, "profiles", "k_match_switch2level_512_a2a_hbm_counters.md")
-MATCH_SRC = os.path.join(ROOT, "paper_2606_07019_amd", "csrc", "pccl_match.hip")
+COUNTERS = os.path.join(ROOT, "profiles", "k_match_nbr_switch2level_512_a2a_hbm_counters.md")
+MATCH_SRC = os.path.join(ROOT, "paper_2606_07019_amd", "csrc", "pccl_match_nbr.hip")
 
 
 def code_sha256(path: str) -> str:
@@ -52,16 +54,16 @@ def code_sha256(path: str) -> str:
 
 
 def measured_traffic(config: int):
-    """HBM bytes per k_match launch from the committed counter summary, or
+    """HBM bytes per k_match_nbr launch from the committed counter summary, or
     None when the kernel's code changed since the counters were taken."""
     if config != 4 or not os.path.exists(COUNTERS):
         return None
     want, traffic = None, None
     with open(COUNTERS) as f:
         for line in f:
-            if "k_match code sha256:" in line:
+            if "k_match_nbr code sha256:" in line:
                 want = line.split(":", 1)[1].strip()
-            elif "k_match traffic bytes per launch:" in line:
+            elif "k_match_nbr traffic bytes per launch:" in line:
                 traffic = int(line.split(":", 1)[1].strip())
     return traffic if want == code_sha256(MATCH_SRC) else None
 
@@ -189,9 +191,10 @@ def switch_model(args, W, Synthesizer, torch):
         torch.cuda.synchronize()
         step_s = (time.perf_counter() - t0) / steps
         st, pr = syn.stats(), syn.profile()
-        # the switch-group kernel, or the plain one when the device found
-        # that the no-multicast rule cannot act (and no buffer limit binds)
-        kern = "k_match_sw" if syn.matcher() == "switch" else "k_match"
+        # the switch-group kernel (over columns where a buffer limit binds),
+        # or the plain windowed one when the device found that the
+        # no-multicast rule cannot act
+        kern = ("k_match_cols" if buf else "k_match_sw") if syn.matcher() == "switch" else "k_match"
         kms = sum(match_ms) / len(match_ms)
         alg = BYTES_PER_SCANNED_WORD * pr["scan_words"] + BYTES_PER_MATCH * syn.n_sends
         pt = {"workload": wl.name, "npus": nn * pn, "buffer_chunks": buf, "unicast": bool(uni),
@@ -302,7 +305,7 @@ def main():
     traffic = measured_traffic(args.config)
     roofline = {"bound": "hbm", "achieved": round(achieved, 3), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM_GBPS, 6), "traffic": traffic,
-                "kernel": "k_match", "kernel_ms": round(avg_match_s * 1e3, 4),
+                "kernel": "k_match_nbr", "kernel_ms": round(avg_match_s * 1e3, 4),
                 "alg_bytes_per_launch": alg_bytes, "scan_words": prof["scan_words"], "matches": n,
                 # the counter bytes (FETCH_SIZE + WRITE_SIZE, calibrated) over the same
                 # kernel time: HBM GB/s as the hardware counts it, MALL hits included

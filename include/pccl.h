@@ -376,7 +376,8 @@ pccl_status pccl_get_setup(pccl_ctx *ctx, uint32_t *link_time_ns, uint32_t *chun
  * through the word holding its pick, or to the end of the row's own
  * ceil(chunks / 64) words when it found none), including the positions a
  * busy link's look-ahead passed; each position is one 64-bit word of each
- * row.  Any pointer may be NULL.
+ * row.  The kernels over columns count the candidate row words their picks
+ * read.  Any pointer may be NULL.
  */
 pccl_status pccl_get_profile(pccl_ctx *ctx, double *setup_ms, double *match_ms, double *output_ms,
                              uint64_t *scan_words);

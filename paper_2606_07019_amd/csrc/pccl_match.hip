@@ -1,5 +1,8 @@
 // The event-stepped chunk-to-link matching, as one persistent cooperative
-// kernel.
+// kernel.  It takes the networks that the neighbour-stepped kernel
+// (pccl_match_nbr.hip) does not: devices beyond one wavefront, more than 1,024
+// devices or 2^18 chunks, link times far apart, workspaces that hold only its
+// layout, and the plain side of the check on unicast switches.
 //
 // Semantics (what the schedule must equal): at every event time t, links
 // whose transfer ends at t deliver and become free; then every free link

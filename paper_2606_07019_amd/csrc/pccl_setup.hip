@@ -225,7 +225,8 @@ __global__ void __launch_bounds__(256) k_chunk_dist(Layout ly, Sizes sz, const u
 // switch's out-links lead to a device that needs the chunk once the needs
 // rows are set up (the matching kernel keeps the count as those devices
 // receive it, and reads it when the switch takes the chunk into a buffer
-// place).  One thread per (row, chunk): the 64 threads of a wave read the
+// place); for the kernel over columns which ones, as a mask.  One thread per
+// (row, chunk): the 64 threads of a wave read the
 // same needs word of each out-neighbour.
 __global__ void k_adm_counts(Layout ly, Sizes sz)
 {
