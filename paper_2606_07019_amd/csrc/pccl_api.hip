@@ -727,7 +727,13 @@ void build_poll(pccl_ctx *c)
 // polled entries), at most 2^18 chunks (two summary levels), all devices
 // resident with the live set and the summaries of the worst case (a device
 // that needs every chunk) in their share of LDS, and link times within a
-// factor of NBR_MAX_RATIO (its windows do not skip idle time).  It takes at
+// factor of NBR_MAX_RATIO.  Its windows do not skip idle time, which costs
+// 0.8-1.0 us each, where the windowed kernel takes 5-8 us for every window
+// with an event: whole calls with almost all links r times as slow as the
+// fastest, neighbour-stepped and windowed, us: 64-ring, 16 chunks per NPU,
+// r 8 5,288 and 7,422, r 16 9,703 and 7,307; 5x5x8 torus with axes 1, r/2 and
+// r, r 8 2,329 and 2,762, r 12 3,260 and 2,851; 9x5 rail cluster with uplinks
+// r times as slow, r 8 562 and 703, r 12 716 and 700.  It takes at
 // most one wave per SIMD: with several workgroups per compute unit (2,200
 // devices, three workgroups of three waves) a wait on a neighbour's entry ran
 // into the spin limit, which reading has not explained; such networks stay

@@ -47,7 +47,7 @@ constexpr uint32_t NBR_XCDS = 8;               // workgroups go to the XCDs in t
 constexpr uint32_t NBR_COUNT_SHIFT = 20;       // column list: above the rank, the in-neighbours that ever hold the chunk
 constexpr uint32_t NBR_RANK_MASK = (1u << NBR_COUNT_SHIFT) - 1u;
 constexpr uint32_t NBR_MAX_POLL = 512;         // entries one device polls per window
-constexpr uint32_t NBR_MAX_RATIO = 64;         // largest link time over the smallest
+constexpr uint32_t NBR_MAX_RATIO = 9;          // largest link time over the smallest
 
 // Switch groups over columns: entries the devices of one group poll, those
 // that reach a limited switch aside (a few registers per thread each).

@@ -34,7 +34,7 @@ def _complete(n):
 
 def _slow_link(ratio):
     """An 8-ring whose links take 1,000 ns but one pair that takes ratio times
-    as long: the kernel is chosen up to a factor of 64."""
+    as long: the kernel is chosen up to a factor of 9."""
     pairs = [(i, (i + s) % 8) for i in range(8) for s in (1, 7)]
     alpha = [900 + (ratio - 1) * 1000 * ({a, b} == {3, 4}) for a, b in pairs]
     return W.make_topology(8, 0, pairs, alpha, 1)
@@ -66,6 +66,8 @@ CASES = {
     "ring 8 x 512": lambda: W.Workload("r8", W.ring(8), W.all_gather(8, range(8), 512, 1 << 14), 9),
     "ring 8 x 520": lambda: W.Workload("r8b", W.ring(8), W.all_gather(8, range(8), 520, 1 << 14), 10),
     # link times a factor 64 and 65 apart
+    "slow link 9": lambda: _generic("slow9", _slow_link(9), 60, 100, 4, 21),
+    "slow link 10": lambda: _generic("slow10", _slow_link(10), 60, 100, 4, 22),
     "slow link 64": lambda: _generic("slow64", _slow_link(64), 60, 100, 4, 11),
     "slow link 65": lambda: _generic("slow65", _slow_link(65), 60, 100, 4, 12),
     # four waves per workgroup, and one device too many for them
