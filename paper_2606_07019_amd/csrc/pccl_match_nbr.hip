@@ -1,6 +1,6 @@
 // The event-stepped chunk-to-link matching with neighbour-only
-// synchronisation: the kernel of every network whose devices each fit one
-// wavefront.
+// synchronisation: the kernel of the networks whose devices each fit one
+// wavefront and whose link times lie close together (plan_nbr has the rule).
 //
 // Semantics are those of the windowed matcher (pccl_match.hip): at every
 // event time links whose transfer ends deliver and become free, every free
