@@ -75,6 +75,9 @@ CASES = {
     "mesh 41x25": lambda: _generic("mesh1025", W.mesh2d(41, 25), 600, 4096, 6, 14),
     # switches with 16,128 columns: their column list stays in device memory
     "rail 64x4": lambda: W.Workload("rail64x4", W.switch2level(64, 4), W.a2a_bitmaps(256, 8192), 15),
+    # a switch of 64 in-links and 8,064 columns that shares its LDS: its candidate rows stay in device memory, set by one
+    # lane and read by another
+    "star 64 x 2": lambda: W.Workload("star64", W.star(64), W.a2a_k_bitmaps(64, 2, 8192), 23),
 }
 
 
