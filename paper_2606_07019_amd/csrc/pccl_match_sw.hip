@@ -1633,12 +1633,52 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
                     if (at == q) ra[q] = NONE32;
                 offer(i, c);
             }
-            if (am && sh.busy[tid] == t) {
-                const uint32_t r = sh.infl[tid], bit = r & 63u;
-                for (; am; am &= am - 1) {
-                    const uint32_t i = sh.blink[sh.booff[db] + (uint32_t)__builtin_ctzll(am)];
-                    const uint64_t at = (uint64_t)sh.ldst[i] * sz.Wp + (r >> 6);
-                    offer(i, ly.need_pre[at] + (uint32_t)__popcll(ly.needs[at] & ((1ull << bit) - 1ull)));
+            // chunks that reach a limited switch now: an offer to every
+            // out-link that wants the chunk, shared out evenly over the wave
+            // (a multicast has up to 64, and one lane for all of them cost an
+            // All-Gather behind a 64-port switch 25 us a window)
+            {
+                const uint32_t lane = tid & 63u;
+                uint64_t wants = 0;
+                if (am && sh.busy[tid] == t) {
+                    wants = am;
+                    am = 0;
+                }
+                const uint32_t cnt = (uint32_t)__popcll(wants);
+                if (__ballot(cnt != 0u)) {
+                    const bool many = __ballot(cnt > 1u) != 0;
+                    uint32_t inc = cnt, total = 64;
+                    if (many) {
+                        for (uint32_t o = 1; o < 64; o <<= 1) {
+                            const uint32_t y = (uint32_t)__shfl_up((int)inc, o);
+                            if (lane >= o) inc += y;
+                        }
+                        total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+                    }
+                    const uint32_t chunk = wants ? sh.infl[tid] : 0u;
+                    for (uint32_t x0 = 0; x0 < total; x0 += 64) {
+                        uint32_t own = lane, nth = 0;
+                        if (many) {
+                            // the lane that has offer number x0 + lane
+                            own = 0;
+                            for (uint32_t o = 32; o; o >>= 1)
+                                if ((uint32_t)__shfl((int)inc, (int)(own + o - 1u)) <= x0 + lane) own += o;
+                            nth = x0 + lane - (uint32_t)__shfl((int)(inc - cnt), (int)own);
+                        }
+                        uint64_t w = wants;
+                        uint32_t r = chunk, b = db;
+                        if (many) {
+                            w = (uint64_t)__shfl((unsigned long long)wants, (int)own);
+                            r = (uint32_t)__shfl((int)chunk, (int)own);
+                            b = (uint32_t)__shfl((int)db, (int)own);
+                        }
+                        if (x0 + lane < total && w) {
+                            const uint32_t q = many ? nth_bit(w, nth) : (uint32_t)__builtin_ctzll(w);
+                            const uint32_t i = sh.blink[sh.booff[b] + q], bit = r & 63u;
+                            const uint64_t at = (uint64_t)sh.ldst[i] * sz.Wp + (r >> 6);
+                            offer(i, ly.need_pre[at] + (uint32_t)__popcll(ly.needs[at] & ((1ull << bit) - 1ull)));
+                        }
+                    }
                 }
             }
             if (__ballot(hit)) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the bits are set
@@ -1764,35 +1804,50 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
                 // what was delivered leaves the limited switches that feed
                 // the destination: one out-link less leads to a device that
                 // needs the chunk, and the place that holds it counts one
-                // less.  The wave looks a place up together, a lane per
-                // place (places change hands in the next stage only).
+                // less (places change hands in the next stage only).  A
+                // place is looked up by the lane itself where the switch has
+                // no more places than the wave has lookups (a multicast),
+                // else by the wave, a lane per place.
                 {
-                    uint32_t i = win ? sh.sfirst[dl] : 0u, have = NONE32, hc = 0, hn = 0;
-                    const uint32_t ie = win ? sh.doff[dl + 1] : 0u, lane = tid & 63u;
-                    for (uint64_t m; (m = __ballot(i < ie)) != 0;) {
-                        const uint32_t who = (uint32_t)__builtin_ctzll(m);
-                        const uint32_t li = (uint32_t)__builtin_amdgcn_readlane((int)i, (int)who);
-                        const uint32_t lc = (uint32_t)__builtin_amdgcn_readlane((int)pk, (int)who);
-                        const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.lsbuf[li]);
-                        const uint32_t s0 = sh.bpoff[b], cap = sh.bpoff[b + 1] - s0;
-                        for (uint32_t o = 0; o < cap; o += 64) {
-                            if (have != s0 + o) {
-                                have = s0 + o;
-                                hc = o + lane < cap ? sh.pc[have + lane] : 0u;
-                                hn = o + lane < cap ? sh.pn[have + lane] : 0u;
-                            }
-                            if (hn && hc == lc) {
-                                if (atomicSub(&sh.pn[have + lane], 1u) == 1u) {
-                                    atomicSub(&sh.occ[b], 1u);
-                                    atomicOr(&sh.rflag[par], 4u);
+                    const uint32_t lane = tid & 63u, ie = win ? sh.doff[dl + 1] : 0u;
+                    uint32_t i = win ? sh.sfirst[dl] : 0u;
+                    for (uint64_t left; (left = __ballot(i < ie)) != 0;) {
+                        const uint32_t b = i < ie ? sh.lsbuf[i] : 0u, s0 = sh.bpoff[b], cap = sh.bpoff[b + 1] - s0;
+                        const bool self = i < ie && cap <= (uint32_t)__popcll(left);
+                        if (i < ie)
+                            __hip_atomic_fetch_and(&ly.sw.amask[(uint64_t)(gp.bbase + b) * sz.C + pk], ~(1ull << sh.lq[i]),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (self)
+                            for (uint32_t o = 0; o < cap; o++)
+                                if (sh.pn[s0 + o] && sh.pc[s0 + o] == pk) {
+                                    if (atomicSub(&sh.pn[s0 + o], 1u) == 1u) {
+                                        atomicSub(&sh.occ[b], 1u);
+                                        atomicOr(&sh.rflag[par], 4u);
+                                    }
+                                    break;
+                                }
+                        uint32_t have = NONE32, hc = 0, hn = 0;
+                        for (uint64_t m = __ballot(i < ie && !self); m; m &= m - 1ull) {
+                            const uint32_t who = (uint32_t)__builtin_ctzll(m);
+                            const uint32_t lc = (uint32_t)__builtin_amdgcn_readlane((int)pk, (int)who);
+                            const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)b, (int)who);
+                            const uint32_t p0 = (uint32_t)__builtin_amdgcn_readlane((int)s0, (int)who);
+                            const uint32_t pe = (uint32_t)__builtin_amdgcn_readlane((int)cap, (int)who);
+                            for (uint32_t o = 0; o < pe; o += 64) {
+                                if (have != p0 + o) {
+                                    have = p0 + o;
+                                    hc = o + lane < pe ? sh.pc[have + lane] : 0u;
+                                    hn = o + lane < pe ? sh.pn[have + lane] : 0u;
+                                }
+                                if (hn && hc == lc) {
+                                    if (atomicSub(&sh.pn[have + lane], 1u) == 1u) {
+                                        atomicSub(&sh.occ[lb], 1u);
+                                        atomicOr(&sh.rflag[par], 4u);
+                                    }
                                 }
                             }
                         }
-                        if (lane == who) {
-                            __hip_atomic_fetch_and(&ly.sw.amask[(uint64_t)(gp.bbase + b) * sz.C + pk], ~(1ull << sh.lq[i]),
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            i = sh.snext[i];
-                        }
+                        if (i < ie) i = sh.snext[i];
                     }
                 }
                 __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the masks are up to date
