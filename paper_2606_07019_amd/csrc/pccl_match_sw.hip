@@ -480,8 +480,7 @@ __device__ void load_group_state(const Layout &ly, const Sizes &sz, const SwGrou
 
 // A unicast switch keeps one copy of a chunk in flight: is chunk c in flight
 // on one of switch u's out-links at time t?
-template <class S>
-__device__ inline bool sending(const S &sh, uint32_t u, uint32_t c, uint32_t t)
+__device__ inline bool sending(const SwShared &sh, uint32_t u, uint32_t c, uint32_t t)
 {
     for (uint32_t q = sh.uoff[u]; q < sh.uoff[u + 1]; q++) {
         const uint32_t j = sh.ulist[q];
@@ -513,8 +512,7 @@ __device__ inline uint32_t filter_bit(uint32_t u, uint32_t c, uint32_t fl)
 
 // Is chunk c in flight on an out-link of unicast switch u at time t?  The
 // filter answers "no" for most chunks without walking the links.
-template <class S>
-__device__ inline bool sent_by(const S &sh, uint32_t u, uint32_t c, uint32_t t, uint32_t fl)
+__device__ inline bool sent_by(const SwShared &sh, uint32_t u, uint32_t c, uint32_t t, uint32_t fl)
 {
     const uint32_t b = filter_bit(u, c, fl);
     return ((sh.filt[b >> 5] >> (b & 31u)) & 1u) && sending(sh, u, c, t);
@@ -1329,8 +1327,24 @@ __device__ void match_group(const Layout &ly, const Sizes &sz, const SwGroup &gp
 //   25.6 / 11.3  six polled entries per thread and one copy of the arrival
 //                code (27 KB of code with registers in scratch before, 21 KB
 //                and none now)
+//   24.2 / 10.8  offers and place look-ups dealt to the lanes
+//   24.5 / 11.0  what a unicast switch is sending in a hashed table (an
+//                All-Gather behind unicast switches took up to 5.6 times as
+//                long with the walk over the out-links)
 constexpr uint32_t GC_ITEMS = 6;  // polled entries per thread
 static_assert(GRP_MAX_ITEMS == GC_ITEMS * ST, "the host's limit");
+
+// What the unicast switches are sending: an open-addressed table of links by
+// (switch, chunk), filled at the window's start from the transfers in flight
+// and at the commits (a link sends at most once per window, so at most two
+// entries per link: the probes end at an empty slot).  A candidate that is
+// being sent is refused after a read or two.  The walk over the switch's
+// out-links behind a bit filter (k_match_sw's, whose lanes share a row's
+// candidates, where a lane has a link's to itself here) made a star of 60 NPUs
+// with 40 places, 8 chunks each, slower than bitmap rows: 654 ms and 569, 122
+// with the table; 60x8 rail cluster All-Gather, 16 places, 106 and 101, 29.6.
+constexpr uint32_t SENT_LOG2 = 11, SENT_SLOTS = 1u << SENT_LOG2;
+static_assert(SENT_SLOTS > 2 * SW_MAX_LINKS, "the probes of the sending table end");
 
 struct ColShared {
     uint64_t top[SW_MAX_LINKS];       // per link: which mid words (over 4,096 columns) or row words hold candidates
@@ -1351,7 +1365,7 @@ struct ColShared {
     uint16_t bpoff[SW_MAX_SW + 1], booff[SW_MAX_SW + 1];
     uint32_t bout[SW_MAX_LINKS];
     uint32_t pc[SW_MAX_POOL], pn[SW_MAX_POOL], occ[SW_MAX_SW];
-    uint32_t filt[SW_FILTER_WORDS];
+    alignas(16) uint32_t sent[SENT_SLOTS];  // by (unicast switch, chunk), hashed: 1 + the link that sends it, 0 empty
     uint16_t uwin[SW_MAX_LINKS];
     uint32_t ucnt[SW_MAX_SW];
     uint32_t hd[SW_HASH_WORDS], hu[SW_HASH_WORDS], dpk[SW_MAX_LINKS / 32];
@@ -1383,6 +1397,25 @@ __device__ __forceinline__ uint32_t nth_bit(uint64_t f, uint32_t x)
         }
     }
     return at;
+}
+
+__device__ __forceinline__ uint32_t sent_slot(uint32_t u, uint32_t c)
+{
+    return ((c ^ (u * 0x9E3779B9u)) * 2654435761u) >> (32u - SENT_LOG2);
+}
+
+// link i of unicast switch u sends chunk c
+__device__ inline void sent_add(ColShared &sh, uint32_t u, uint32_t c, uint32_t i)
+{
+    for (uint32_t s = sent_slot(u, c); atomicCAS(&sh.sent[s], 0u, i + 1u) != 0u;) s = (s + 1u) & (SENT_SLOTS - 1u);
+}
+
+// Is chunk c in flight on an out-link of unicast switch u at time t?
+__device__ inline bool sent_now(const ColShared &sh, uint32_t u, uint32_t c, uint32_t t)
+{
+    for (uint32_t s = sent_slot(u, c), j; (j = sh.sent[s]) != 0u; s = (s + 1u) & (SENT_SLOTS - 1u))
+        if (sh.infl[j - 1u] == c && sh.luni[j - 1u] == u && sh.busy[j - 1u] > t) return true;
+    return false;
 }
 
 // The group's static tables and starting state; a thread per link (nL <= ST).
@@ -1554,8 +1587,6 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
 #pragma unroll
     for (uint32_t k = 0; k < GC_ITEMS; k++) item[k] = tid + k * ST < tot ? sh.item[tid + k * ST] : NONE32;
     const uint32_t nk = (tot + ST - 1) / ST;
-    const uint32_t fl = filter_log2(gp.nU);
-    const uint32_t nfw = gp.nU ? (gp.nU << fl) >> 5 : 0u;
     const unsigned long long max_windows = ctl->needs_total + 2ull;
     unsigned long long remaining = ctl->needs_total, k = 0;
     SwAcc acc = {NONE32, 0u, 0u, 0u, 0ull, 0ull, 0ull};
@@ -1576,9 +1607,10 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
         uint32_t ra[GC_ITEMS];
 #pragma unroll
         for (uint32_t q = 0; q < GC_ITEMS; q++) ra[q] = ea[q] >= t0 && (uint64_t)ea[q] < t1 ? ea[q] : NONE32;
-        // the sending filter, from the transfers in flight at t0 (a superset
-        // at every later event of the window); the round tables start empty
-        for (uint32_t x = tid; x < nfw; x += ST) sh.filt[x] = 0u;
+        // the sending table, from the transfers in flight at t0; the round
+        // tables start empty
+        if (gp.nU)
+            for (uint32_t x = tid; x < SENT_SLOTS / 4u; x += ST) reinterpret_cast<uint4 *>(sh.sent)[x] = make_uint4(0, 0, 0, 0);
         for (uint32_t x = tid; x < SW_HASH_WORDS; x += ST) {
             sh.hd[x] = 0u;
             sh.hu[x] = 0u;
@@ -1586,10 +1618,7 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
         for (uint32_t x = tid; x < SW_MAX_LINKS / 32; x += ST) sh.dpk[x] = 0u;
         if (tid < 2) sh.rflag[tid] = 0u;
         __syncthreads();
-        if (u != NONE32 && sh.infl[tid] != NONE32 && sh.busy[tid] > t0) {
-            const uint32_t b = filter_bit(u, sh.infl[tid], fl);
-            atomicOr(&sh.filt[b >> 5], 1u << (b & 31u));
-        }
+        if (u != NONE32 && sh.infl[tid] != NONE32 && sh.busy[tid] > t0) sent_add(sh, u, sh.infl[tid], tid);
         uint32_t par = 0;
         int64_t t_prev = k == 0 ? -1 : (int64_t)t0 - 1;
         for (;;) {
@@ -1709,7 +1738,7 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
                             for (uint64_t y = x; y && pk == NONE32; y &= y - 1) {
                                 const uint32_t cc = w * 64u + (uint32_t)__builtin_ctzll(y);
                                 const uint32_t r = rank[cc] & NBR_RANK_MASK;
-                                if (u != NONE32 && sent_by(sh, u, r, t, fl)) continue;
+                                if (u != NONE32 && sent_now(sh, u, r, t)) continue;
                                 pk = r;
                                 col = cc;
                                 px = x;
@@ -1793,10 +1822,7 @@ __global__ void __launch_bounds__(ST) k_match_cols(Layout ly, Sizes sz)
                     const uint32_t e32 = end > 0xFFFFFFFFull ? NONE32 - 1u : (uint32_t)end;
                     sh.busy[tid] = e32;
                     sh.infl[tid] = pk;
-                    if (u != NONE32) {
-                        const uint32_t fb = filter_bit(u, pk, fl);
-                        atomicOr(&sh.filt[fb >> 5], 1u << (fb & 31u));
-                    }
+                    if (u != NONE32) sent_add(sh, u, pk, tid);
                     acc.cstar = max(acc.cstar, e32);
                     logged = false;
                     acc.sent++;
