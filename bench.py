@@ -34,6 +34,9 @@ PEAK_HBM_GBPS = 8000.0
 # record and one atomic).
 BYTES_PER_SCANNED_WORD = 16
 BYTES_PER_MATCH = 96
+# pccl_get_kernel's names and the matching kernels they stand for
+KERNEL_SYMBOLS = {"windowed": "k_match", "neighbour": "k_match_nbr", "switch rows": "k_match_sw",
+                  "switch columns": "k_match_cols"}
 
 
 COUNTERS = os.path.join(ROOT, "profiles", "k_match_nbr_switch2level_512_a2a_hbm_counters.md")
@@ -191,10 +194,7 @@ def switch_model(args, W, Synthesizer, torch):
         torch.cuda.synchronize()
         step_s = (time.perf_counter() - t0) / steps
         st, pr = syn.stats(), syn.profile()
-        # the switch-group kernel (over columns where a buffer limit binds),
-        # or the plain windowed one when the device found that the
-        # no-multicast rule cannot act
-        kern = ("k_match_cols" if buf else "k_match_sw") if syn.matcher() == "switch" else "k_match"
+        kern = KERNEL_SYMBOLS[syn.kernel()[0]]
         kms = sum(match_ms) / len(match_ms)
         alg = BYTES_PER_SCANNED_WORD * pr["scan_words"] + BYTES_PER_MATCH * syn.n_sends
         pt = {"workload": wl.name, "npus": nn * pn, "buffer_chunks": buf, "unicast": bool(uni),
@@ -302,10 +302,11 @@ def main():
     avg_match_s = sum(match_ms) / len(match_ms) / 1e3
     alg_bytes = BYTES_PER_SCANNED_WORD * prof["scan_words"] + BYTES_PER_MATCH * n
     achieved = alg_bytes / avg_match_s / 1e9
-    traffic = measured_traffic(args.config)
+    kern = KERNEL_SYMBOLS[syn.kernel()[0]]
+    traffic = measured_traffic(args.config) if kern == "k_match_nbr" else None
     roofline = {"bound": "hbm", "achieved": round(achieved, 3), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM_GBPS, 6), "traffic": traffic,
-                "kernel": "k_match_nbr", "kernel_ms": round(avg_match_s * 1e3, 4),
+                "kernel": kern, "kernel_ms": round(avg_match_s * 1e3, 4),
                 "alg_bytes_per_launch": alg_bytes, "scan_words": prof["scan_words"], "matches": n,
                 # the counter bytes (FETCH_SIZE + WRITE_SIZE, calibrated) over the same
                 # kernel time: HBM GB/s as the hardware counts it, MALL hits included

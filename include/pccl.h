@@ -357,6 +357,16 @@ pccl_status pccl_get_stats(pccl_ctx *ctx, uint64_t *events, uint64_t *rounds,
 pccl_status pccl_get_matcher(pccl_ctx *ctx, uint32_t *kernel);
 
 /*
+ * The same in full: *kernel = 0 for the windowed kernel, 1 for the
+ * neighbour-stepped kernel (both report 0 above), 2 for the switch-group
+ * kernel over bitmap rows, 3 for the one over columns (both report 1 above);
+ * *pruned = 1 when the setup dropped the polled entries that no needed chunk
+ * can come through.  The schedule does not depend on it.  Either pointer may
+ * be NULL.  PCCL_ESTATE before a schedule exists.
+ */
+pccl_status pccl_get_kernel(pccl_ctx *ctx, uint32_t *kernel, uint32_t *pruned);
+
+/*
  * Setup products of the last synthesize call, copied to host arrays (any may
  * be NULL): link_time_ns[L] = alpha + ceil(m / bw); chunk_src[C] (source NPU
  * or 0xFFFFFFFF when the chunk is unused); chunk_dist[C] (max shortest-path

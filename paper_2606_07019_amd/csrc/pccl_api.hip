@@ -1717,6 +1717,17 @@ pccl_status pccl_get_matcher(pccl_ctx *c, uint32_t *kernel)
     GUARD_END(c)
 }
 
+pccl_status pccl_get_kernel(pccl_ctx *c, uint32_t *kernel, uint32_t *pruned)
+{
+    if (!c) return PCCL_EINVAL;
+    GUARD_BEGIN
+    if (!result_alive(c)) return fail(c, PCCL_ESTATE, c->have_result ? "the static scratch holding this schedule was reused" : "no schedule");
+    if (kernel) *kernel = c->ran_sw ? (c->sw_cols ? 3u : 2u) : (c->nbr ? 1u : 0u);
+    if (pruned) *pruned = c->nbr_prune ? 1u : 0u;
+    return PCCL_OK;
+    GUARD_END(c)
+}
+
 pccl_status pccl_get_stats(pccl_ctx *c, uint64_t *events, uint64_t *rounds, uint64_t *clashes, uint64_t *windows)
 {
     if (!c) return PCCL_EINVAL;

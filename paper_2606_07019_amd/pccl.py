@@ -65,6 +65,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "pccl_get_path": ([P, U32, U32, P, P, U32, ctypes.POINTER(U32)], I),
         "pccl_export_program": ([P, P, U64, P, U64, ctypes.POINTER(U64), ctypes.POINTER(U64)], I),
         "pccl_get_matcher": ([P, ctypes.POINTER(U32)], I),
+        "pccl_get_kernel": ([P, ctypes.POINTER(U32), ctypes.POINTER(U32)], I),
         "pccl_get_stats": ([P, ctypes.POINTER(U64), ctypes.POINTER(U64), ctypes.POINTER(U64),
                             ctypes.POINTER(U64)], I),
         "pccl_get_setup": ([P, P, P, P, P], I),
@@ -221,6 +222,16 @@ def pccl_get_matcher(h) -> str:
     return "switch" if v.value else "plain"
 
 
+KERNELS = ("windowed", "neighbour", "switch rows", "switch columns")
+
+
+def pccl_get_kernel(h):
+    """(name in KERNELS of the kernel that made the last schedule, polled entries pruned)"""
+    k, p = ctypes.c_uint32(), ctypes.c_uint32()
+    _check(h, load_library().pccl_get_kernel(h, ctypes.byref(k), ctypes.byref(p)))
+    return KERNELS[k.value], bool(p.value)
+
+
 def pccl_get_link_usage(h, n_links: int, n_bins: int = 20):
     """(busy_ns per link, busy link-time per time bin, bin width in ns)."""
     busy = np.zeros(max(n_links, 1), np.uint64)
@@ -310,6 +321,9 @@ class Synthesizer:
 
     def matcher(self) -> str:
         return pccl_get_matcher(self.h)
+
+    def kernel(self):
+        return pccl_get_kernel(self.h)
 
     def link_usage(self, n_bins: int = 20):
         return pccl_get_link_usage(self.h, self.topo.n_links, n_bins)

@@ -1,6 +1,6 @@
 """GPU parity of the neighbour-stepped matching kernel where its dispatch and
 its tables change: whole schedules and statistics against the CPU oracle
-(integers, so equality is exact)."""
+(integers, so equality is exact), and the kernel that ran."""
 
 import numpy as np
 import pytest
@@ -65,7 +65,7 @@ CASES = {
     "ring 5 x 13": lambda: W.Workload("r5", W.ring(5), W.all_gather(5, range(5), 13, 1 << 14), 8),
     "ring 8 x 512": lambda: W.Workload("r8", W.ring(8), W.all_gather(8, range(8), 512, 1 << 14), 9),
     "ring 8 x 520": lambda: W.Workload("r8b", W.ring(8), W.all_gather(8, range(8), 520, 1 << 14), 10),
-    # link times a factor 64 and 65 apart
+    # link times a factor of 9 apart, and of more
     "slow link 9": lambda: _generic("slow9", _slow_link(9), 60, 100, 4, 21),
     "slow link 10": lambda: _generic("slow10", _slow_link(10), 60, 100, 4, 22),
     "slow link 64": lambda: _generic("slow64", _slow_link(64), 60, 100, 4, 11),
@@ -79,6 +79,11 @@ CASES = {
     # lane and read by another
     "star 64 x 2": lambda: W.Workload("star64", W.star(64), W.a2a_k_bitmaps(64, 2, 8192), 23),
 }
+
+
+# the kernel expected on each side of its rule, and where polled entries are pruned
+WINDOWED = {"slow link 10", "slow link 64", "slow link 65", "mesh 41x25"}
+PRUNED = {"complete 10", "digraph 40 degree 9", "digraph 90 degree 9", "rail 12x8 generic", "rail 13x8", "rail 64x4"}
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -96,5 +101,6 @@ def test_neighbour_stepped_parity(name):
             assert s.collective_time == ref.collective_time
             st = s.stats()
             assert [st[k] for k in ("events", "rounds", "clashes")] == [ref.stats[k] for k in ("events", "rounds", "clashes")]
+            assert s.kernel() == ("windowed" if name in WINDOWED else "neighbour", name in PRUNED)
     finally:
         s.close()

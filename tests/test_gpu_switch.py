@@ -20,16 +20,16 @@ def _run_gpu(wl):
         try:
             s.synthesize()
         except PcclError as e:
-            return e.name, None, None, None
-        return "PCCL_OK", s.schedule(), s.collective_time, s.stats()
+            return e.name, None, None, None, None
+        return "PCCL_OK", s.schedule(), s.collective_time, s.stats(), s.kernel()
     finally:
         s.close()
 
 
-def _compare(wl, label):
+def _compare(wl, label, kernel=None):
     print(f"[switch parity] {label}: {wl.name}", flush=True)
     ref = O.run_workload(wl)
-    status, sched, ct, st = _run_gpu(wl)
+    status, sched, ct, st, ran = _run_gpu(wl)
     if ref.status != 0:
         assert status == "PCCL_" + ref.status_name, (status, ref.message)
         return
@@ -39,6 +39,7 @@ def _compare(wl, label):
     assert st["events"] == ref.stats["events"]
     assert st["rounds"] == ref.stats["rounds"]
     assert st["clashes"] == ref.stats["clashes"]
+    assert kernel is None or ran == kernel
 
 
 @pytest.mark.parametrize("name", sorted(HAND_WORKLOADS))
@@ -109,7 +110,7 @@ def test_model_without_limits_uses_the_plain_matcher():
     ref = O.run_workload(wl)
     for buf in (0, wl.coll.n_chunks, wl.coll.n_chunks + 7):
         t = W.with_switch_model(wl.topo, buf, 0)
-        status, sched, ct, _ = _run_gpu(W.Workload(wl.name, t, wl.coll, wl.tie_seed))
+        status, sched, ct, _, _ = _run_gpu(W.Workload(wl.name, t, wl.coll, wl.tie_seed))
         assert status == "PCCL_OK" and ct == ref.collective_time
         np.testing.assert_array_equal(sched, ref.sends)
 
@@ -127,7 +128,7 @@ def test_full_size_unicast_rails_match_the_plain_oracle_schedule():
     with open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "config4.json")) as f:
         g = json.load(f)
     wl = W.switch2level_model(64, 8, 0, True)
-    status, sched, ct, st = _run_gpu(wl)
+    status, sched, ct, st, _ = _run_gpu(wl)
     assert status == "PCCL_OK"
     assert len(sched) == g["n_sends"] and ct == g["collective_time_ns"]
     idx = np.array(g["sample_index"], dtype=np.int64)
@@ -145,7 +146,7 @@ def test_full_size_buffered_rails_invariants():
     from tests.invariants import check_copy_schedule, check_switch_model
     print("[switch fullsize] switch2level_512_a2a_b64_u1", flush=True)
     wl = W.switch2level_model(64, 8, 64, True)
-    status, sched, ct, _ = _run_gpu(wl)
+    status, sched, ct, _, _ = _run_gpu(wl)
     assert status == "PCCL_OK"
     # every chunk crosses the same relays as without limits (the needs are
     # set before matching): the plain transfer count
@@ -170,7 +171,7 @@ def test_full_size_switch_model_digest(nodes, per_node, buffer, unicast):
     with open(path) as f:
         g = json.load(f)
     print(f"[switch fullsize] {wl.name}", flush=True)
-    status, sched, ct, st = _run_gpu(wl)
+    status, sched, ct, st, _ = _run_gpu(wl)
     assert status == "PCCL_OK"
     assert len(sched) == g["n_sends"] and ct == g["collective_time_ns"]
     idx = np.array(g["sample_index"], dtype=np.int64)
