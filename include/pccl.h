@@ -215,7 +215,9 @@ pccl_status pccl_workspace_bytes(pccl_ctx *ctx, uint64_t max_sends, size_t *out_
  * memory of its own (a context holds pinned host memory: the copies of the
  * inputs and of its small tables, and a 2 x 160-byte block for reading the
  * device's counters).  The workspace must not be used by the caller while a
- * synthesize call runs.  PCCL_ENOMEM if `bytes` is too small.
+ * synthesize call runs.  A smaller one that still holds the layout of the
+ * other matching kernels is taken too and runs those (pccl_get_kernel): the
+ * same schedule, later.  PCCL_ENOMEM if `bytes` is too small for either.
  */
 pccl_status pccl_set_workspace(pccl_ctx *ctx, void *device_ptr, size_t bytes,
                                uint64_t max_sends, void *hip_stream);

@@ -25,6 +25,31 @@ using namespace pccl;
 // the array's name.
 static __device__ __align__(256) unsigned char scratch[PCCL_STATIC_SCRATCH_BYTES];
 
+// One way to run the matching: the kernel, its launch shape, the deal of
+// destinations and switch groups to its waves and workgroups; the workspace
+// layout follows from it.
+struct Plan {
+    bool ok = false;
+    bool nbr = false;              // the neighbour-stepped kernel
+    bool sw_cols = false;          // the switch groups are matched over columns
+    bool prune = false;            // the setup drops polled entries no needed chunk can come through
+    size_t nbr_lds = 0;            // neighbour-stepped kernel: LDS per workgroup,
+    uint32_t nbr_spread = 1;       // every how many workgroups of the launch one holds devices
+    int grid = 0, wpb = 0;         // workgroups, waves per workgroup
+    bool mirror = false;           // windowed kernel: keeps each destination's needs row in LDS,
+    bool resident = true;          // one destination (or part) per wave for the whole run
+    std::vector<uint32_t> split;   // split destinations, each taking one workgroup (heaviest first)
+    std::vector<std::vector<uint32_t>> split_cuts;  // their parts: first in-link of each part, then the in-degree
+    uint32_t alone = 0;            // heaviest other destinations dealt to a workgroup of their own
+    std::vector<uint32_t> wave_dest;  // destination of (pass, wave) in the matching kernel
+    std::vector<uint32_t> wave_part;  // its part when the destination is split over a workgroup's waves
+    int sw_grid = 0;               // workgroups of the switch-group kernel
+    std::vector<uint32_t> sw_deal; // its groups by workgroup (the tables' blk and blk_list)
+};
+// its arrays in the pinned image, behind the common ones: wave_dest,
+// wave_part, and sw_deal where the tables hold the other plan's
+constexpr int PLAN_PARTS = 3;
+
 struct pccl_ctx {
     int device = 0;
     uint64_t seed = 0;
@@ -40,12 +65,6 @@ struct pccl_ctx {
     std::vector<uint32_t> out_off, out_dst, slot_out;  // out-links by device: their destinations; a slot's index among them
     uint32_t max_out = 0;                  // most out-links of one device
     uint32_t max_poll = 0, max_in = 0;     // most polled entries / in-links of one device
-    std::vector<uint32_t> wave_dest;  // destination of (pass, wave) in the matching kernel
-    std::vector<uint32_t> wave_part;  // its part when the destination is split over a workgroup's waves
-    std::vector<uint32_t> split;      // split destinations, each taking one workgroup (heaviest first)
-    std::vector<std::vector<uint32_t>> split_cuts;  // their parts: first in-link of each part, then the in-degree
-    bool resident = true;             // one destination (or part) per wave for the whole run
-    uint32_t alone = 0;               // heaviest other destinations dealt to a workgroup of their own
     // collective; the pre/post bitmaps and chunk groups are copied into
     // `pin_in` (pinned host memory: pre, then post, then the group ids)
     uint32_t C = 0, G = 0;
@@ -70,24 +89,22 @@ struct pccl_ctx {
     uint32_t sw_nuni = 0;          // unicast switches with out-links
     bool ran_sw = false;           // the last synthesis ran the switch-group kernel
     uint32_t sw_groups = 0, sw_pool = 0, sw_nbt = 0;
-    int sw_grid = 0;
-    bool sw_cols = false;          // the switch groups are matched over columns
     std::vector<uint32_t> sw_mem, sw_mem_off;  // the groups' devices
-    // plan (made once per collective and switch model, before any workspace)
+    // plans (made once per collective and switch model, before any workspace):
+    // over columns, where some rule takes that, and over bitmap rows; the
+    // first whose layout fits the workspace runs
+    Plan plans[2];
+    const Plan *use = &plans[1];   // the bound workspace's
+    const Plan &preferred() const { return plans[0].ok ? plans[0] : plans[1]; }
     bool planned = false;
     uint64_t plan_gen = 0;         // changes with every plan (static scratch ownership)
     // pinned host image of the small per-topology arrays the kernels read
     // (link and slot tables, destination deal, group masks, switch tables),
-    // built by the plan; IMG_PARTS pieces at img_off[k], img_len[k] bytes
+    // built with the plans; IMG_PARTS pieces at img_off[k], img_len[k] bytes
+    // (the common ones, then PLAN_PARTS of each plan)
     char *pin_img = nullptr;
     size_t pin_img_cap = 0;
-    size_t img_off[20] = {}, img_len[20] = {};
-    // neighbour-stepped matching kernel: chosen by the plan (nbr_ok: not
-    // ruled out by a workspace only the windowed kernel fits in)
-    bool nbr_ok = true, nbr = false;
-    size_t nbr_lds = 0;            // LDS per workgroup
-    bool nbr_prune = false;        // the setup drops polled entries no needed chunk can come through
-    uint32_t nbr_spread = 1;       // every how many workgroups of the launch one holds devices
+    size_t img_off[18 + 2 * PLAN_PARTS] = {}, img_len[18 + 2 * PLAN_PARTS] = {};
     uint64_t serial = 0;           // unique per context
     uint64_t static_call = 0;      // the static-scratch call whose result this context holds
     // workspace
@@ -98,9 +115,6 @@ struct pccl_ctx {
     hipStream_t stream = nullptr;
     Layout ly{};
     Sizes sz{};
-    int grid = 0, wpb = 0;  // matching kernel: workgroups, waves per workgroup
-
-    bool mirror = false;    // matching kernel keeps each destination's needs row in LDS
     // stage timing; ev[1] also marks that the setup's counts have reached `pin`
     // (events and the pinned block are made by pccl_create, so that a
     // synthesize call allocates nothing)
@@ -166,7 +180,7 @@ struct Carver {
     }
 };
 
-void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, size_t &total)
+void carve(const pccl_ctx *c, const Plan &pl, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, size_t &total)
 {
     sz.N = c->N;
     sz.S = c->S;
@@ -179,12 +193,12 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
     sz.WN = words(c->N);
     sz.max_sends = max_sends;
     sz.tmin = c->tmin;
-    sz.resident = c->resident ? 1u : 0u;
+    sz.resident = pl.resident ? 1u : 0u;
     sz.sw_gate = c->sw_active && c->sw_gate ? 1u : 0u;
     sz.sw_nbt = c->sw_active ? c->sw_nbt : 0u;
-    const bool cols = c->nbr || c->sw_cols;
+    const bool cols = pl.nbr || pl.sw_cols;
     sz.cols = cols ? 1u : 0u;
-    sz.sw_cols = c->sw_cols ? 1u : 0u;
+    sz.sw_cols = pl.sw_cols ? 1u : 0u;
     const uint64_t hb = (uint64_t)sz.D * sz.Wp * sizeof(uint64_t);
     sz.hbytes = hb < (1ull << 31) ? (uint32_t)hb : 0u;
     const uint64_t nsort = std::max<uint64_t>(c->C, max_sends);
@@ -248,8 +262,8 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
         ly.dest_cols = cv.take<uint32_t>(D);
         ly.poll_off = cv.take<uint32_t>(D + 1);
         ly.poll = cv.take<uint32_t>(c->poll.size());
-        sz.nbr_prune = c->nbr_prune ? 1u : 0u;
-        if (c->nbr_prune) {
+        sz.nbr_prune = pl.prune ? 1u : 0u;
+        if (pl.prune) {
             ly.out_off = cv.take<uint32_t>(D + 1);
             ly.out_dst = cv.take<uint32_t>(L);
             ly.slot_out = cv.take<uint32_t>(L);
@@ -259,7 +273,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
             ly.poll_cnt = cv.take<uint32_t>(D);
             ly.poll_use = cv.take<uint32_t>(c->poll.size() + L);
         }
-        if (c->sw_cols) ly.xslot = cv.take<uint64_t>(2ull * MAX_MATCH_GRID * XSLOT_WORDS);
+        if (pl.sw_cols) ly.xslot = cv.take<uint64_t>(2ull * MAX_MATCH_GRID * XSLOT_WORDS);
     } else {
         ly.holds = cv.take<uint64_t>(D * sz.Wp);
         ly.busy = cv.take<uint32_t>(L);
@@ -283,7 +297,7 @@ void carve(pccl_ctx *c, char *base, uint64_t max_sends, Layout &ly, Sizes &sz, s
         ly.sw.pool_c = cv.take<uint32_t>(c->sw_pool);
         ly.sw.pool_n = cv.take<uint32_t>(c->sw_pool);
         ly.sw.occ = cv.take<uint32_t>(c->sw_nbt);
-        if (c->sw_cols) ly.sw.amask = cv.take<uint64_t>((uint64_t)c->sw_nbt * C);
+        if (pl.sw_cols) ly.sw.amask = cv.take<uint64_t>((uint64_t)c->sw_nbt * C);
         else ly.sw.acnt = cv.take<uint32_t>((uint64_t)c->sw_nbt * std::max<uint64_t>(C, 1));
     }
     total = (cv.off + 255) & ~size_t(255);
@@ -517,14 +531,16 @@ pccl_status build_switch_tables(pccl_ctx *c)
 }
 
 // Switch groups to workgroups: heaviest first, dealt round-robin.
-pccl_status deal_switch_groups(pccl_ctx *c)
+pccl_status deal_switch_groups(pccl_ctx *c, Plan &pl)
 {
-    const uint32_t G = c->sw_groups, nb = (uint32_t)c->sw_grid;
+    const uint32_t G = c->sw_groups, nb = (uint32_t)pl.sw_grid;
     std::vector<uint32_t> byweight(G);
     std::iota(byweight.begin(), byweight.end(), 0u);
     std::stable_sort(byweight.begin(), byweight.end(),
                      [&](uint32_t a, uint32_t b) { return c->sw_links[a] > c->sw_links[b]; });
-    uint32_t *blk = c->swt.data() + c->swo[1], *list = c->swt.data() + c->swo[2];
+    // (laid out as in the tables)
+    pl.sw_deal.assign(c->swo[3] - c->swo[1], 0u);
+    uint32_t *blk = pl.sw_deal.data(), *list = blk + (c->swo[2] - c->swo[1]);
     uint32_t k = 0;
     for (uint32_t b = 0; b < nb; b++) {
         blk[b] = k;
@@ -557,11 +573,11 @@ void deal_order(const pccl_ctx *c, std::vector<uint32_t> &v)
 // workgroups before filling any workgroup's second wave, so that heavy
 // destinations do not share a compute unit and its memory pipeline.  Pass r
 // of wave w handles entry r * nwaves + w.
-void deal_destinations(pccl_ctx *c)
+void deal_destinations(const pccl_ctx *c, Plan &pl)
 {
-    const uint32_t D = c->D, nb = (uint32_t)c->grid, wpb = (uint32_t)c->wpb, nw = nb * wpb;
+    const uint32_t D = c->D, nb = (uint32_t)pl.grid, wpb = (uint32_t)pl.wpb, nw = nb * wpb;
     std::vector<uint8_t> is_split(D, 0);
-    for (uint32_t d : c->split) is_split[d] = 1;
+    for (uint32_t d : pl.split) is_split[d] = 1;
     std::vector<uint32_t> byweight;
     byweight.reserve(D);
     for (uint32_t v = 0; v < D; v++)
@@ -569,26 +585,26 @@ void deal_destinations(pccl_ctx *c)
     deal_order(c, byweight);
     // the `alone` heaviest unsplit destinations take wave 0 of the next
     // workgroups (one pass, by construction of the grid)
-    const uint32_t hs = (uint32_t)c->split.size(), ha = c->alone, h = hs + ha;
+    const uint32_t hs = (uint32_t)pl.split.size(), ha = pl.alone, h = hs + ha;
     const uint32_t nb2 = nb - h, rest = (uint32_t)byweight.size() - ha;
     const uint32_t n2 = nb2 * wpb;
     const uint32_t passes = n2 ? std::max(1u, (rest + n2 - 1) / n2) : 1u;
-    c->wave_dest.assign((size_t)passes * nw, NONE32);
-    c->wave_part.assign((size_t)passes * nw, 0u);
+    pl.wave_dest.assign((size_t)passes * nw, NONE32);
+    pl.wave_part.assign((size_t)passes * nw, 0u);
     for (uint32_t i = 0; i < hs; i++) {
-        const uint32_t d = c->split[i];
-        const std::vector<uint32_t> &cut = c->split_cuts[i];  // cut[p] = first in-link of part p; cut.back() = in-degree
+        const uint32_t d = pl.split[i];
+        const std::vector<uint32_t> &cut = pl.split_cuts[i];  // cut[p] = first in-link of part p; cut.back() = in-degree
         const uint32_t parts = (uint32_t)cut.size() - 1;
         for (uint32_t p = 0; p < wpb; p++) {
             const uint32_t first = p < parts ? cut[p] : cut.back(), cnt = p < parts ? cut[p + 1] - cut[p] : 0u;
-            c->wave_dest[(size_t)i * wpb + p] = d;
-            c->wave_part[(size_t)i * wpb + p] = (wpb << 24) | (p << 16) | (first << 8) | cnt;
+            pl.wave_dest[(size_t)i * wpb + p] = d;
+            pl.wave_part[(size_t)i * wpb + p] = (wpb << 24) | (p << 16) | (first << 8) | cnt;
         }
     }
-    for (uint32_t i = 0; i < ha; i++) c->wave_dest[(size_t)(hs + i) * wpb] = byweight[i];
+    for (uint32_t i = 0; i < ha; i++) pl.wave_dest[(size_t)(hs + i) * wpb] = byweight[i];
     for (uint32_t q = 0; q < rest; q++) {
         const uint32_t r = q / n2, j = q % n2, w = (h + j % nb2) * wpb + j / nb2;
-        c->wave_dest[(size_t)r * nw + w] = byweight[ha + q];
+        pl.wave_dest[(size_t)r * nw + w] = byweight[ha + q];
     }
 }
 
@@ -630,7 +646,7 @@ pccl_status ensure_pinned(pccl_ctx *c, char **buf, size_t *cap, size_t bytes)
     return PCCL_OK;
 }
 
-constexpr int IMG_PARTS = 20;
+constexpr int IMG_COMMON = 18, IMG_PARTS = IMG_COMMON + 2 * PLAN_PARTS;
 
 // Parts of destination d for a split over the waves of a workgroup:
 // consecutive in-links, at most `target` links and MAX_PAIRS arrival pairs
@@ -738,10 +754,9 @@ void build_poll(pccl_ctx *c)
 // devices, three workgroups of three waves) a wait on a neighbour's entry ran
 // into the spin limit, which reading has not explained; such networks stay
 // with the windowed kernel.
-bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
+bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
 {
-    c->nbr_prune = false;
-    if (!c->nbr_ok || c->sw_active || c->D == 0 || c->L == 0 || c->C > NBR_MAX_CHUNKS) return false;
+    if (c->sw_active || c->D == 0 || c->L == 0 || c->C > NBR_MAX_CHUNKS) return false;
     uint32_t tmax = 0;
     for (uint32_t t : c->T) tmax = std::max(tmax, t);
     if (tmax / NBR_MAX_RATIO > c->tmin) return false;
@@ -795,18 +810,15 @@ bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
         break;
     }
     if (!spread) return false;
-    c->nbr_spread = spread;
+    pl.nbr_spread = spread;
     // worth its setup (0.03-0.06 ms) where some device polls several entries
     // per lane; the relations are masks over a device's out-links
-    c->nbr_prune = c->max_poll > 64 && c->max_out <= 64;
-    c->wpb = (int)w;
-    c->grid = (int)grid;
-    c->alone = alone;
-    c->resident = true;
-    c->mirror = false;
-    c->nbr_lds = lds_cu;
-    c->split.clear();
-    c->split_cuts.clear();
+    pl.prune = c->max_poll > 64 && c->max_out <= 64;
+    pl.wpb = (int)w;
+    pl.grid = (int)grid;
+    pl.alone = alone;
+    pl.nbr_lds = lds_cu;
+    pl.nbr = true;
     return true;
 }
 
@@ -819,9 +831,9 @@ bool plan_nbr(pccl_ctx *c, size_t lds_cu, uint32_t n_heavy)
 // rows is queued beside the group kernel and both read one layout.  Within
 // these bounds the columns were the faster side wherever both were measured
 // (rail clusters of 128 and 512 NPUs: 18.8 and 11.3 ms, 57.5 and 25.6).
-bool plan_switch_columns(pccl_ctx *c)
+bool plan_switch_columns(pccl_ctx *c, Plan &pl)
 {
-    if (!c->nbr_ok || !c->sw_active || c->sw_gate || c->C == 0 || c->C > NBR_MAX_CHUNKS) return false;
+    if (!c->sw_active || c->sw_gate || c->C == 0 || c->C > NBR_MAX_CHUNKS) return false;
     if ((int)c->sw_groups > std::min<int>(match_cols_max_grid(c->device), (int)MAX_MATCH_GRID)) return false;
     for (uint32_t d = 0; d < c->D; d++)
         if (c->in_off[d + 1] - c->in_off[d] > MAX_IN_LINKS) return false;
@@ -844,14 +856,17 @@ bool plan_switch_columns(pccl_ctx *c)
     for (uint32_t v : c->src) n_out[v]++;
     for (uint32_t i = 0; i < c->S; i++)
         if (limited(c->N + i) && n_out[c->N + i] > 64) return false;
-    c->nbr_prune = c->max_poll > 64 && c->max_out <= 64;
-    return c->pub_off[c->D] < (1u << 22);
+    if (c->pub_off[c->D] >= (1u << 22)) return false;
+    pl.prune = c->max_poll > 64 && c->max_out <= 64;
+    pl.sw_grid = (int)c->sw_groups;
+    pl.sw_cols = true;
+    return true;
 }
 
 // The windowed kernel's launch shape: waves per workgroup, needs rows in
 // LDS, grid, split and lone destinations.
-pccl_status plan_windowed(pccl_ctx *c, const std::vector<uint32_t> &must, uint32_t need_w, uint32_t n_heavy, bool desc_ok,
-                          size_t lds_cu, uint64_t Wp)
+pccl_status plan_windowed(pccl_ctx *c, Plan &pl, const std::vector<uint32_t> &must, uint32_t need_w, uint32_t n_heavy,
+                          bool desc_ok, size_t lds_cu, uint64_t Wp)
 {
     const uint32_t D1 = std::max<uint32_t>(c->D, 1);
     // the grid for w waves per workgroup with at most gmax workgroups:
@@ -887,7 +902,7 @@ pccl_status plan_windowed(pccl_ctx *c, const std::vector<uint32_t> &must, uint32
     wpb = std::max<int>(wpb, (int)need_w);
     // needs rows in LDS: with as many of those waves as leave room for one
     // row per wave, when every wave then owns one destination (or part)
-    c->mirror = false;
+    pl.mirror = false;
     const size_t lds_static = match_static_lds(), row_bytes = (size_t)Wp * sizeof(uint64_t);
     const bool spl = !must.empty();
     int grid = 0;
@@ -899,11 +914,11 @@ pccl_status plan_windowed(pccl_ctx *c, const std::vector<uint32_t> &must, uint32
         const int gmax = std::min<int>(match_max_grid(c->device, w, true, dyn, spl), (int)MAX_MATCH_GRID);
         if (gmax > 0 && shape((uint32_t)w, gmax, grid, resident, alone) && resident) {
             wpb = w;
-            c->mirror = true;
+            pl.mirror = true;
             break;
         }
     }
-    if (!c->mirror) {
+    if (!pl.mirror) {
         const int gmax = std::min<int>(match_max_grid(c->device, wpb, false, 0, spl), (int)MAX_MATCH_GRID);
         if (gmax <= 0) return fail(c, PCCL_EDEVICE, "matching kernel cannot be resident");
         if (!shape((uint32_t)wpb, gmax, grid, resident, alone))
@@ -911,29 +926,29 @@ pccl_status plan_windowed(pccl_ctx *c, const std::vector<uint32_t> &must, uint32
                         "matching kernel cannot keep a workgroup per such device and a wave per other device "
                         "resident (%d workgroups of %d waves at most)", must[0], need_w, gmax, wpb);
     }
-    c->wpb = wpb;
-    c->grid = grid;
-    c->resident = resident;
-    c->alone = alone;
-    c->split = must;
-    c->split_cuts.clear();
-    for (uint32_t d : c->split) {
+    pl.wpb = wpb;
+    pl.grid = grid;
+    pl.resident = resident;
+    pl.alone = alone;
+    pl.split = must;
+    for (uint32_t d : pl.split) {
         // the in-links spread evenly over the workgroup's waves (as few
         // parts as fit when the pairs do not allow that)
         const uint32_t n = c->in_off[d + 1] - c->in_off[d];
         std::vector<uint32_t> cut = cut_parts(c, d, (n + wpb - 1) / wpb);
         if (cut.size() - 1 > (size_t)wpb) cut = cut_parts(c, d, MAX_IN_LINKS);
-        c->split_cuts.push_back(cut);
+        pl.split_cuts.push_back(cut);
     }
     return PCCL_OK;
 }
 
 // Everything that depends on the topology, the collective and the switch
-// model but not on the workspace: the switch tables, the matching kernel's
-// launch shape (waves per workgroup, needs rows in LDS, grid), the deal of
-// destinations to waves and the pinned image of the small arrays the kernels
-// read.  Made when the collective or the switch model is set, so that binding
-// a workspace only carves it and a synthesize call allocates nothing.
+// model but not on the workspace: the switch tables, the plan over columns
+// where its rules take the collective, the plan over bitmap rows for
+// workspaces that hold only its layout (either may be the smaller one), and
+// the pinned image of the small arrays the kernels read.  Made when the
+// collective or the switch model is set, so that binding a workspace only
+// picks a plan and carves, and a synthesize call allocates nothing.
 pccl_status plan(pccl_ctx *c)
 {
     c->planned = false;
@@ -972,23 +987,32 @@ pccl_status plan(pccl_ctx *c)
     }
     int lds_cu = 0;
     HIP_OR_FAIL(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, c->device));
-    c->nbr_prune = c->sw_cols = false;
-    c->nbr = must.empty() && plan_nbr(c, (size_t)lds_cu, n_heavy);
-    if (!c->nbr) {
-        st = plan_windowed(c, must, need_w, n_heavy, desc_ok, (size_t)lds_cu, Wp);
-        if (st != PCCL_OK) return st;
-    }
-    deal_destinations(c);
+    Plan &over = c->plans[0], &rows = c->plans[1];
+    over = Plan{};
+    rows = Plan{};
+    c->use = &rows;
     if (c->sw_active) {
-        c->sw_cols = plan_switch_columns(c);
-        c->sw_grid = c->sw_cols ? (int)c->sw_groups
-                                : std::min<int>(std::min<int>(match_sw_max_grid(c->device), (int)MAX_MATCH_GRID),
-                                                (int)c->sw_groups);
-        if (c->sw_grid <= 0) return fail(c, PCCL_EDEVICE, "switch-model matching kernel cannot be resident");
-        st = deal_switch_groups(c);
-        if (st != PCCL_OK) return st;
+        over.ok = plan_switch_columns(c, over) && deal_switch_groups(c, over) == PCCL_OK;
+    } else {
+        over.ok = must.empty() && plan_nbr(c, over, (size_t)lds_cu, n_heavy);
+        if (over.ok) deal_destinations(c, over);
     }
-    const bool cols = c->nbr || c->sw_cols;
+    st = plan_windowed(c, rows, must, need_w, n_heavy, desc_ok, (size_t)lds_cu, Wp);
+    rows.ok = st == PCCL_OK;
+    // (with a switch model what the windowed kernel cannot take is refused)
+    if (!rows.ok && (c->sw_active || !over.ok)) return st;
+    if (rows.ok) deal_destinations(c, rows);
+    if (c->sw_active) {
+        rows.sw_grid = std::min<int>(std::min<int>(match_sw_max_grid(c->device), (int)MAX_MATCH_GRID), (int)c->sw_groups);
+        st = rows.sw_grid > 0 ? deal_switch_groups(c, rows)
+                              : fail(c, PCCL_EDEVICE, "switch-model matching kernel cannot be resident");
+        rows.ok = st == PCCL_OK;
+        if (!rows.ok && !over.ok) return st;
+        const Plan &first = c->preferred();
+        std::copy(first.sw_deal.begin(), first.sw_deal.end(), c->swt.begin() + c->swo[1]);
+    }
+    c->err.clear();
+    c->use = &c->preferred();
     // the pinned image, in the order upload() copies it
     const std::pair<const void *, size_t> parts[IMG_PARTS] = {
         {c->src.data(), 4ull * c->L},         {c->dst.data(), 4ull * c->L},
@@ -996,16 +1020,20 @@ pccl_status plan(pccl_ctx *c)
         {c->in_off.data(), 4ull * (c->D + 1)}, {c->slot_link.data(), 4ull * c->L},
         {c->slot_src.data(), 4ull * c->L},    {c->slot_time.data(), 4ull * c->L},
         {c->slot_cum.data(), 4ull * c->L},    {c->dest_pairs.data(), 4ull * c->D},
-        {c->wave_dest.data(), 4ull * c->wave_dest.size()},
-        {c->wave_part.data(), 4ull * c->wave_part.size()},
         {c->gmask.data(), 8ull * c->gmask.size()},
         {c->swt.data(), c->sw_active ? 4ull * c->swt.size() : 0ull},
-        {c->poll_off.data(), cols ? 4ull * c->poll_off.size() : 0ull},
-        {c->poll.data(), cols ? 4ull * c->poll.size() : 0ull},
-        {c->pub_off.data(), cols ? 4ull * c->pub_off.size() : 0ull},
-        {c->out_off.data(), c->nbr_prune ? 4ull * c->out_off.size() : 0ull},
-        {c->out_dst.data(), c->nbr_prune ? 4ull * c->out_dst.size() : 0ull},
-        {c->slot_out.data(), c->nbr_prune ? 4ull * c->slot_out.size() : 0ull}};
+        {c->poll_off.data(), over.ok ? 4ull * c->poll_off.size() : 0ull},
+        {c->poll.data(), over.ok ? 4ull * c->poll.size() : 0ull},
+        {c->pub_off.data(), over.ok ? 4ull * c->pub_off.size() : 0ull},
+        {c->out_off.data(), over.prune ? 4ull * c->out_off.size() : 0ull},
+        {c->out_dst.data(), over.prune ? 4ull * c->out_dst.size() : 0ull},
+        {c->slot_out.data(), over.prune ? 4ull * c->slot_out.size() : 0ull},
+        {over.wave_dest.data(), 4ull * over.wave_dest.size()},
+        {over.wave_part.data(), 4ull * over.wave_part.size()},
+        {nullptr, 0},
+        {rows.wave_dest.data(), 4ull * rows.wave_dest.size()},
+        {rows.wave_part.data(), 4ull * rows.wave_part.size()},
+        {rows.sw_deal.data(), over.ok ? 4ull * rows.sw_deal.size() : 0ull}};
     size_t total = 0;
     for (int k = 0; k < IMG_PARTS; k++) {
         c->img_off[k] = total;
@@ -1021,37 +1049,31 @@ pccl_status plan(pccl_ctx *c)
     return PCCL_OK;
 }
 
-// Points the context at a workspace: carves the layout for `max_sends`
-// transfers.  The inputs are copied in by the next synthesize call.
+// Points the context at a workspace: picks the first plan whose layout for
+// `max_sends` transfers fits and carves it.  The inputs are copied in by the
+// next synthesize call.
 pccl_status bind_workspace(pccl_ctx *c, char *ptr, size_t bytes, uint64_t ms, hipStream_t st, bool is_static)
 {
     Layout ly{};
     Sizes sz{};
-    size_t need = 0;
-    carve(c, nullptr, ms, ly, sz, need);
-    if (bytes < need && (c->nbr || c->sw_cols)) {
-        // the layout of the kernels over bitmap rows may still fit (it lacks
-        // the column and poll tables): plan for those instead
-        const bool nbr = c->nbr, sw_cols = c->sw_cols;
-        c->nbr = c->sw_cols = false;
-        size_t alt = 0;
-        carve(c, nullptr, ms, ly, sz, alt);
-        c->nbr = nbr;
-        c->sw_cols = sw_cols;
-        if (bytes >= alt) {
-            c->nbr_ok = false;
-            const pccl_status ps = plan(c);
-            if (ps != PCCL_OK) return ps;
-            need = alt;
-        }
+    size_t need = 0, least = ~size_t(0);
+    const Plan *pl = nullptr;
+    for (const Plan &p : c->plans) {
+        if (!p.ok) continue;
+        carve(c, p, nullptr, ms, ly, sz, need);
+        least = std::min(least, need);
+        if (need > bytes) continue;
+        pl = &p;
+        break;
     }
-    if (bytes < need) {
+    if (!pl) {
         if (is_static)
             return fail(c, PCCL_ENOMEM, "the library's static scratch holds %zu bytes, this collective needs %zu "
-                        "(pass a tighter max_sends, or bring a workspace with pccl_set_workspace)", bytes, need);
-        return fail(c, PCCL_ENOMEM, "workspace has %zu bytes, needs %zu", bytes, need);
+                        "(pass a tighter max_sends, or bring a workspace with pccl_set_workspace)", bytes, least);
+        return fail(c, PCCL_ENOMEM, "workspace has %zu bytes, needs %zu", bytes, least);
     }
-    carve(c, ptr, ms, c->ly, c->sz, need);
+    c->use = pl;
+    carve(c, *pl, ptr, ms, c->ly, c->sz, need);
     c->ws = ptr;
     c->ws_bytes = bytes;
     c->max_sends = ms;
@@ -1287,7 +1309,6 @@ pccl_status pccl_set_collective(pccl_ctx *c, uint32_t n_chunks, uint64_t chunk_b
     c->T.swap(T);
     c->slot_time.swap(slot_time);
     c->tmin = c->L ? tmin : 1;
-    c->nbr_ok = true;
     c->have_coll = true;
     return plan(c);
     GUARD_END(c)
@@ -1309,7 +1330,6 @@ pccl_status pccl_set_switch_model(pccl_ctx *c, uint32_t n_switches, const uint32
         any = any || c->sw_buf[i] || c->sw_uni[i];
     }
     c->sw_model = any;
-    c->nbr_ok = true;
     c->sw_built = c->sw_active = false;
     c->have_ws = c->uploaded = c->have_result = false;
     return c->have_coll ? plan(c) : PCCL_OK;
@@ -1325,7 +1345,7 @@ pccl_status pccl_workspace_bytes(pccl_ctx *c, uint64_t max_sends, size_t *out_by
     Layout ly{};
     Sizes sz{};
     size_t total = 0;
-    carve(c, nullptr, max_sends ? max_sends : safe_max_sends(c), ly, sz, total);
+    carve(c, c->preferred(), nullptr, max_sends ? max_sends : safe_max_sends(c), ly, sz, total);
     *out_bytes = total;
     return PCCL_OK;
     GUARD_END(c)
@@ -1352,13 +1372,17 @@ static pccl_status upload(pccl_ctx *c)
 {
     const Layout &ly = c->ly;
     hipStream_t st = c->stream;
-    void *dst[IMG_PARTS] = {ly.lsrc,      ly.ldst,     ly.ltime,      ly.lrev,      ly.in_off,
-                            ly.slot_link, ly.slot_src, ly.slot_time,  ly.slot_cum,  ly.dest_pairs,
-                            ly.wave_dest, ly.wave_part, ly.group_masks, const_cast<uint32_t *>(ly.sw.grp),
-                            ly.poll_off,  ly.poll,     ly.pub_off,    ly.out_off,   ly.out_dst,
-                            ly.slot_out};
+    // (null: not in this plan's layout)
+    void *dst[IMG_PARTS] = {ly.lsrc,      ly.ldst,     ly.ltime,     ly.lrev,      ly.in_off,  ly.slot_link,
+                            ly.slot_src,  ly.slot_time, ly.slot_cum, ly.dest_pairs, ly.group_masks,
+                            const_cast<uint32_t *>(ly.sw.grp),
+                            ly.poll_off,  ly.poll,     ly.pub_off,   ly.out_off,   ly.out_dst, ly.slot_out};
+    void **own = dst + IMG_COMMON + PLAN_PARTS * (c->use - c->plans);
+    own[0] = ly.wave_dest;
+    own[1] = ly.wave_part;
+    own[2] = const_cast<uint32_t *>(ly.sw.blk);
     for (int k = 0; k < IMG_PARTS; k++)
-        if (c->img_len[k])
+        if (c->img_len[k] && dst[k])
             HIP_OR_FAIL(c, hipMemcpyAsync(dst[k], c->pin_img + c->img_off[k], c->img_len[k], hipMemcpyHostToDevice, st));
     const size_t bm = (size_t)c->N * c->sz.W * sizeof(uint64_t);
     if (bm) {
@@ -1402,6 +1426,7 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
 {
     c->have_result = false;
     HIP_OR_FAIL(c, hipSetDevice(c->device));
+    const Plan &pl = *c->use;
     hipStream_t st = c->stream;
     HIP_OR_FAIL(c, hipEventRecord(c->ev[0], st));
     if (!c->uploaded) {
@@ -1421,16 +1446,16 @@ static pccl_status synthesize_bound(pccl_ctx *c, uint64_t *n_sends, uint32_t *co
         // both kernels are queued; the check picks the one that runs and the
         // other returns at once
         if (c->sw_nuni) HIP_OR_FAIL(c, launch_unicast_check(c->ly, c->sz, st, c->sw_nuni));
-        HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, c->sw_grid));
-        HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
-    } else if (c->sw_cols) {
-        HIP_OR_FAIL(c, launch_match_cols(c->ly, c->sz, st, c->sw_grid));
+        HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, pl.sw_grid));
+        HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, pl.grid, pl.wpb, pl.mirror, !pl.split.empty()));
+    } else if (pl.sw_cols) {
+        HIP_OR_FAIL(c, launch_match_cols(c->ly, c->sz, st, pl.sw_grid));
     } else if (c->sw_active) {
-        HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, c->sw_grid));
-    } else if (c->nbr) {
-        HIP_OR_FAIL(c, launch_match_nbr(c->ly, c->sz, st, c->grid, c->wpb, c->nbr_lds, c->nbr_spread));
+        HIP_OR_FAIL(c, launch_match_sw(c->ly, c->sz, st, pl.sw_grid));
+    } else if (pl.nbr) {
+        HIP_OR_FAIL(c, launch_match_nbr(c->ly, c->sz, st, pl.grid, pl.wpb, pl.nbr_lds, pl.nbr_spread));
     } else {
-        HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, c->grid, c->wpb, c->mirror, !c->split.empty()));
+        HIP_OR_FAIL(c, launch_match(c->ly, c->sz, st, pl.grid, pl.wpb, pl.mirror, !pl.split.empty()));
     }
     HIP_OR_FAIL(c, hipEventRecord(c->ev[2], st));
     bool out_queued = true;
@@ -1722,8 +1747,8 @@ pccl_status pccl_get_kernel(pccl_ctx *c, uint32_t *kernel, uint32_t *pruned)
     if (!c) return PCCL_EINVAL;
     GUARD_BEGIN
     if (!result_alive(c)) return fail(c, PCCL_ESTATE, c->have_result ? "the static scratch holding this schedule was reused" : "no schedule");
-    if (kernel) *kernel = c->ran_sw ? (c->sw_cols ? 3u : 2u) : (c->nbr ? 1u : 0u);
-    if (pruned) *pruned = c->nbr_prune ? 1u : 0u;
+    if (kernel) *kernel = c->ran_sw ? (c->use->sw_cols ? 3u : 2u) : (c->use->nbr ? 1u : 0u);
+    if (pruned) *pruned = c->use->prune ? 1u : 0u;
     return PCCL_OK;
     GUARD_END(c)
 }
