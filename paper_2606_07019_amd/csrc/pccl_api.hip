@@ -759,7 +759,7 @@ bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
     if (c->sw_active || c->D == 0 || c->L == 0 || c->C > NBR_MAX_CHUNKS) return false;
     uint32_t tmax = 0;
     for (uint32_t t : c->T) tmax = std::max(tmax, t);
-    if (tmax / NBR_MAX_RATIO > c->tmin) return false;
+    if ((uint64_t)tmax > (uint64_t)NBR_MAX_RATIO * c->tmin) return false;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus <= 0)
         return false;

@@ -32,11 +32,11 @@ def _complete(n):
     return W.make_topology(n, 0, [(i, j) for i in range(n) for j in range(n) if i != j], 500, 50)
 
 
-def _slow_link(ratio):
-    """An 8-ring whose links take 1,000 ns but one pair that takes ratio times
+def _slow_link(ratio, fast=1000, chunk=100):
+    """An 8-ring whose links take `fast` ns but one pair that takes ratio times
     as long: the kernel is chosen up to a factor of 9."""
     pairs = [(i, (i + s) % 8) for i in range(8) for s in (1, 7)]
-    alpha = [900 + (ratio - 1) * 1000 * ({a, b} == {3, 4}) for a, b in pairs]
+    alpha = [fast - chunk + (ratio - 1) * fast * ({a, b} == {3, 4}) for a, b in pairs]
     return W.make_topology(8, 0, pairs, alpha, 1)
 
 
@@ -70,6 +70,9 @@ CASES = {
     "slow link 10": lambda: _generic("slow10", _slow_link(10), 60, 100, 4, 22),
     "slow link 64": lambda: _generic("slow64", _slow_link(64), 60, 100, 4, 11),
     "slow link 65": lambda: _generic("slow65", _slow_link(65), 60, 100, 4, 12),
+    # the same bound where the fastest link takes 1 ns
+    "slow link 9 of 1 ns": lambda: _generic("fast9", _slow_link(9, 1, 1), 60, 1, 4, 24),
+    "slow link 10 of 1 ns": lambda: _generic("fast10", _slow_link(10, 1, 1), 60, 1, 4, 24),
     # four waves per workgroup, and one device too many for them
     "mesh 32x32": lambda: _generic("mesh1024", W.mesh2d(32, 32), 600, 4096, 6, 13),
     "mesh 41x25": lambda: _generic("mesh1025", W.mesh2d(41, 25), 600, 4096, 6, 14),
@@ -82,7 +85,7 @@ CASES = {
 
 
 # the kernel expected on each side of its rule, and where polled entries are pruned
-WINDOWED = {"slow link 10", "slow link 64", "slow link 65", "mesh 41x25"}
+WINDOWED = {"slow link 10", "slow link 10 of 1 ns", "slow link 64", "slow link 65", "mesh 41x25"}
 PRUNED = {"complete 10", "digraph 40 degree 9", "digraph 90 degree 9", "rail 12x8 generic", "rail 13x8", "rail 64x4"}
 
 
