@@ -749,11 +749,14 @@ void build_poll(pccl_ctx *c)
 // fastest, neighbour-stepped and windowed, us: 64-ring, 16 chunks per NPU,
 // r 8 5,288 and 7,422, r 16 9,703 and 7,307; 5x5x8 torus with axes 1, r/2 and
 // r, r 8 2,329 and 2,762, r 12 3,260 and 2,851; 9x5 rail cluster with uplinks
-// r times as slow, r 8 562 and 703, r 12 716 and 700.  It takes at
-// most one wave per SIMD: with several workgroups per compute unit (2,200
-// devices, three workgroups of three waves) a wait on a neighbour's entry ran
-// into the spin limit, which reading has not explained; such networks stay
-// with the windowed kernel.
+// r times as slow, r 8 562 and 703, r 12 716 and 700.  It takes one
+// workgroup per compute unit, so at most one wave per SIMD.  With three (2,200
+// devices of a mesh, a third of the unit's LDS each) a wait on a neighbour's
+// entry ran into the spin limit: 54,608 bytes are 27 of the 80 blocks of 2,048
+// in which LDS is given out, so three do not fit, although the occupancy
+// query, which divides bytes, answers three; a workgroup that is not resident
+// publishes nothing.  (A model of the protocol on that mesh stops when a third
+// of the workgroups does not run, and only then.)
 bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
 {
     if (c->sw_active || c->D == 0 || c->L == 0 || c->C > NBR_MAX_CHUNKS) return false;
