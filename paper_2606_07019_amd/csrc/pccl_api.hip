@@ -814,9 +814,19 @@ bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
     }
     if (!spread) return false;
     pl.nbr_spread = spread;
-    // worth its setup (0.03-0.06 ms) where some device polls several entries
-    // per lane; the relations are masks over a device's out-links
-    pl.prune = c->max_poll > 64 && c->max_out <= 64;
+    // Pruning costs 0.02-0.1 ms of setup (0.2 ms on the 512-NPU rail cluster)
+    // and is worth it where some device polls three entries per lane or more,
+    // over many windows.  Whole calls, us, without and with: All-to-Alls of
+    // rail clusters 18x8 (126 entries) 1,035 and 1,012, 20x8 (140) 1,148 and
+    // 1,095, 48x4 (144) 1,433 and 1,266, 64x8 (448) 4,576 and 3,413; 20x8
+    // All-Gather of 12 NPUs 3,597 and 3,041; 400-NPU digraph of degree 12 882
+    // and 825.  Fewer entries: 16x8 (112) 926 and 954, 32x4 (96) 935 and 972.
+    // Fewer chunks: 16x8 All-Gather, 128 chunks, 277 and 308, 10 NPUs with all
+    // links, 10 chunks, 114 and 139; 20 such, 300 chunks each, 1,239 and 1,279.
+    // (It loses up to 4 % above both lines too where nothing can be dropped:
+    // 14 NPUs with all links, 400 chunks each, 1,227 and 1,284.)
+    // (The relations are masks over a device's out-links.)
+    pl.prune = c->max_poll > 128 && c->C > 4096 && c->max_out <= 64;
     pl.wpb = (int)w;
     pl.grid = (int)grid;
     pl.alone = alone;
@@ -860,7 +870,12 @@ bool plan_switch_columns(pccl_ctx *c, Plan &pl)
     for (uint32_t i = 0; i < c->S; i++)
         if (limited(c->N + i) && n_out[c->N + i] > 64) return false;
     if (c->pub_off[c->D] >= (1u << 22)) return false;
-    pl.prune = c->max_poll > 64 && c->max_out <= 64;
+    // (the group's entries are polled by all of its threads, so fewer of them
+    // pay sooner than above; whole calls, us, without and with: All-to-Alls of
+    // rail clusters 6x12 2,973 and 2,922, 12x8 6,680 and 6,730, 16x8 11,596 and
+    // 11,349, 32x8 16,795 and 16,041, 64x8 27,300 and 25,393; with few chunks
+    // it costs: All-Gathers of 6x12 449 and 478, 16x8 559 and 587)
+    pl.prune = c->max_poll > 64 && c->C > 4096 && c->max_out <= 64;
     pl.sw_grid = (int)c->sw_groups;
     pl.sw_cols = true;
     return true;

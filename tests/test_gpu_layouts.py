@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 # collectives whose layout over columns is the larger one: 102,400 polled
 # entries; a 64-bit mask per limited switch and chunk against a 32-bit count
 CASES = {
-    "plain": (lambda: _generic("digraph400", _digraph(400, 16, 3), 300, 20000, 4, 3), "neighbour", "windowed"),
+    "plain": (lambda: _generic("digraph400", _digraph(400, 16, 3), 4200, 20000, 2, 3), "neighbour", "windowed"),
     "switch": (lambda: W.Workload("rail9", W.with_switch_model(W.switch2level(9, 5), 7, 1),
                                   W.a2a_k_bitmaps(45, 5, 9000), 8), "switch columns", "switch rows"),
 }

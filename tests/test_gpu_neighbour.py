@@ -53,13 +53,21 @@ CASES = {
     # 56 and 72 polled entries per device: one and several per lane
     "complete 9": lambda: _generic("complete9", _complete(9), 200, 10000, 8, 5),
     "complete 10": lambda: _generic("complete10", _complete(10), 200, 10000, 9, 6),
-    # more than 64 polled entries, pruned to those a needed chunk can come through: one-way and switched networks,
-    # chunks with one and with many destinations, a chunk that several neighbours can offer
+    # several polled entries per lane in one-way and switched networks
     "digraph 40 degree 9": lambda: _generic("digraph40", _digraph(40, 9, 18), 1200, 20000, 30, 18),
     "digraph 90 degree 9": lambda: _generic("digraph90", _digraph(90, 9, 19), 2500, 20000, 2, 19),
     "rail 12x6 all-gather": lambda: W.Workload("rail12ag", W.switch2level(12, 6), W.all_gather(72, range(72), 5, 9000), 20),
     "rail 12x8 generic": lambda: _generic("rail12g", W.switch2level(12, 8), 3000, 7000, 9, 21),
     "rail 13x8": lambda: W.Workload("rail13x8", W.switch2level(13, 8), W.a2a_bitmaps(104, 8192), 22),
+    # more than 128 polled entries and 4,096 chunks, pruned to those a needed chunk can come through: one-way and switched
+    # networks, chunks with one and with many destinations, a chunk that several neighbours can offer; both bounds
+    "digraph 40 degree 13": lambda: _generic("digraph40p", _digraph(40, 13, 25), 4200, 20000, 30, 25),
+    "digraph 90 degree 12": lambda: _generic("digraph90p", _digraph(90, 12, 26), 4100, 20000, 2, 26),
+    "rail 20x8 generic": lambda: _generic("rail20g", W.switch2level(20, 8), 4200, 7000, 9, 27),
+    "rail 20x8 all-gather": lambda: W.Workload("rail20ag", W.switch2level(20, 8), W.all_gather(160, range(0, 160, 14), 342, 9000), 28),
+    "complete 13, 4,096": lambda: _generic("c13a", _complete(13), 4096, 10000, 6, 29),
+    "complete 13, 4,097": lambda: _generic("c13b", _complete(13), 4097, 10000, 6, 29),
+    "rail 18x8": lambda: W.Workload("rail18", W.switch2level(18, 8), W.a2a_bitmaps(144, 8192), 30),
     # 64 and 65 chunks (one and two row words), 4,096 and 4,160 (one and two summary levels), all needed everywhere
     "ring 4 x 16": lambda: W.Workload("r4", W.ring(4), W.all_gather(4, range(4), 16, 1 << 14), 7),
     "ring 5 x 13": lambda: W.Workload("r5", W.ring(5), W.all_gather(5, range(5), 13, 1 << 14), 8),
@@ -86,7 +94,8 @@ CASES = {
 
 # the kernel expected on each side of its rule, and where polled entries are pruned
 WINDOWED = {"slow link 10", "slow link 10 of 1 ns", "slow link 64", "slow link 65", "mesh 41x25"}
-PRUNED = {"complete 10", "digraph 40 degree 9", "digraph 90 degree 9", "rail 12x8 generic", "rail 13x8", "rail 64x4"}
+PRUNED = {"digraph 40 degree 13", "digraph 90 degree 12", "rail 20x8 generic", "rail 20x8 all-gather", "complete 13, 4,097",
+          "rail 64x4"}
 
 
 @pytest.mark.parametrize("name", list(CASES))

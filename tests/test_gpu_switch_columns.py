@@ -44,21 +44,23 @@ CASES = {
     "fan 65": lambda b, u: _limited(_fan(65), b, u),
     # more than 4,096 columns per device: two summary levels
     "star 3 long": lambda b, u: _limited(W.Workload("star3", W.star(3), W.all_gather(3, range(3), 2500, 4096), 3), b, u),
-    # a group that polls 1,584 entries (several per thread, pruned) and one of 7,220 (too many: bitmap rows)
+    # a group that polls 1,584 entries (several per thread; pruned over 4,096 chunks) and one of 7,220 (too many: bitmap rows)
     "meshed star 12": lambda b, u: _limited(_generic("mstar12", _meshed_star(12), 400, 9000, 8, 4), b, u),
+    "meshed star 12 long": lambda b, u: _limited(_generic("mstar12l", _meshed_star(12), 4100, 9000, 4, 10), b, u),
     "meshed star 20": lambda b, u: _limited(_generic("mstar20", _meshed_star(20), 300, 9000, 8, 5), b, u),
     # two limited switches in one group: chunks come in over both, or past both
     "two switches 9": lambda b, u: _limited(_generic("two9", _two_switches(9), 250, 9000, 6, 6), b, u),
     "two switches 30": lambda b, u: _limited(_generic("two30", _two_switches(30), 900, 9000, 20, 7), b, u),
     # a group per rail
     "rail 9x5": lambda b, u: _limited(W.Workload("rail9", W.switch2level(9, 5), W.all_to_all(45, range(45), 9000), 8), b, u),
+    "rail 6x12 a2a": lambda b, u: _limited(W.Workload("rail6a", W.switch2level(6, 12), W.a2a_bitmaps(72, 9000), 11), b, u),
     "rail 6x12": lambda b, u: _limited(W.Workload("rail6", W.switch2level(6, 12), W.all_gather(72, range(72), 3, 9000), 9), b, u),
 }
 
 
 # the kernel expected on each side of its rule, and where polled entries are pruned
 ROWS = {"fan 65", "meshed star 20"}
-PRUNED = {"meshed star 12", "rail 6x12"}
+PRUNED = {"meshed star 12 long", "rail 6x12 a2a"}
 
 
 # buffers of one place, of part of a wave, and of more than 64 places (looked up 64 at a time)
