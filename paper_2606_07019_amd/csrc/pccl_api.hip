@@ -842,8 +842,14 @@ bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
 // group at most GRP_MAX_ITEMS polled entries (registers), and a buffer limit
 // binds: where only the no-multicast rule may, the plain kernel over bitmap
 // rows is queued beside the group kernel and both read one layout.  Within
-// these bounds the columns were the faster side wherever both were measured
-// (rail clusters of 128 and 512 NPUs: 18.8 and 11.3 ms, 57.5 and 25.6).
+// these bounds the columns were the faster side in all of 75 networks measured
+// (stars of 4 to 64 NPUs, rail clusters of 4x2 to 64x8, All-to-All and
+// All-Gather, 1 to 200 places, with and without multicast) by 1.1 to 4.7:
+// rows and columns, ms, 512-NPU All-to-All, 64 places 57.7 and 25.4; 16x8, 4
+// places 19.2 and 11.4; star of 8 NPUs, All-Gather, unicast, 16 places 0.68 and
+// 0.62.  GRP_MAX_ITEMS is what six registers of each thread hold, counted
+// before pruning; no kernel over columns takes what lies beyond (48x10, 4,800
+// entries: 53.3 ms over rows), so that side is not measured.
 bool plan_switch_columns(pccl_ctx *c, Plan &pl)
 {
     if (!c->sw_active || c->sw_gate || c->C == 0 || c->C > NBR_MAX_CHUNKS) return false;
