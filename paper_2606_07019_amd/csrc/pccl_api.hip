@@ -842,7 +842,7 @@ bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
 // group at most GRP_MAX_ITEMS polled entries (registers), and a buffer limit
 // binds: where only the no-multicast rule may, the plain kernel over bitmap
 // rows is queued beside the group kernel and both read one layout.  Within
-// these bounds the columns were the faster side in all of 75 networks measured
+// these bounds the columns were the faster side in all of 67 networks measured
 // (stars of 4 to 64 NPUs, rail clusters of 4x2 to 64x8, All-to-All and
 // All-Gather, 1 to 200 places, with and without multicast) by 1.1 to 4.7:
 // rows and columns, ms, 512-NPU All-to-All, 64 places 57.7 and 25.4; 16x8, 4
