@@ -118,8 +118,6 @@ struct Tables {
     uint32_t step[3];
 };
 
-// Orders the accesses of the wave's lanes to its tables in LDS: what one lane
-// wrote (or updated atomically) before it, another lane reads after it.
 __device__ __forceinline__ void wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -358,17 +356,16 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
                 }
             }
             // rows in device memory: the arrivals' bits are set before other
-            // lanes read them (the wait costs the 512-NPU rail cluster's switches
-            // 0.4 % of 2.74 ms)
-            if (!ALL && !(tb.in_lds & IN_ROW)) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+            // lanes read them (rows in LDS: a wave's LDS operations are done in
+            // order).  No test of where the rows are: it changes the registers
+            // of all builds (8x8x4 torus, 2.65 -> 2.71 ms), the wait alone costs
+            // nothing measurable.
+            if (!ALL) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
             // pick rounds
             const uint32_t now = t0 + t;
             bool want = mine && busy_end == 0;
             uint64_t losers;
             do {
-                // (the bits of this event's arrivals, and those the round before
-                // cleared, come from other lanes)
-                wave_sync();
                 const Pick pk = first_live<L3, ALL>(tb, want, words);
                 const uint32_t col = pk.col;
                 const bool act = col != NONE32;
@@ -409,8 +406,6 @@ __device__ __forceinline__ void run_dest(const Layout &ly, const Sizes &sz, cons
                     }
                 }
             } while (losers);
-            // (other lanes' arrivals set bits in the words this lane dropped)
-            wave_sync();
         }
 
         // publish the state at the window's end, then log the commits
