@@ -59,6 +59,7 @@ struct pccl_ctx {
     uint32_t N = 0, S = 0, D = 0, L = 0;
     std::vector<uint32_t> src, dst, alpha, bw;
     std::vector<uint32_t> in_off, slot_link, slot_src, slot_cum, dest_pairs, rev;
+    std::vector<uint32_t> heavy_first;     // the devices, most arrival pairs, then most in-links first
     std::vector<uint32_t> pub_off;         // where each device's published link entries start
     std::vector<uint32_t> poll_off, poll;  // entries each device polls in the neighbour-stepped matcher
     bool poll_built = false;               // the lists match the topology
@@ -557,15 +558,6 @@ pccl_status deal_switch_groups(pccl_ctx *c, Plan &pl)
     return PCCL_OK;
 }
 
-// Heaviest devices first: most arrival pairs, then most in-links.
-void deal_order(const pccl_ctx *c, std::vector<uint32_t> &v)
-{
-    std::stable_sort(v.begin(), v.end(), [&](uint32_t a, uint32_t b) {
-        if (c->dest_pairs[a] != c->dest_pairs[b]) return c->dest_pairs[a] > c->dest_pairs[b];
-        return c->in_off[a + 1] - c->in_off[a] > c->in_off[b + 1] - c->in_off[b];
-    });
-}
-
 // Destinations of the matching kernel's waves.  Split destinations first,
 // each taking a whole workgroup (wave p is part p; parts past the last are
 // empty and only take part in the part barriers).  The others heaviest first
@@ -580,9 +572,8 @@ void deal_destinations(const pccl_ctx *c, Plan &pl)
     for (uint32_t d : pl.split) is_split[d] = 1;
     std::vector<uint32_t> byweight;
     byweight.reserve(D);
-    for (uint32_t v = 0; v < D; v++)
+    for (uint32_t v : c->heavy_first)
         if (!is_split[v]) byweight.push_back(v);
-    deal_order(c, byweight);
     // the `alone` heaviest unsplit destinations take wave 0 of the next
     // workgroups (one pass, by construction of the grid)
     const uint32_t hs = (uint32_t)pl.split.size(), ha = pl.alone, h = hs + ha;
@@ -781,7 +772,6 @@ bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
     // another in 0.72-0.93 us, and that is most of a window.
     uint32_t w = 0, alone = 0, spread = 0;
     uint64_t grid = 0;
-    std::vector<uint32_t> order;
     for (uint32_t sp : {NBR_XCDS, 1u}) {
         const uint32_t room = (uint32_t)cus / sp;
         if (c->D > room * MATCH_WAVES) continue;
@@ -795,13 +785,11 @@ bool plan_nbr(pccl_ctx *c, Plan &pl, size_t lds_cu, uint32_t n_heavy)
         if (grid * sp > MAX_MATCH_GRID) continue;
         // the worst case of the devices that share a workgroup, and of the
         // others (the heavy devices come first in the deal)
-        if (order.empty()) {
-            order.resize(c->D);
-            std::iota(order.begin(), order.end(), 0u);
-            deal_order(c, order);
-        }
         uint32_t n_shared = 0;
-        for (uint32_t i = alone; i < c->D; i++) n_shared = std::max(n_shared, c->in_off[order[i] + 1] - c->in_off[order[i]]);
+        for (uint32_t i = alone; i < c->D; i++) {
+            const uint32_t v = c->heavy_first[i];
+            n_shared = std::max(n_shared, c->in_off[v + 1] - c->in_off[v]);
+        }
         const size_t share = w > 1 ? (lds_cu / w) & ~size_t(15) : lds_cu;
         if (worst(n_shared) > share || worst(c->max_in) > (alone ? lds_cu : share)) continue;
         // (the tables of a device grow with the chunks: with a share of less
@@ -1261,6 +1249,12 @@ pccl_status pccl_load_topology(pccl_ctx *c, uint32_t n_npus, uint32_t n_switches
     c->slot_cum.swap(slot_cum);
     c->dest_pairs.swap(dest_pairs);
     c->rev.swap(rev);
+    c->heavy_first.resize(D);
+    std::iota(c->heavy_first.begin(), c->heavy_first.end(), 0u);
+    std::stable_sort(c->heavy_first.begin(), c->heavy_first.end(), [&](uint32_t a, uint32_t b) {
+        if (c->dest_pairs[a] != c->dest_pairs[b]) return c->dest_pairs[a] > c->dest_pairs[b];
+        return c->in_off[a + 1] - c->in_off[a] > c->in_off[b + 1] - c->in_off[b];
+    });
     c->sw_buf.assign(n_switches, 0u);
     c->sw_uni.assign(n_switches, 0u);
     c->sw_model = c->sw_built = c->sw_active = false;
