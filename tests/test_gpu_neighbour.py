@@ -46,8 +46,10 @@ CASES = {
     "one-way ring 70": lambda: _generic("ring70", W.ring(70, bidirectional=False), 300, 4096, 4, 2),
     "digraph 60 degree 2": lambda: _generic("digraph60", _digraph(60, 2, 3), 500, 20000, 6, 3),
     "digraph 300 degree 3": lambda: _generic("digraph300", _digraph(300, 3, 4), 3000, 20000, 5, 4),
-    # two NPUs that only follow each other's progress, over thousands of windows (either may be ahead by up to three)
+    # two NPUs that only follow each other's progress (either may be ahead by up to three windows), also over more windows
+    # than the 4,096 that a tag counts
     "pair": lambda: _generic("pair", W.make_topology(2, 0, [(0, 1), (1, 0)], [500, 700], 10), 6000, 4096, 1, 16),
+    "pair, long": lambda: _generic("pairl", W.make_topology(2, 0, [(0, 1), (1, 0)], [500, 700], 10), 20000, 4096, 1, 31),
     # leaves: an NPU whose only neighbour follows its progress
     "star 3": lambda: W.Workload("star3", W.star(3), W.all_gather(3, range(3), 300, 4096), 17),
     # 56 and 72 polled entries per device: one and several per lane
